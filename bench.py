@@ -120,7 +120,16 @@ def gather_launches(card, trace_groups, gather_batch_kb, elem=4):
     return -(-tpg // batch)
 
 
-def kernel_work(name, card, n_off, trace_groups, gather_batch_kb=4096, elem=4):
+def moments_of(card, kernel, products=2):
+    """Moments per sample that a sweep kernel of a bench workload carries (0:
+    it sweeps the fine grid): the 500 kHz pulse needs 5 at 20 MHz and 6 at 10
+    MHz.  With 16-bit storage only the forward runs as moments."""
+    if products != 2 or any(card.medium.atten) or (card.acq.storage and kernel not in ("splat", "conv")):
+        return 0
+    return {20e6: 5, 10e6: 6}.get(card.acq.fs, 0)
+
+
+def kernel_work(name, card, n_off, trace_groups, gather_batch_kb=4096, elem=4, moments=0):
     """Algorithmic work of one launch and its bound.
 
     conv / corr: the polyphase convolution and correlation, 2 M Q L_h flop per
@@ -131,12 +140,24 @@ def kernel_work(name, card, n_off, trace_groups, gather_batch_kb=4096, elem=4):
     of which also reads the leg table and the transmittances and writes the
     trace groups' partial images (the first launch writes them, later ones
     read and write them): the per-launch figure is that total over the
-    launches."""
+    launches.  With `moments` R > 0 the sweeps carry R moments a sample in
+    place of the Q fine positions: 2 M R L_h flop per trace; the splat reads
+    its records (R + 1 words per receiver, row and relative column) in place
+    of the leg table and the adjoint has one gather launch."""
     acq = card.acq
     P, K, M, Q = card.array.n_scans, card.array.n_rx, acq.n_samples, acq.oversample
     lh = int(round(acq.t_win * acq.fs))
     N, nz = card.n_voxels, card.grid.nz
     legs = nz * n_off * 16
+    if moments:
+        fine = P * K * M * moments * 4
+        pitch = round((card.array.tx_x[1] - card.array.tx_x[0]) / card.grid.dx) if P > 1 else 1
+        if name in ("conv", "corr"):
+            return 2.0 * P * K * M * moments * lh, "mfma"
+        if name == "splat":
+            return float(K * nz * (card.grid.nx + pitch * (P - 1)) * 4 * (moments + 1) + 4 * N + fine), "hbm"
+        if name == "gather":
+            return float(fine + legs + 4 * nz + 4 * N * trace_groups), "hbm"
     fine = P * K * M * Q * elem
     if name in ("conv", "corr"):
         return 2.0 * P * K * M * Q * lh, ("mfma" if Q in (32, 64) else "alu")
@@ -177,7 +198,7 @@ PEAK_MFMA = {4: 157.3e12, 2: 2.5e15}  # dense matrix peak by element bytes: FP32
 PIECE_PRODUCTS = 6  # bf16 piece products per FP32 product (umbir_tuning.products = 2)
 
 
-def roofline(name, prof, steps, card, n_off, trace_groups, gather_batch_kb=4096, elem=4, products=1):
+def roofline(name, prof, steps, card, n_off, trace_groups, gather_batch_kb=4096, elem=4, products=1, moments=0):
     """One kernel's achieved rate against its bound.  With products = 2 the
     FP32 convolution and correlation run on the bf16 matrix cores, six piece
     products per FP32 product: the record then counts those bf16 flops
@@ -186,7 +207,7 @@ def roofline(name, prof, steps, card, n_off, trace_groups, gather_batch_kb=4096,
         return None
     launches, ms = prof[name]
     avg_s = ms / launches / 1e3
-    amount, bound = kernel_work(name, card, n_off, trace_groups, gather_batch_kb, elem)
+    amount, bound = kernel_work(name, card, n_off, trace_groups, gather_batch_kb, elem, moments)
     if bound is None:
         return None
     pieces = bound == "mfma" and elem == 4 and products == 2
@@ -295,7 +316,9 @@ def precision_section(umbir, torch, dev, with_parity):
         elem = 4 if st == umbir.STORAGE_F32 else 2
         tn = gm.tuning()
         kb = tn["gather_batch_kb"]
-        kern = {k: roofline(k, prof, 3, card, gm.n_off, gm.trace_groups, kb, elem, tn["products"])
+        mom = {k: moments_of(card, k, tn["products"]) for k in ("splat", "conv", "corr", "gather")}
+        kern = {k: roofline(k, prof, 3, card, gm.n_off, gm.trace_groups, kb, 4 if mom[k] else elem, tn["products"],
+                            mom[k])
                 for k in ("splat", "conv", "corr", "gather")}
         dom = max(kern, key=lambda k: kern[k]["avg_launch_us"] * kern[k]["launches_per_step"] if kern[k] else -1)
         res = {"A_evals_per_s": triples / t_a, "AT_evals_per_s": triples / t_at,
@@ -482,8 +505,9 @@ def main():
     # kernel from the profiled untimed step
     tg, kb = gm.trace_groups, tuning["gather_batch_kb"]
     pr = tuning["products"]
-    kernels = {k: roofline(k, prof_all, 1, card, gm.n_off, tg, kb, products=pr) for k in ("splat", "conv", "corr", "gather")}
-    roof = roofline(dname, prof, args.steps, card, gm.n_off, tg, kb, products=pr)
+    kernels = {k: roofline(k, prof_all, 1, card, gm.n_off, tg, kb, products=pr, moments=moments_of(card, k, pr))
+               for k in ("splat", "conv", "corr", "gather")}
+    roof = roofline(dname, prof, args.steps, card, gm.n_off, tg, kb, products=pr, moments=moments_of(card, dname, pr))
     if roof is not None:  # launches per step from the fully profiled step; the timed ones are a sample
         roof["launches_per_step"] = prof_all[dname][0]
         roof["timed_launches"] = prof[dname][0]

@@ -339,7 +339,12 @@ typedef struct {
 int umbir_get_dims(const umbir_geometry* geom, umbir_dims* out);
 
 /* Launch and tile shapes of the sweeps, tunable per problem shape.  None
- * changes a result beyond rounding order, nor any memory size:
+ * changes a result beyond rounding order, nor any memory size.  Where the
+ * factored form with bf16-piece products (both defaults) runs as moments (FP32
+ * storage, one template, scan positions a constant whole number of voxels
+ * apart, Q >= 16 and a pulse that a polynomial of degree 7 or less follows over
+ * a sample period to 1e-8 of its peak), the launch and tile shapes and the
+ * gather's form concern the curvature pass only:
  *  splat_blocks     target workgroup count of the splat: the fine grid of each
  *                   trace is cut into ceil(splat_blocks / traces) chunks of at
  *                   least 1024 positions.  Results are bitwise identical for

@@ -12,6 +12,8 @@ import os
 import shutil
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -31,17 +33,24 @@ def sources():
 
 
 def build(verbose: bool = False) -> str:
-    """Compiles every source into libumbir.so (always rebuilds); returns its path."""
+    """Compiles every source (side by side) into libumbir.so (always rebuilds); returns its path."""
     tmp = LIB + ".tmp"
-    cmd = [hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"),
-           *sources(), "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
+    flags = [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
+             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+             "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc")]
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
+
+    with tempfile.TemporaryDirectory() as objs:
+        pairs = [(s, os.path.join(objs, os.path.basename(s) + ".o")) for s in sources()]
+        with ThreadPoolExecutor(max_workers=4) as pool:
+            list(pool.map(lambda p: run([hipcc(), *flags, "-c", p[0], "-o", p[1]]), pairs))
+        run([hipcc(), f"--offload-arch={ARCH}", "-fPIC", "-shared", *(o for _, o in pairs), "-o", tmp])
     os.replace(tmp, LIB)
     return LIB
 

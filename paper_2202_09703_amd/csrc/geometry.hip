@@ -505,6 +505,12 @@ size_t table_bytes(int nz, int n_off, int P, int K, int M, int Q, int Lh, int n_
          size_t(P) * K * sizeof(float) + att;
 }
 
+MomentInput moment_input(const umbir_problem* pb, const Derived& dv) {
+  return {pb->grid.nx,   pb->grid.nz, pb->array.n_scans, pb->array.n_rx, pb->acq.n_samples,
+          pb->acq.oversample, dv.Lh,  pb->acq.storage,   dv.n_gamma,     pb->acq.fs,
+          pb->acq.f_c,   pb->acq.sigma_t, pb->acq.t_win, dv.base.data()};
+}
+
 }  // namespace
 
 int fail(int status, const std::string& msg) {
@@ -570,7 +576,8 @@ size_t umbir_estimate_bytes(const umbir_problem* pb) {
                      pb->acq.n_samples, pb->acq.oversample, dv.Lh, dv.n_gamma) +
          (dv.n_gamma > 1 ? 0
                          : gather_window_bytes(pb->grid.nx, pb->grid.nz, long(pb->array.n_scans) * pb->array.n_rx,
-                                               long(pb->acq.n_samples) * pb->acq.oversample, pb->acq.storage));
+                                               long(pb->acq.n_samples) * pb->acq.oversample, pb->acq.storage)) +
+         moment_shape(moment_input(pb, dv)).table_bytes;
 }
 
 void umbir_geometry_free(umbir_geometry* G) {
@@ -579,7 +586,8 @@ void umbir_geometry_free(umbir_geometry* G) {
   (void)hipGetDevice(&cur);
   if (G->device >= 0) (void)hipSetDevice(G->device);
   void* ptrs[] = {G->legs, G->legs_t, G->tau, G->base, G->bank, G->h, G->habs, G->dbasis, G->dnorm, G->gmask,
-                  G->gunit, G->gunit_t, G->gwin};
+                  G->gunit, G->gunit_t, G->gwin, G->mom_start, G->mom_rec4, G->mom_rec_hi, G->mom_rec_off,
+                  G->mom_taps};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (cur >= 0) (void)hipSetDevice(cur);
@@ -822,12 +830,36 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
                  size_t(G->mask_blocks) * sizeof(unsigned long long), s, G->legs, G->gunit, G->n_off, G->base, G->P,
                  G->K, G->nx, G->voxels(), qs, MQ, NG - 1, G->mask_blocks, G->gmask);
   }
+  // the moment form's tables, where the geometry takes it
+  G->mom = moment_shape(moment_input(pb, dv));
+  int max_bin = 0;
+  if (G->mom.R) {
+    const MomentShape& ms = G->mom;
+    if ((st = alloc((void**)&G->mom_start, size_t(G->K) * (G->M + 1) * sizeof(int))) ||
+        (st = alloc((void**)&G->mom_rec4, ms.records * sizeof(float4))) ||
+        (st = alloc((void**)&G->mom_rec_hi, ms.records * (ms.R - 4) * sizeof(float))) ||
+        (st = alloc((void**)&G->mom_rec_off, ms.records * sizeof(unsigned))) ||
+        (st = alloc((void**)&G->mom_taps, size_t(ms.R) * 3 * ms.LT * sizeof(uint4))) ||
+        (st = build_moments(G, &max_bin, s)))
+      return bail(st);
+  }
   if (gam_dev) (void)hipFreeAsync(gam_dev, s);
   if (nodes_dev) (void)hipFreeAsync(nodes_dev, s);
   st = check_hip(hipGetLastError(), "geometry kernels");
   (void)hipFreeAsync(td_dev, s);
   const int st2 = check_hip(hipStreamSynchronize(s), "hipStreamSynchronize(build_geometry)");
   if (!st) st = st2;
+  if (!st && !moment_plan_fits(max_bin)) {  // the fine grid stays
+    G->bytes -= G->mom.table_bytes;
+    void* tables[] = {G->mom_start, G->mom_rec4, G->mom_rec_hi, G->mom_rec_off, G->mom_taps};
+    for (void* p : tables) (void)hipFree(p);
+    G->mom_start = nullptr;
+    G->mom_rec4 = nullptr;
+    G->mom_rec_hi = nullptr;
+    G->mom_rec_off = nullptr;
+    G->mom_taps = nullptr;
+    G->mom = MomentShape{};
+  }
   if (st) {
     umbir_geometry_free(G);
     return st;

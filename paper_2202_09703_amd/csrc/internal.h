@@ -168,6 +168,26 @@ struct Carve {
   }
 };
 
+// The moment form of a geometry (see moment.hip): R moments per sample (0: the
+// fine grid is kept), in planes of Ms samples; dense operand table of LT
+// entries per moment and piece; scan positions `pitch` voxels apart (reversed:
+// from right to left), relative columns rel0 .. rel0 + NR - 1, the image by
+// phase of the pitch in rows of Lq; 2^ls lanes per splat record; bytes of u
+// (or v) and of the whole workspace it needs; records and table bytes.
+struct MomentShape {
+  int R = 0, Ms = 0, LT = 0;
+  int pitch = 0, Lq = 0, NR = 0, rel0 = 0, ls = 0, reversed = 0;
+  size_t u_bytes = 0, work_bytes = 0, records = 0, table_bytes = 0;
+};
+
+// What decides it.
+struct MomentInput {
+  int nx, nz, P, K, M, Q, Lh, storage, n_gamma;
+  double fs, f_c, sigma_t, t_win;
+  const int* base;  // [P + P K] lattice bases
+};
+MomentShape moment_shape(const MomentInput& in);
+
 // Block-wide copy into LDS: store(i, load(i)) for i < n, with eight loads in
 // flight per thread.  The stores are branch-free (a slot past the end repeats
 // element n - 1, with its own value), so the compiler keeps every load of a
@@ -252,6 +272,14 @@ struct umbir_geometry {
   float* dnorm = nullptr;    // [P*K] squared norms of the columns of D
   int2* gwin = nullptr;      // [gather tiles][P*K] windowed gather's {first fine position, count} (or absent)
   int gather_form = 1;       // 1 row-wise gather, 2 windowed (needs gwin)
+  // the moment form (mom.R > 0): the splat's records sorted by sample per
+  // receiver, where each sample's begin, and the dense kernels' table
+  umbir::MomentShape mom;
+  int* mom_start = nullptr;         // [K][M + 1]
+  float4* mom_rec4 = nullptr;       // [records] coefficients 0 .. 3
+  float* mom_rec_hi = nullptr;      // [records][R - 4] the others
+  unsigned* mom_rec_off = nullptr;  // [records] offset in the image by phase
+  uint4* mom_taps = nullptr;        // [R][3][LT]
   size_t bytes = 0;
 
   int traces() const { return P * K; }
@@ -275,10 +303,13 @@ struct umbir_geometry {
                         : fine_grid_bytes();
   }
   // the fine-grid workspace: the grid(s), then the forward's prescaled image
-  // and the prescale blocks' maxima
+  // and the prescale blocks' maxima; the moment form's u or v and its image
+  // share the bytes
   size_t fine_bytes() const {
-    return grids_bytes() + ((size_t(nx) * nzp * 4 + 15) & ~size_t(15)) + 4 * umbir::kPrescaleBlocks;
+    const size_t fine = grids_bytes() + ((size_t(nx) * nzp * 4 + 15) & ~size_t(15)) + 4 * umbir::kPrescaleBlocks;
+    return fine > mom.work_bytes ? fine : mom.work_bytes;
   }
+  size_t prescale_max_offset() const { return grids_bytes() + ((size_t(nx) * nzp * 4 + 15) & ~size_t(15)); }
   size_t trace_bytes() const { return size_t(traces()) * M * elem(); }
   size_t taps_per_bin() const { return size_t(Q) * Lh; }
 };
@@ -305,7 +336,58 @@ struct CostFold {
   double* out;
 };
 
+#ifdef __HIPCC__
+// CostFold's sums by the first 256 threads of a block of at least 256; sh:
+// 256 doubles of LDS, free before and after.
+__device__ __forceinline__ void fold_cost(const CostFold& f, double* sh) {
+  const int t = threadIdx.x;
+  double v[2] = {0.0, 0.0};
+  if (t < 256) {
+    for (int i = t; i < f.n_ess; i += 256) v[0] += f.ess[i];
+    for (int i = t; i < f.n_p; i += 256) v[1] += f.pcost[i];
+  }
+  double r[2];
+  for (int k = 0; k < 2; ++k) {
+    if (t < 256) sh[t] = v[k];
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+      if (t < w) sh[t] += sh[t + w];
+      __syncthreads();
+    }
+    r[k] = sh[0];
+    __syncthreads();
+  }
+  if (t == 0) *f.out = r[0] * f.inv_2s2 + r[1];
+}
+#endif
+
+// Does the factored form with bf16-piece products (the default) run as
+// moments?  A caller that keeps state between calls (sessions) decides once.
+// FP32 storage only: with 16-bit storage the taps and the fine grid are held
+// in that type by contract, and the image of an adjoint or a reconstruction
+// (FP32) shows those roundings.  A forward alone may (forward_moments_on): its
+// result is rounded to the 16-bit type anyway, and comes out nearer the exact
+// one.
+bool moments_on(const umbir_geometry& G);
+bool forward_moments_on(const umbir_geometry& G);
+
+// The moment form's counterparts of run_forward and run_adjoint_partial.
+// in_place: the workspace holds x by phase already (run_phase_image, or the
+// prior update); with one scan position x itself is read and must be given.
+int run_phase_image(const umbir_geometry& G, const float* x, void* fine, hipStream_t s);
+float* moment_image(const umbir_geometry& G, void* fine);  // NULL with one scan position
+int run_forward_moments(const umbir_geometry& G, const float* x, void* out, const void* base, float sign,
+                        const float* g, void* fine, hipStream_t s, bool in_place, const CostFold* fold);
+int run_adjoint_moments(const umbir_geometry& G, const float* r, void* fine, float* partial, hipStream_t s);
+
+// Queues the building of the moment tables (allocated by the caller); the
+// largest number of records of one sample goes to *max_bin, and the tables
+// hold only if moment_plan_fits(*max_bin) once the stream was synchronized.
+int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s);
+bool moment_plan_fits(int max_bin);
+
 // y = base + sign * A x - g D   (base, g may be NULL; x NULL means all ones).
+// `mom` runs it as moments (never with abs_op, whose |h| is not smooth).
 // `abs_op` builds the operator from |W| and |h|.  Trace buffers (out, base) hold
 // the geometry's storage type; fine: G.fine_bytes() of workspace.  With
 // pre_max the workspace already holds tau x for this x (as
@@ -313,7 +395,7 @@ struct CostFold {
 // is the largest of the n_pre_max words at pre_max, and x is not read.  With
 // fold, its cost is also computed (before any of the forward's writes).
 int run_forward(const umbir_geometry& G, const float* x, void* out, const void* base,
-                float sign, const float* g, bool abs_op, void* fine, hipStream_t s,
+                float sign, const float* g, bool abs_op, bool mom, void* fine, hipStream_t s,
                 const unsigned* pre_max = nullptr, int n_pre_max = 0, const CostFold* fold = nullptr);
 
 // Can the direct form serve this geometry (FP32 storage, one template, the
@@ -326,12 +408,12 @@ int run_prescale_blocks(const umbir_geometry& G, const float* x, void* fine, uns
                         hipStream_t s);
 
 // out = scale * A^T r (r in the storage type).  partial: trace_groups * N floats.
-int run_adjoint(const umbir_geometry& G, const void* r, float* out, float scale, bool abs_op,
+int run_adjoint(const umbir_geometry& G, const void* r, float* out, float scale, bool abs_op, bool mom,
                 void* fine, float* partial, hipStream_t s);
 
 // A^T r left as the trace_groups partial images (partial[g][v]); their sum in
 // the order g = 0, 1, ... is run_adjoint's result with scale 1.
-int run_adjoint_partial(const umbir_geometry& G, const void* r, bool abs_op, void* fine, float* partial,
+int run_adjoint_partial(const umbir_geometry& G, const void* r, bool abs_op, bool mom, void* fine, float* partial,
                         hipStream_t s);
 
 // y = D g (or y += D g), y in the storage type.
@@ -373,6 +455,14 @@ struct BatchProb {
   int groups, tpg, gbatch, vpb;     // gather: trace groups, traces per group and launch, voxels per block
                                     // (row-wise) or voxel tiles per block (windowed)
   const int2* gwin;                 // windowed gather: the geometry's window table
+  // moment form (mom.R > 0: the problem runs the moment stages instead)
+  MomentShape mom;
+  const int* mom_start;
+  const float4* mom_rec4;
+  const float* mom_rec_hi;
+  const unsigned* mom_rec_off;
+  const uint4* mom_taps;
+  int mom_tiles;                    // 32-sample tiles per block of its dense kernels
   int nblk;                         // prior-update blocks
   // session state
   const float* y;
@@ -394,7 +484,10 @@ struct BatchProb {
 };
 
 // Stages of one iteration, in launch order.
-enum BatchStage { kStPrescale = 0, kStSplat, kStConv, kStGstep, kStCorr, kStGather, kStGatherW, kStPrior, kStCost, kStages };
+enum BatchStage {
+  kStPrescale = 0, kStSplat, kStMSplat, kStConv, kStMConv, kStGstep, kStCorr, kStMCorr, kStGather, kStGatherW,
+  kStMGather, kStPrior, kStCost, kStages
+};
 
 // A stage's launch: its items, grid (blocks walk the items with a stride of
 // the grid) and dynamic LDS bytes.
@@ -409,7 +502,11 @@ struct StageLaunch {
 // and appends problem pi's items of the sweep stages (splat, conv, corr,
 // gather) to items[stage]; lds[stage] grows to what the problem needs.
 // Gather items carry the index of their launch (batch of traces) in .w.
-void plan_sweeps(const umbir_geometry& G, int pi, BatchProb& bp, std::vector<int4>* items, size_t* lds);
+// With mom the problem's items are those of the moment stages.
+void plan_sweeps(const umbir_geometry& G, bool mom, int pi, BatchProb& bp, std::vector<int4>* items, size_t* lds);
+void plan_moments(const umbir_geometry& G, int pi, BatchProb& bp, std::vector<int4>* items, size_t* lds);
+int launch_moment_stage(int stage, const BatchProb* probs, const int* active, const StageLaunch& L, int which,
+                        hipStream_t s);
 
 // Launches one sweep stage (splat, conv, corr, gather) over the batch; items
 // of problem i run only while active[i] is nonzero.

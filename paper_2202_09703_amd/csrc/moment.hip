@@ -1,0 +1,1208 @@
+// The moment form of the factored operator A = C o S (see operator.hip for
+// the factoring): the same operator with the fine grid's Q positions per
+// sample carried as R moments per sample.
+//
+// Over one sample period the tabulated pulse is very smooth (its band is far
+// below the sampling rate), so for every tap k the Q + 1 table values
+// b[(k + 1) Q - t], t = 0 .. Q, are a polynomial of degree R - 1 in
+// z = 2 t / Q - 1 to far below FP32 rounding (build_moments bounds the
+// remainder by 1e-8 of the pulse's peak: R = 5 at 20 MHz, 6 at 10 MHz for a
+// 500 kHz pulse):
+//     b[(k + 1) Q - t] = sum_{p < R} G_p[k] z^p.
+// A voxel whose echo starts at fine position n Q + t + phi in sample n, with
+// weight W, then contributes
+//     y[n + 1 + k] += W x sum_p G_p[k] a_p,   a_p = (1 - phi) z_t^p + phi z_{t+1}^p,
+// exactly the linear interpolation of the table that operator.hip states.  So
+//   S: u_p[n] = sum over the trace's voxels of sample n of W x a_p;
+//   C: y[m] = sum_p sum_n u_p[n] G_p[m - 1 - n];
+//   C^T: v_p[n] = sum_m r[m] G_p[m - 1 - n];
+//   S^T: sum over the traces of W sum_p a_p v_p[n].
+// Against the fine grid this cuts the dense products and the traffic between
+// the sparse and the dense part by Q / R (6.4 at Q = 32).
+//
+// Arrays u and v are [trace][R][Ms] floats, Ms = M rounded up to 32, whatever
+// the storage type of the traces.
+//
+// The splat also uses that the medium is layered: when the scan positions are
+// a constant whole number of voxels apart, the delay and weight of (scan i,
+// receiver j, row, column c) depend on (j, row, c - pitch i) only.  A record
+// per (j, row, relative column) holds n, a_0 .. a_{R-1} (times the weight);
+// the records of each j are sorted by n once per geometry, and u of one (j, n)
+// for all scan positions is then a sum over its records of coefficients times
+// consecutive elements of the image (stored by phase of the pitch), in
+// registers: no atomics, and a fixed order of the sums.
+
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+#include <vector>
+
+#include "internal.h"
+#include "storage.h"
+
+namespace umbir {
+namespace {
+
+constexpr int kBufferWord3 = 0x00020000;  // word 3 of a raw buffer resource: 32-bit data, no swizzle
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// ---- the plan (once per geometry)
+
+// The two legs of (receiver j, row, relative column) at scan position 0.
+struct PairLegs {
+  uint64_t D;  // Q32.32 samples
+  float w;     // product of the apodisations
+};
+
+__device__ __forceinline__ PairLegs pair_legs(const Leg* __restrict__ legs, int n_off, int bt, int br, int row,
+                                              int rel) {
+  const int half = n_off / 2;
+  const Leg a = legs[size_t(row) * n_off + leg_slot(abs(bt + 2 * rel), half)];
+  const Leg b = legs[size_t(row) * n_off + leg_slot(abs(br + 2 * rel), half)];
+  return {uint64_t(a.delay + b.delay), a.apod * b.apod};
+}
+
+// Lattice bases of scan lane 0 (the leftmost position) for receiver j.
+__device__ __forceinline__ void plan_bases(const int* __restrict__ base, const MomentShape& ms, int P, int K, int j,
+                                           int* bt, int* br) {
+  const int i = ms.reversed ? P - 1 : 0;
+  *bt = base[i];
+  *br = base[P + i * K + j];
+}
+
+// Relative columns per plan block: one histogram of samples per (j, chunk).
+constexpr int kPlanChunk = 64;
+
+// counts[j][chunk][n]: records of receiver j and the chunk's relative columns
+// in sample n.
+__global__ __launch_bounds__(256) void k_plan_count(const Leg* __restrict__ legs, const int* __restrict__ base,
+                                                    MomentShape ms, int P, int K, int nz, int n_off, int M,
+                                                    int* __restrict__ counts) {
+  extern __shared__ int hist[];
+  const int j = blockIdx.x, ch = blockIdx.y;
+  for (int i = threadIdx.x; i < M; i += blockDim.x) hist[i] = 0;
+  __syncthreads();
+  int bt, br;
+  plan_bases(base, ms, P, K, j, &bt, &br);
+  const int r0 = ch * kPlanChunk, rn = min(kPlanChunk, ms.NR - r0);
+  for (int i = threadIdx.x; i < nz * kPlanChunk; i += blockDim.x) {
+    const int row = i / kPlanChunk, rc = i - row * kPlanChunk;
+    if (rc >= rn) continue;
+    const PairLegs p = pair_legs(legs, n_off, bt, br, row, ms.rel0 + r0 + rc);
+    const uint64_t n = p.D >> 32;
+    if (n < uint64_t(M)) atomicAdd(&hist[int(n)], 1);
+  }
+  __syncthreads();
+  int* out = counts + (size_t(j) * gridDim.y + ch) * M;
+  for (int i = threadIdx.x; i < M; i += blockDim.x) out[i] = hist[i];
+}
+
+// Per receiver: start[j][n] (the first record of sample n, start[j][M] the
+// end) and, in place of each count, the first record of (chunk, n).  Records
+// of receiver j begin at j * cap.  max_bin receives the largest bin.
+__global__ __launch_bounds__(1024) void k_plan_scan(int M, int chunks, int cap, int* __restrict__ counts,
+                                                    int* __restrict__ start, int* __restrict__ max_bin) {
+  __shared__ int part[1024];
+  const int j = blockIdx.x, t = threadIdx.x;
+  const int per = (M + 1023) / 1024;
+  const int n0 = min(t * per, M), n1 = min(n0 + per, M);
+  int* cj = counts + size_t(j) * chunks * M;
+  int sum = 0, big = 0;
+  for (int n = n0; n < n1; ++n) {
+    int c = 0;
+    for (int k = 0; k < chunks; ++k) c += cj[size_t(k) * M + n];
+    sum += c;
+    big = max(big, c);
+  }
+  part[t] = sum;
+  __syncthreads();
+  for (int off = 1; off < 1024; off <<= 1) {
+    const int v = t >= off ? part[t - off] : 0;
+    __syncthreads();
+    part[t] += v;
+    __syncthreads();
+  }
+  int at = j * cap + part[t] - sum;
+  for (int n = n0; n < n1; ++n) {
+    start[size_t(j) * (M + 1) + n] = at;
+    for (int k = 0; k < chunks; ++k) {
+      const int c = cj[size_t(k) * M + n];
+      cj[size_t(k) * M + n] = at;
+      at += c;
+    }
+  }
+  if (t == 1023) start[size_t(j) * (M + 1) + M] = j * cap + part[1023];
+  if (big > 0) atomicMax(max_bin, big);
+}
+
+// Keys row * NR + (rel - rel0) of every record into its bin, in any order.
+__global__ __launch_bounds__(256) void k_plan_fill(const Leg* __restrict__ legs, const int* __restrict__ base,
+                                                   MomentShape ms, int P, int K, int nz, int n_off, int M,
+                                                   const int* __restrict__ first, unsigned* __restrict__ keys) {
+  extern __shared__ int cursor[];
+  const int j = blockIdx.x, ch = blockIdx.y;
+  const int* f = first + (size_t(j) * gridDim.y + ch) * M;
+  for (int i = threadIdx.x; i < M; i += blockDim.x) cursor[i] = f[i];
+  __syncthreads();
+  int bt, br;
+  plan_bases(base, ms, P, K, j, &bt, &br);
+  const int r0 = ch * kPlanChunk, rn = min(kPlanChunk, ms.NR - r0);
+  for (int i = threadIdx.x; i < nz * kPlanChunk; i += blockDim.x) {
+    const int row = i / kPlanChunk, rc = i - row * kPlanChunk;
+    if (rc >= rn) continue;
+    const PairLegs p = pair_legs(legs, n_off, bt, br, row, ms.rel0 + r0 + rc);
+    const uint64_t n = p.D >> 32;
+    if (n < uint64_t(M)) keys[atomicAdd(&cursor[int(n)], 1)] = unsigned(row) * unsigned(ms.NR) + unsigned(r0 + rc);
+  }
+}
+
+// A bin larger than this would take its wave too long to order (only voxels
+// far smaller than a sample period reach it): such a geometry keeps the fine
+// grid (the host reads max_bin after the build).
+constexpr int kMaxBin = 8192;
+
+// One wave per (j, n): the bin's keys put in ascending order by counting the
+// smaller ones, and the records written in that order: coefficients
+// tau a_tx a_rx ((1 - phi) z_t^p + phi z_{t+1}^p) in double, rounded once, and
+// the offset of the voxel in the phase-major image (lane i of the splat adds
+// its scan position).
+template <int R>
+__global__ __launch_bounds__(256) void k_plan_emit(const Leg* __restrict__ legs, const int* __restrict__ base,
+                                                   const float* __restrict__ tau, MomentShape ms, int P, int K,
+                                                   int n_off, int qs, int M, const int* __restrict__ start,
+                                                   const unsigned* __restrict__ keys,
+                                                   const int* __restrict__ max_bin, float4* __restrict__ rec4,
+                                                   float* __restrict__ rec_hi, unsigned* __restrict__ rec_off) {
+  if (*max_bin > kMaxBin) return;
+  const int j = blockIdx.x;
+  const int n = blockIdx.y * 4 + (threadIdx.x >> 6);
+  if (n >= M) return;
+  const int lane = threadIdx.x & 63;
+  const int s = start[size_t(j) * (M + 1) + n], e = start[size_t(j) * (M + 1) + n + 1];
+  int bt, br;
+  plan_bases(base, ms, P, K, j, &bt, &br);
+  for (int i0 = s; i0 < e; i0 += 64) {
+    const unsigned key = i0 + lane < e ? keys[i0 + lane] : 0xffffffffu;
+    int rank = 0;
+    for (int k0 = s; k0 < e; k0 += 64) {  // past the end: no key is smaller than it
+      const unsigned other = k0 + lane < e ? keys[k0 + lane] : 0xffffffffu;
+#pragma unroll
+      for (int k = 0; k < 64; ++k) rank += unsigned(__builtin_amdgcn_readlane(int(other), k)) < key ? 1 : 0;
+    }
+    if (i0 + lane >= e) continue;
+    const int at = s + rank;
+    const int row = int(key / unsigned(ms.NR)), rel = ms.rel0 + int(key - unsigned(row) * unsigned(ms.NR));
+    const PairLegs p = pair_legs(legs, n_off, bt, br, row, rel);
+    const unsigned frac = unsigned(p.D);
+    const double t = double(frac >> (32 - qs));
+    const double phi = double(unsigned(frac << qs)) * (1.0 / 4294967296.0);
+    const double h = 2.0 / double(1 << qs);
+    const double z0 = t * h - 1.0, z1 = (t + 1.0) * h - 1.0;
+    const double w = double(tau[row]) * double(p.w);
+    double p0 = w * (1.0 - phi), p1 = w * phi;
+    float a[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      a[q] = float(p0 + p1);
+      p0 *= z0;
+      p1 *= z1;
+    }
+    rec4[at] = make_float4(a[0], a[1], a[2], a[3]);
+#pragma unroll
+    for (int q = 4; q < R; ++q) rec_hi[size_t(at) * (R - 4) + (q - 4)] = a[q];
+    int rq = rel >= 0 ? rel / ms.pitch : -((-rel + ms.pitch - 1) / ms.pitch);  // floor
+    const int phase = rel - rq * ms.pitch;
+    rec_off[at] = unsigned((row * ms.pitch + phase) * ms.Lq + rq + P - 1);
+  }
+}
+
+// G_p[k] = sum_t fit[p][t] b[(k + 1) Q - t] (fit: least squares on the Q + 1
+// points, R x (Q + 1) doubles), b evaluated in double.  One wave per k.
+__global__ __launch_bounds__(256) void k_moment_fit(int R, int Q, int Lh, double dt, double f_c, double inv2s2,
+                                                    double t_c, const double* __restrict__ fit,
+                                                    float* __restrict__ g) {
+  const int k = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (k >= Lh) return;
+  const int QLh = Q * Lh;
+  double acc[8] = {};
+  for (int t = lane; t <= Q; t += 64) {
+    const int n = (k + 1) * Q - t;
+    const double x = n * dt - t_c;
+    const double b = n <= 0 || n >= QLh ? 0.0 : sin(2.0 * M_PI * f_c * x) * exp(-x * x * inv2s2);
+#pragma unroll
+    for (int p = 0; p < 8; ++p)
+      if (p < R) acc[p] += fit[p * (Q + 1) + t] * b;
+  }
+#pragma unroll
+  for (int p = 0; p < 8; ++p) {
+    for (int off = 32; off > 0; off >>= 1) acc[p] += __shfl_xor(acc[p], off, 64);
+    if (lane == 0 && p < R) g[p * Lh + k] = float(acc[p]);
+  }
+}
+
+// The dense kernels' operand table F[p][piece][D + 1], D = -1 .. Lh + 7: the 8
+// values G_p[D], G_p[D - 1], ..., G_p[D - 7] (zero outside [0, Lh)) split into
+// three bf16 pieces.
+__global__ __launch_bounds__(256) void k_moment_table(int R, int Lh, int LT, const float* __restrict__ g,
+                                                      uint4* __restrict__ F) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= R * LT) return;
+  const int p = i / LT, D = i - p * LT - 1;
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = D - e >= 0 && D - e < Lh ? g[p * Lh + D - e] : 0.0f;
+  const Pieces8 pc = split8_bf16x3(make_float4(v[0], v[1], v[2], v[3]), make_float4(v[4], v[5], v[6], v[7]));
+#pragma unroll
+  for (int q = 0; q < 3; ++q) F[(size_t(p) * 3 + q) * LT + D + 1] = pc.p[q];
+}
+
+// ---- the image by phase of the pitch: xp[row][phase][q + P - 1], column
+// c = phase + pitch q, zero where c lies outside the grid (x NULL: ones).
+
+__global__ void k_phase_image(const float* __restrict__ x, int nx, int nz, int P, MomentShape ms,
+                              float* __restrict__ xp) {
+  const int n = nz * ms.pitch * ms.Lq;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    const int rp = i / ms.Lq, q = i - rp * ms.Lq - (P - 1);
+    const int row = rp / ms.pitch, c = rp - row * ms.pitch + ms.pitch * q;
+    xp[i] = c >= 0 && c < nx ? (x ? x[row * nx + c] : 1.0f) : 0.0f;
+  }
+}
+
+// ---- S
+
+// u of receiver bx, samples 16 by .. 16 by + 15, scan lanes 64 bz ...: a wave
+// takes a sample at a time, 64 of its records at a time: loaded one per lane,
+// parked in the wave's own LDS, then multiplied G = 64 / S records a step (S
+// lanes, a power of two >= 4, per record: one scan position each) on the
+// matrix cores, v_mfma_f32_4x4x1: lane l holds coefficient l % 4 of its
+// record (A) and the image element of its scan position (B), and the four
+// results of a lane are its moments 0 .. 3; higher moments take an FMA each.
+// Runs of 64 records sum in FP32, the runs in FP64.  The splat it replaces
+// (64-bit LDS atomics on the fine grid) was bound by address processing at
+// 118 clocks per 64 (trace, voxel) pairs and CU; a step here costs one
+// coalesced image load and three or four LDS reads.
+constexpr int kMsBins = 16;   // samples per block
+constexpr int kMsWaves = 4;
+
+template <int R>
+__host__ __device__ constexpr int msplat_chunk_words() { return 64 * (R + 1); }
+
+template <int R>
+__device__ __forceinline__ void msplat_body(int bx, int by, int bz, const float* __restrict__ xp, int xp_bytes,
+                                            const int* __restrict__ start, const float4* __restrict__ rec4,
+                                            const float* __restrict__ rec_hi, const unsigned* __restrict__ rec_off,
+                                            int P, int K, int M, int Ms, int ls, int reversed,
+                                            float* __restrict__ u) {
+  extern __shared__ __align__(16) float sm[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int S = 1 << ls, G = 64 >> ls;
+  float4* c4 = reinterpret_cast<float4*>(sm) + wave * 64;                       // [64] moments 0 .. 3
+  float* chi = sm + kMsWaves * 256 + wave * 64 * (R - 4);                       // [64][R - 4]
+  unsigned* cof = reinterpret_cast<unsigned*>(sm + kMsWaves * 64 * R) + wave * 64;  // [64]
+  float* outu = sm + kMsWaves * msplat_chunk_words<R>();                        // [R][S][kMsBins + 1]
+  const __amdgpu_buffer_rsrc_t xrs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xp), 0, xp_bytes, kBufferWord3);
+  const int j = bx, n0 = by * kMsBins;
+  const int sl = lane & (S - 1), grp = lane >> ls;
+  const unsigned xl = unsigned(64 * bz + sl);  // this lane's scan position
+  const float* c4f = reinterpret_cast<const float*>(c4) + (lane & 3);
+  for (int b = wave; b < kMsBins; b += kMsWaves) {
+    const int n = n0 + b;
+    double acc[R];
+#pragma unroll
+    for (int p = 0; p < R; ++p) acc[p] = 0.0;
+    if (n < M) {
+      const int s = start[size_t(j) * (M + 1) + n], e = start[size_t(j) * (M + 1) + n + 1];
+      for (int c = s; c < e; c += 64) {
+        {  // past the end: the bin's last record with coefficients zero
+          const int i = min(c + lane, e - 1);
+          const bool in = c + lane < e;
+          const float4 v = rec4[i];
+          float hi[R - 4];
+#pragma unroll
+          for (int q = 0; q < R - 4; ++q) hi[q] = rec_hi[size_t(i) * (R - 4) + q];
+          const unsigned o = rec_off[i];
+          __builtin_amdgcn_wave_barrier();
+          c4[lane] = in ? v : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+          for (int q = 0; q < R - 4; ++q) chi[lane * (R - 4) + q] = in ? hi[q] : 0.0f;
+          cof[lane] = o;
+          __builtin_amdgcn_wave_barrier();
+        }
+        floatx4 d = {0.0f, 0.0f, 0.0f, 0.0f};
+        float dh[R - 4] = {};
+        const int steps = (min(64, e - c) + G - 1) >> (6 - ls);
+        constexpr int U = 8;
+        for (int k0 = 0; k0 < steps; k0 += U) {
+          float xv[U];
+#pragma unroll
+          for (int q = 0; q < U; ++q) {
+            const int r = (min(k0 + q, steps - 1) << (6 - ls)) + grp;
+            xv[q] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(xrs, int((cof[r] + xl) * 4u), 0, 0));
+          }
+#pragma unroll
+          for (int q = 0; q < U; ++q) {
+            if (k0 + q >= steps) break;
+            const int r = ((k0 + q) << (6 - ls)) + grp;
+            d = __builtin_amdgcn_mfma_f32_4x4x1f32(c4f[4 * r], xv[q], d, 0, 0, 0);
+#pragma unroll
+            for (int w = 0; w < R - 4; ++w) dh[w] = fmaf(chi[r * (R - 4) + w], xv[q], dh[w]);
+          }
+        }
+#pragma unroll
+        for (int p = 0; p < 4; ++p) acc[p] += double(d[p]);
+#pragma unroll
+        for (int p = 4; p < R; ++p) acc[p] += double(dh[p - 4]);
+      }
+    }
+    for (int off = S; off < 64; off <<= 1) {
+#pragma unroll
+      for (int p = 0; p < R; ++p) acc[p] += __shfl_xor(acc[p], off, 64);
+    }
+    if (lane < S) {
+#pragma unroll
+      for (int p = 0; p < R; ++p) outu[(p * S + lane) * (kMsBins + 1) + b] = float(acc[p]);
+    }
+  }
+  __syncthreads();
+  // runs of 16 samples of one (trace, moment)
+  for (int i = threadIdx.x; i < R * S * kMsBins; i += blockDim.x) {
+    const int b = i & (kMsBins - 1), ps = i >> 4;
+    const int p = ps >> ls, sc = 64 * bz + (ps & (S - 1));
+    if (sc < P) {
+      const int t = (reversed ? P - 1 - sc : sc) * K + j;
+      u[(size_t(t) * R + p) * Ms + n0 + b] = outu[ps * (kMsBins + 1) + b];
+    }
+  }
+}
+static_assert(kMsBins == 16, "msplat_body's index shifts");
+
+template <int R>
+size_t msplat_lds(int ls) {
+  return size_t(kMsWaves * msplat_chunk_words<R>() + R * (1 << ls) * (kMsBins + 1)) * sizeof(float);
+}
+
+template <int R>
+__global__ __launch_bounds__(64 * kMsWaves) void k_msplat(const float* __restrict__ xp, int xp_bytes,
+                                                          const int* __restrict__ start,
+                                                          const float4* __restrict__ rec4,
+                                                          const float* __restrict__ rec_hi,
+                                                          const unsigned* __restrict__ rec_off, int P, int K, int M,
+                                                          int Ms, int ls, int reversed, float* __restrict__ u,
+                                                          CostFold fold) {
+  if (fold.out && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) {  // uniform
+    extern __shared__ __align__(16) float sm[];
+    fold_cost(fold, reinterpret_cast<double*>(sm));
+  }
+  msplat_body<R>(blockIdx.x, blockIdx.y, blockIdx.z, xp, xp_bytes, start, rec4, rec_hi, rec_off, P, K, M, Ms, ls,
+                 reversed, u);
+}
+
+// ---- C and C^T: banded Toeplitz products on the bf16 matrix cores, FP32
+// products from bf16 pieces (storage.h).  D = A B with 32 traces as rows; the
+// Toeplitz operand B[k][col] = G_p[col's d - k] is a table in LDS whose entry
+// D holds G_p[D .. D - 7] as one 16-byte word per piece, so every lane's eight
+// contraction values are one aligned read and neighbouring lanes read
+// neighbouring words.
+
+constexpr int kMcWaves = 8;
+
+__device__ __forceinline__ void stage_table(uint4* tab, const uint4* __restrict__ F, int n) {
+  stage_block<uint4>(n, [&](int i) { return F[i]; }, [&](int i, const uint4& v) { tab[i] = v; });
+}
+
+// C: a block computes 32 traces x 32 NTC samples; its eight waves take the
+// (16 samples of u, moment) items of the window in turn, each item split into
+// pieces once and multiplied into every tile it reaches; the waves' sums are
+// added in LDS, two tiles at a time, in wave order.
+template <int R, int NTC, int ST>
+__device__ __forceinline__ void mconv_body(int bx, int by, const float* __restrict__ u, int Ms,
+                                           const uint4* __restrict__ F, int LT, int M, int Lh, int PK,
+                                           const typename Store<ST>::T* base, float sign,
+                                           const float* __restrict__ g, const float* __restrict__ dbasis,
+                                           typename Store<ST>::T* out) {
+  extern __shared__ __align__(16) float sm[];
+  uint4* tab = reinterpret_cast<uint4*>(sm);
+  const int tr0 = bx * 32, m0 = by * 32 * NTC;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int li = lane & 31, lk = lane >> 5;
+  stage_table(tab, F, R * 3 * LT);
+  // the epilogue's inputs, fetched while the window multiplies: thread
+  // (wave, lane) finishes registers wave and wave + 8 of every tile
+  constexpr int E = 2 * NTC;
+  float pre_base[E], pre_db[E], pre_g[E];
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    const int i = wave + 8 * (q & 1);
+    const int mm = min(m0 + 32 * (q >> 1) + li, M - 1);
+    const int tr = min(tr0 + 8 * (i >> 2) + 4 * lk + (i & 3), PK - 1);
+    const size_t idx = size_t(tr) * M + mm;
+    pre_base[q] = base ? Store<ST>::get(base[idx]) : 0.0f;
+    pre_db[q] = g ? dbasis[idx] : 0.0f;
+    pre_g[q] = g ? g[tr] : 0.0f;
+  }
+  floatx16 acc[NTC];
+#pragma unroll
+  for (int j = 0; j < NTC; ++j)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[j][i] = 0.0f;
+  const float* ut = u + size_t(min(tr0 + li, PK - 1)) * R * Ms;
+  // rows n of the window [m0 - Lh, m0 + 32 NTC - 2], in steps of 16 from a
+  // multiple of 8 (a group of 8 lies wholly before sample 0 or not at all)
+  const int ns = (m0 - Lh) & ~7;
+  const int s_lo = ns < 0 ? (-ns) >> 4 : 0;
+  const int s_hi = min((m0 + 32 * NTC - 1 - ns + 15) >> 4, (Ms - ns + 15) >> 4);
+  const int items = (s_hi - s_lo) * R;
+  auto fetch = [&](int q, float4& x, float4& y) {
+    const int s = s_lo + q / R, p = q - (q / R) * R;
+    const int n = ns + 16 * s + 8 * lk;
+    const float* row = ut + p * Ms + min(max(n, 0), Ms - 8);
+    x = *reinterpret_cast<const float4*>(row);
+    y = *reinterpret_cast<const float4*>(row + 4);
+  };
+  auto multiply = [&](int q, float4 x, float4 y) {
+    const int s = s_lo + q / R, p = q - (q / R) * R;
+    const int n0 = ns + 16 * s;
+    if (n0 + 8 * lk < 0) x = y = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const Pieces8 a = split8_bf16x3(x, y);
+    const uint4* tp = tab + p * 3 * LT + 1;
+#pragma unroll
+    for (int j = 0; j < NTC; ++j) {
+      const int dj = m0 + 32 * j - 1 - n0;  // lane's D = dj + li - 8 lk
+      if (dj + 31 < 0 || dj - 8 > Lh + 6) continue;  // uniform: no tap meets the tile
+      const int D = min(max(dj + li - 8 * lk, -1), LT - 2);
+      const uint4 b[3] = {tp[D], tp[LT + D], tp[2 * LT + D]};
+      acc[j] = mfma_bf16x3(a.p, b, acc[j]);
+    }
+  };
+  __syncthreads();
+  float4 x0, y0, x1, y1;
+  if (wave < items) fetch(wave, x0, y0);
+  for (int q = wave; q < items; q += 2 * kMcWaves) {
+    if (q + kMcWaves < items) fetch(q + kMcWaves, x1, y1);
+    multiply(q, x0, y0);
+    if (q + kMcWaves < items) {
+      if (q + 2 * kMcWaves < items) fetch(q + 2 * kMcWaves, x0, y0);
+      multiply(q + kMcWaves, x1, y1);
+    }
+  }
+  // red[tile of the pair][wave][register][lane]
+  constexpr int NP = NTC < 2 ? 1 : 2;
+  float* red = sm;
+#pragma unroll
+  for (int j0 = 0; j0 < NTC; j0 += NP) {
+    __syncthreads();  // the table (or the pair before) is read
+#pragma unroll
+    for (int jj = 0; jj < NP; ++jj)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) red[((jj * kMcWaves + wave) * 16 + i) * 64 + lane] = acc[j0 + jj][i];
+    __syncthreads();
+#pragma unroll
+    for (int q = 2 * j0; q < 2 * (j0 + NP); ++q) {
+      const int i = wave + 8 * (q & 1), jj = (q >> 1) - j0;
+      float v = red[(jj * kMcWaves * 16 + i) * 64 + lane];
+      for (int w = 1; w < kMcWaves; ++w) v += red[((jj * kMcWaves + w) * 16 + i) * 64 + lane];
+      const int mm = m0 + 32 * (q >> 1) + li, tr = tr0 + 8 * (i >> 2) + 4 * lk + (i & 3);
+      if (mm < M && tr < PK) {
+        float val = sign * v;
+        if (base) val += pre_base[q];
+        if (g) val -= pre_g[q] * pre_db[q];
+        out[size_t(tr) * M + mm] = Store<ST>::put(val);
+      }
+    }
+  }
+}
+
+size_t mconv_lds(int R, int LT, int ntc) {
+  return std::max(size_t(R) * 3 * LT * sizeof(uint4),
+                  size_t(ntc < 2 ? 1 : 2) * kMcWaves * 1024 * sizeof(float));
+}
+
+template <int R, int NTC, int ST>
+__global__ __launch_bounds__(64 * kMcWaves) void k_mconv(const float* __restrict__ u, int Ms,
+                                                         const uint4* __restrict__ F, int LT, int M, int Lh, int PK,
+                                                         const typename Store<ST>::T* base, float sign,
+                                                         const float* __restrict__ g,
+                                                         const float* __restrict__ dbasis,
+                                                         typename Store<ST>::T* out) {
+  mconv_body<R, NTC, ST>(blockIdx.x, blockIdx.y, u, Ms, F, LT, M, Lh, PK, base, sign, g, dbasis, out);
+}
+
+// Eight consecutive samples of a trace row from m on; samples at or past M
+// are zero.  `inside` (uniform): every lane's eight lie in the record.
+__device__ __forceinline__ void load8(const float* row, int m, int M, bool inside, float (&v)[8]) {
+  if (inside) {
+    __builtin_memcpy(v, row + m, sizeof(v));  // rows start at any multiple of 4 bytes
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = m + e < M ? row[m + e] : 0.0f;
+  }
+}
+
+// C^T: a wave computes 32 traces x 32 samples x all R moments (the trace
+// samples are split into pieces once for the R products); a block has NT
+// sample tiles and 8 / NT waves on each, which share the window's steps and
+// add their sums in LDS, halving.  The eight samples of a lane go in reversed,
+// so that C's table serves.
+template <int R, int NT>
+__device__ __forceinline__ void mcorr_body(int bx, int by, const float* __restrict__ r,
+                                           const uint4* __restrict__ F, int LT, int M, int Lh, int PK, int Ms,
+                                           float* __restrict__ v) {
+  extern __shared__ __align__(16) float sm[];
+  constexpr int KS = kMcWaves / NT;
+  uint4* tab = reinterpret_cast<uint4*>(sm);
+  const int tr0 = bx * 32;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int li = lane & 31, lk = lane >> 5;
+  const int jt = wave % NT, ks = wave / NT;
+  const int n0 = (by * NT + jt) * 32;
+  stage_table(tab, F, R * 3 * LT);
+  floatx16 acc[R];
+#pragma unroll
+  for (int p = 0; p < R; ++p)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[p][i] = 0.0f;
+  const float* row = r + size_t(min(tr0 + li, PK - 1)) * M;
+  // samples m of [n0 + 1, n0 + 31 + Lh], in steps of 16 from n0
+  const int steps = n0 < M ? min((Lh + 32 + 15) >> 4, (M - n0 + 15) >> 4) : 0;
+  auto multiply = [&](int s, const float (&x)[8]) {
+    const Pieces8 a = split8_bf16x3(make_float4(x[7], x[6], x[5], x[4]), make_float4(x[3], x[2], x[1], x[0]));
+    const int D = min(max(16 * s + 8 * lk + 6 - li, -1), LT - 2);
+    const uint4* tp = tab + 1 + D;
+#pragma unroll
+    for (int p = 0; p < R; ++p) {
+      const uint4 b[3] = {tp[(3 * p) * LT], tp[(3 * p + 1) * LT], tp[(3 * p + 2) * LT]};
+      acc[p] = mfma_bf16x3(a.p, b, acc[p]);
+    }
+  };
+  auto fetch = [&](int s, float (&x)[8]) {
+    load8(row, n0 + 16 * s + 8 * lk, M, n0 + 16 * s + 16 <= M, x);
+  };
+  __syncthreads();
+  float x0[8], x1[8];
+  if (ks < steps) fetch(ks, x0);
+  for (int s = ks; s < steps; s += 2 * KS) {
+    if (s + KS < steps) fetch(s + KS, x1);
+    multiply(s, x0);
+    if (s + KS < steps) {
+      if (s + 2 * KS < steps) fetch(s + 2 * KS, x0);
+      multiply(s + KS, x1);
+    }
+  }
+  float* red = sm;
+#pragma unroll
+  for (int h = KS / 2; h >= 1; h >>= 1) {
+    __syncthreads();
+    if (ks >= h && ks < 2 * h) {
+      float* d = red + size_t(jt * h + ks - h) * R * 1024 + lane;
+#pragma unroll
+      for (int p = 0; p < R; ++p)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) d[(p * 16 + i) * 64] = acc[p][i];
+    }
+    __syncthreads();
+    if (ks < h) {
+      const float* d = red + size_t(jt * h + ks) * R * 1024 + lane;
+#pragma unroll
+      for (int p = 0; p < R; ++p)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[p][i] += d[(p * 16 + i) * 64];
+    }
+  }
+  if (ks != 0 || n0 >= Ms) return;
+#pragma unroll
+  for (int p = 0; p < R; ++p)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int tr = tr0 + 8 * (i >> 2) + 4 * lk + (i & 3);
+      if (tr < PK) v[(size_t(tr) * R + p) * Ms + n0 + li] = acc[p][i];
+    }
+}
+
+size_t mcorr_lds(int R, int LT) {
+  return std::max(size_t(R) * 3 * LT * sizeof(uint4), size_t(kMcWaves / 2) * R * 1024 * sizeof(float));
+}
+
+template <int R, int NT>
+__global__ __launch_bounds__(64 * kMcWaves) void k_mcorr(const float* __restrict__ r, const uint4* __restrict__ F,
+                                                         int LT, int M, int Lh, int PK, int Ms,
+                                                         float* __restrict__ v) {
+  mcorr_body<R, NT>(blockIdx.x, blockIdx.y, r, F, LT, M, Lh, PK, Ms, v);
+}
+
+// ---- S^T
+
+// The windowed gather over moments: blocks of 512 threads take 32 x 64 voxel
+// tiles (wave w's load q covers tile row 8 q + w, one lane per column); for
+// every trace of group bx the tile's window of v (R planes, from the
+// geometry's table of (tile, trace) windows) is copied into LDS with 16-byte
+// loads, one trace ahead, into the other of two buffers (one barrier per
+// trace), and every voxel evaluates its polynomial at its two table points
+// and interpolates.  A window longer than a buffer reads v from memory.  The
+// window is Q / R times smaller than the fine grid's, so almost every window
+// fits (of 1632 .. 2048 samples) and two buffers do.  One partial image per
+// group, traces in order.
+constexpr int kMgBufBytes = 40960;  // one window buffer; two per block, two blocks per CU
+
+template <int R>
+__host__ __device__ constexpr int mgather_cap() { return kMgBufBytes / (4 * R) / 4 * 4; }
+
+template <int R>
+__device__ __forceinline__ void mgather_body(int bx, int by, const float* __restrict__ v, int Ms, int nx, int nz,
+                                             int n_off, const Leg* __restrict__ legs,
+                                             const float* __restrict__ tau, const int* __restrict__ base, int P,
+                                             int K, int qs, int M, int tpg, const int2* __restrict__ gwin,
+                                             int tiles_per_block, float* __restrict__ partial) {
+  extern __shared__ __align__(16) float sm[];  // [2][R][kCap]
+  constexpr int kCap = mgather_cap<R>();
+  static_assert(kCap <= 4 * 512, "one 16-byte load per thread and plane");
+  constexpr int VPT = kGatherTileRows / 8;
+  const int N = nx * nz, PK = P * K;
+  const int t0 = bx * tpg, t1 = min(t0 + tpg, PK);
+  const int tiles_x = (nx + kGatherTileCols - 1) / kGatherTileCols;
+  const int n_tiles = tiles_x * ((nz + kGatherTileRows - 1) / kGatherTileRows);
+  const int tile_end = min(n_tiles, (by + 1) * tiles_per_block);
+  const int half = n_off / 2;
+  const int wave = int(threadIdx.x >> 6), lane = int(threadIdx.x & 63);
+  const float h = 2.0f / float(1 << qs);
+  const __amdgpu_buffer_rsrc_t leg_rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<Leg*>(legs), 0, nz * n_off * int(sizeof(Leg)), kBufferWord3);
+  struct Legs { int64_t d[VPT]; float p[VPT]; };
+  for (int tile = by * tiles_per_block; tile < tile_end; ++tile) {
+    const int tz = tile / tiles_x;
+    const int tx = tile - tz * tiles_x;
+    int col2[VPT], rowoff[VPT], vox[VPT];
+    bool ok[VPT];
+    float acc[VPT];
+#pragma unroll
+    for (int q = 0; q < VPT; ++q) {
+      const int row = tz * kGatherTileRows + 8 * q + wave;
+      const int col = tx * kGatherTileCols + lane;
+      ok[q] = row < nz && col < nx;
+      const int r = min(row, nz - 1), c = min(col, nx - 1);  // outside the grid: a voxel of the tile, unused
+      vox[q] = r * nx + c;
+      col2[q] = 2 * c;
+      rowoff[q] = r * n_off;
+      acc[q] = 0.0f;
+    }
+    const int2* wt = gwin + size_t(tile) * PK;
+    auto load_leg = [&](int bt, Legs& L) {
+#pragma unroll
+      for (int q = 0; q < VPT; ++q) {
+        const int o = (rowoff[q] + leg_slot(abs(bt + col2[q]), half)) * int(sizeof(Leg));
+        const auto a = __builtin_amdgcn_raw_buffer_load_b64(leg_rs, o, 0, 0);
+        L.p[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(leg_rs, o + 8, 0, 0));
+        L.d[q] = int64_t((uint64_t(a[1]) << 32) | a[0]);
+      }
+    };
+    // the window of trace t in samples: {first (a multiple of 4), count (a
+    // multiple of 4, 0: no voxel of the tile lies in the record)}
+    auto window = [&](int t) {
+      const int2 w = wt[min(t, t1 - 1)];
+      if (w.y == 0 || t >= t1) return make_int2(0, 0);
+      const int lo = (w.x >> qs) & ~3;
+      const int hi = min((w.x + w.y - 1) >> qs, M - 1);
+      return make_int2(lo, (hi + 1 - lo + 3) & ~3);
+    };
+    const int x4 = 4 * int(threadIdx.x);
+    // (unconditional loads: slots past the window read out of range, zero)
+    auto stage_load = [&](int2 W, int t, uint4 (&rg)[R]) {
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<float*>(v + size_t(min(t, t1 - 1)) * R * Ms), 0, R * Ms * 4, kBufferWord3);
+      const bool in = W.y <= kCap && x4 < W.y;
+#pragma unroll
+      for (int p = 0; p < R; ++p) {
+        const auto q = __builtin_amdgcn_raw_buffer_load_b128(rs, in ? (p * Ms + W.x + x4) * 4 : 0x7ffffff0, 0, 0);
+        rg[p] = make_uint4(q[0], q[1], q[2], q[3]);
+      }
+    };
+    auto stage_store = [&](int2 W, float* buf, const uint4 (&rg)[R]) {
+      if (W.y <= kCap && x4 < W.y) {
+#pragma unroll
+        for (int p = 0; p < R; ++p) *reinterpret_cast<uint4*>(buf + p * kCap + x4) = rg[p];
+      }
+    };
+    Legs TX, La, Lb;
+    auto add = [&](const Legs& L, int2 W, int t, const float* buf) {
+      if (W.y == 0) return;
+      const bool fits = W.y <= kCap;
+      const float* vt = v + size_t(t) * R * Ms;
+#pragma unroll
+      for (int q = 0; q < VPT; ++q) {
+        const uint64_t D = uint64_t(TX.d[q] + L.d[q]);
+        const unsigned n = unsigned(min(D >> 32, uint64_t(M)));
+        const bool in = n < unsigned(M);
+        const unsigned fr = unsigned(D);
+        const float w = in ? TX.p[q] * L.p[q] : 0.0f;
+        const float z0 = fmaf(float(fr >> (32 - qs)), h, -1.0f), z1 = z0 + h;
+        const float phi = float(fr << qs) * 2.3283064365386963e-10f;
+        float c[R];
+        if (fits) {
+          const float* s = buf + (in ? int(n) - W.x : 0);
+#pragma unroll
+          for (int p = 0; p < R; ++p) c[p] = s[p * kCap];
+        } else {
+          const float* s = vt + (in ? n : 0u);
+#pragma unroll
+          for (int p = 0; p < R; ++p) c[p] = s[size_t(p) * Ms];
+        }
+        float f0 = c[R - 1], f1 = c[R - 1];
+#pragma unroll
+        for (int p = R - 2; p >= 0; --p) {
+          f0 = fmaf(f0, z0, c[p]);
+          f1 = fmaf(f1, z1, c[p]);
+        }
+        acc[q] = fmaf(w, fmaf(phi, f1 - f0, f0), acc[q]);
+      }
+    };
+    if (t0 < t1) {
+      uint4 rg[R];
+      int scan = t0 / K;
+      load_leg(base[scan], TX);
+      load_leg(base[P + t0], La);
+      int2 Wc = window(t0), Wn = window(t0 + 1);
+      stage_load(Wc, t0, rg);
+      __syncthreads();  // the tile before is done with the buffers
+      stage_store(Wc, sm, rg);
+      stage_load(Wn, t0 + 1, rg);
+      __syncthreads();
+      // trace t: window in buffer (t - t0) & 1, legs in L; the window of
+      // t + 1 is in rg (in flight)
+      auto step = [&](int t, Legs& L, Legs& Ln) {
+        float* cur = sm + ((t - t0) & 1) * (kMgBufBytes / 4);
+        float* nxt = sm + ((t - t0 + 1) & 1) * (kMgBufBytes / 4);
+        if (t + 1 < t1) load_leg(base[P + t + 1], Ln);
+        if (t / K != scan) {  // uniform: the next scan position's transmit legs
+          scan = t / K;
+          load_leg(base[scan], TX);
+        }
+        const int2 W2 = window(t + 2);
+        add(L, Wc, t, cur);
+        stage_store(Wn, nxt, rg);
+        stage_load(W2, t + 2, rg);
+        Wc = Wn;
+        Wn = W2;
+        __syncthreads();
+      };
+      for (int t = t0; t < t1; t += 2) {
+        step(t, La, Lb);
+        if (t + 1 < t1) step(t + 1, Lb, La);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < VPT; ++q)
+      if (ok[q]) partial[size_t(bx) * N + vox[q]] = acc[q] * tau[vox[q] / nx];
+  }
+}
+
+template <int R>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(R < 8 ? 4 : 2))) void k_mgather(
+    const float* __restrict__ v, int Ms, int nx, int nz, int n_off, const Leg* __restrict__ legs,
+    const float* __restrict__ tau, const int* __restrict__ base, int P, int K, int qs, int M, int tpg,
+    const int2* __restrict__ gwin, int tiles_per_block, float* __restrict__ partial) {
+  mgather_body<R>(blockIdx.x, blockIdx.y, v, Ms, nx, nz, n_off, legs, tau, base, P, K, qs, M, tpg, gwin,
+                  tiles_per_block, partial);
+}
+
+// ---- work-list forms (see the sweeps' in operator.hip): an item runs the
+// block (y, z, w) of its problem's own launch.
+
+// Calls f(integral_constant) for the problem's R.
+template <typename F>
+__device__ __forceinline__ void with_r_device(int R, F&& f) {
+  if (R == 5) f(std::integral_constant<int, 5>());
+  else if (R == 6) f(std::integral_constant<int, 6>());
+  else f(std::integral_constant<int, 8>());
+}
+template <typename F>
+__device__ __forceinline__ void with_tiles_device(int n, F&& f) {
+  if (n == 4) f(std::integral_constant<int, 4>());
+  else if (n == 2) f(std::integral_constant<int, 2>());
+  else f(std::integral_constant<int, 1>());
+}
+
+__global__ __launch_bounds__(64 * kMsWaves) void k_msplat_list(const BatchProb* __restrict__ probs,
+                                                               const int* __restrict__ active,
+                                                               const int4* __restrict__ items, int n_items,
+                                                               int which) {
+  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
+    const int4 w = items[it];
+    if (!active[w.x]) continue;  // uniform: the problem left the batch
+    const BatchProb& p = probs[w.x];
+    const float* xp = p.P == 1 ? p.x[which] : p.xt;
+    with_r_device(p.mom.R, [&](auto rc) {
+      msplat_body<decltype(rc)::value>(w.y, w.z, w.w, xp, p.nz * p.mom.pitch * p.mom.Lq * 4, p.mom_start, p.mom_rec4,
+                                       p.mom_rec_hi, p.mom_rec_off, p.P, p.K, p.M, p.mom.Ms, p.mom.ls, p.mom.reversed,
+                                       p.fine);
+    });
+    __syncthreads();
+  }
+}
+
+// residual e = y - A x - g D of the iteration
+__global__ __launch_bounds__(64 * kMcWaves) void k_mconv_list(const BatchProb* __restrict__ probs,
+                                                              const int* __restrict__ active,
+                                                              const int4* __restrict__ items, int n_items) {
+  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
+    const int4 w = items[it];
+    if (!active[w.x]) continue;
+    const BatchProb& p = probs[w.x];
+    with_r_device(p.mom.R, [&](auto rc) {
+      with_tiles_device(p.mom_tiles, [&](auto nc) {
+        mconv_body<decltype(rc)::value, decltype(nc)::value, UMBIR_STORAGE_F32>(
+            w.y, w.z, p.fine, p.mom.Ms, p.mom_taps, p.mom.LT, p.M, p.Lh, p.P * p.K, p.y, -1.0f, p.g, p.dbasis, p.e);
+      });
+    });
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(64 * kMcWaves) void k_mcorr_list(const BatchProb* __restrict__ probs,
+                                                              const int* __restrict__ active,
+                                                              const int4* __restrict__ items, int n_items) {
+  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
+    const int4 w = items[it];
+    if (!active[w.x]) continue;
+    const BatchProb& p = probs[w.x];
+    with_r_device(p.mom.R, [&](auto rc) {
+      with_tiles_device(p.mom_tiles, [&](auto nc) {
+        mcorr_body<decltype(rc)::value, decltype(nc)::value>(
+            w.y, w.z, p.e, p.mom_taps, p.mom.LT, p.M, p.Lh, p.P * p.K, p.mom.Ms, p.fine);
+      });
+    });
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(512) void k_mgather_list(const BatchProb* __restrict__ probs,
+                                                      const int* __restrict__ active,
+                                                      const int4* __restrict__ items, int n_items) {
+  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
+    const int4 w = items[it];
+    if (!active[w.x]) continue;
+    const BatchProb& p = probs[w.x];
+    with_r_device(p.mom.R, [&](auto rc) {
+      mgather_body<decltype(rc)::value>(w.y, w.z, p.fine, p.mom.Ms, p.nx, p.nz, p.n_off, p.legs, p.tau, p.base, p.P,
+                                        p.K, p.qs, p.M, p.tpg, p.gwin, p.vpb, p.partial);
+    });
+    __syncthreads();
+  }
+}
+
+// ---- launches
+
+template <int R, int NTC, int ST>
+void launch_mconv(const umbir_geometry& G, const float* u, const void* base, float sign, const float* g, void* out,
+                  hipStream_t s) {
+  using T = typename Store<ST>::T;
+  const dim3 grid(unsigned((G.traces() + 31) / 32), unsigned((G.M + 32 * NTC - 1) / (32 * NTC)));
+  UMBIR_LAUNCH("conv", (k_mconv<R, NTC, ST>), grid, dim3(64 * kMcWaves), mconv_lds(R, G.mom.LT, NTC), s, u,
+               G.mom.Ms, G.mom_taps, G.mom.LT, G.M, G.Lh, G.traces(), static_cast<const T*>(base), sign, g, G.dbasis,
+               static_cast<T*>(out));
+}
+
+template <int R, int NT>
+void launch_mcorr(const umbir_geometry& G, const float* r, float* v, hipStream_t s) {
+  const dim3 grid(unsigned((G.traces() + 31) / 32), unsigned((G.mom.Ms / 32 + NT - 1) / NT));
+  UMBIR_LAUNCH("corr", (k_mcorr<R, NT>), grid, dim3(64 * kMcWaves), mcorr_lds(R, G.mom.LT), s, r, G.mom_taps,
+               G.mom.LT, G.M, G.Lh, G.traces(), G.mom.Ms, v);
+}
+
+// Calls f(integral_constant R, integral_constant storage).
+template <typename F>
+void with_r(int R, F&& f) {
+  if (R == 5) f(std::integral_constant<int, 5>());
+  else if (R == 6) f(std::integral_constant<int, 6>());
+  else f(std::integral_constant<int, 8>());
+}
+template <typename F>
+void with_storage(int st, F&& f) {
+  if (st == UMBIR_STORAGE_F16) f(std::integral_constant<int, UMBIR_STORAGE_F16>());
+  else if (st == UMBIR_STORAGE_BF16) f(std::integral_constant<int, UMBIR_STORAGE_BF16>());
+  else f(std::integral_constant<int, UMBIR_STORAGE_F32>());
+}
+template <typename F>
+void with_tiles(int n, F&& f) {
+  if (n == 4) f(std::integral_constant<int, 4>());
+  else if (n == 2) f(std::integral_constant<int, 2>());
+  else f(std::integral_constant<int, 1>());
+}
+
+// Sample tiles of 32 per block: four where that leaves a block per CU, else
+// two likewise, else one (the waves of a block then share one tile's window).
+int moment_tiles(const umbir_geometry& G) {
+  const long tt = (G.traces() + 31) / 32;
+  return tt * ((G.M + 127) / 128) >= 256 ? 4 : tt * ((G.M + 63) / 64) >= 256 ? 2 : 1;
+}
+
+float* phase_image(const umbir_geometry& G, void* fine) {
+  return reinterpret_cast<float*>(static_cast<char*>(fine) + G.mom.u_bytes);
+}
+
+}  // namespace
+
+bool forward_moments_on(const umbir_geometry& G) { return G.form == 1 && G.split && G.mom.R > 0; }
+
+bool moments_on(const umbir_geometry& G) { return forward_moments_on(G) && G.storage == UMBIR_STORAGE_F32; }
+
+// One scan position reads the image as it is.
+float* moment_image(const umbir_geometry& G, void* fine) {
+  return G.P == 1 ? nullptr : phase_image(G, fine);
+}
+
+int run_phase_image(const umbir_geometry& G, const float* x, void* fine, hipStream_t s) {
+  if (G.P == 1 && x) return UMBIR_OK;
+  const long n = long(G.nz) * G.mom.pitch * G.mom.Lq;
+  UMBIR_LAUNCH("prescale", k_phase_image, dim3(unsigned(std::min<long>((n + 255) / 256, 2048))), dim3(256), 0, s, x,
+               G.nx, G.nz, G.P, G.mom, phase_image(G, fine));
+  return check_hip(hipGetLastError(), "k_phase_image");
+}
+
+int run_forward_moments(const umbir_geometry& G, const float* x, void* out, const void* base, float sign,
+                        const float* g, void* fine, hipStream_t s, bool in_place, const CostFold* fold) {
+  int st = UMBIR_OK;
+  if (!in_place && (st = run_phase_image(G, x, fine, s))) return st;
+  float* u = static_cast<float*>(fine);
+  const float* xp = G.P == 1 && x ? x : phase_image(G, fine);
+  const int xp_bytes = int(size_t(G.nz) * G.mom.pitch * G.mom.Lq * 4);  // P == 1: the image's own bytes
+  const CostFold f = fold ? *fold : CostFold{};
+  with_r(G.mom.R, [&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    const size_t lds = std::max<size_t>(fold ? 256 * sizeof(double) : 0, msplat_lds<R>(G.mom.ls));
+    const dim3 grid(unsigned(G.K), unsigned(G.mom.Ms / kMsBins), unsigned((G.P + 63) / 64));
+    UMBIR_LAUNCH("splat", k_msplat<R>, grid, dim3(64 * kMsWaves), lds, s, xp, xp_bytes, G.mom_start, G.mom_rec4,
+                 G.mom_rec_hi, G.mom_rec_off, G.P, G.K, G.M, G.mom.Ms, G.mom.ls, G.mom.reversed, u, f);
+  });
+  if ((st = check_hip(hipGetLastError(), "k_msplat"))) return st;
+  with_r(G.mom.R, [&](auto rc) {
+    with_tiles(moment_tiles(G), [&](auto nc) {
+      with_storage(G.storage, [&](auto sc) {
+        launch_mconv<decltype(rc)::value, decltype(nc)::value, decltype(sc)::value>(G, u, base, sign, g, out, s);
+      });
+    });
+  });
+  return check_hip(hipGetLastError(), "k_mconv");
+}
+
+int run_adjoint_moments(const umbir_geometry& G, const float* r, void* fine, float* partial, hipStream_t s) {
+  float* v = static_cast<float*>(fine);
+  with_r(G.mom.R, [&](auto rc) {
+    with_tiles(moment_tiles(G), [&](auto nc) {
+      launch_mcorr<decltype(rc)::value, decltype(nc)::value>(G, r, v, s);
+    });
+  });
+  int st = check_hip(hipGetLastError(), "k_mcorr");
+  if (st) return st;
+  const int tpg = (G.traces() + G.trace_groups - 1) / G.trace_groups;
+  int tpb;
+  const dim3 grid(unsigned(G.trace_groups), unsigned(gather_lds_blocks(G.nx, G.nz, G.trace_groups, &tpb)));
+  with_r(G.mom.R, [&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    UMBIR_LAUNCH("gather", k_mgather<R>, grid, dim3(512), size_t(2) * kMgBufBytes, s, v, G.mom.Ms, G.nx, G.nz,
+                 G.n_off, G.legs, G.tau, G.base, G.P, G.K, log2_int(G.Q), G.M, tpg, G.gwin, tpb, partial);
+  });
+  return check_hip(hipGetLastError(), "k_mgather");
+}
+
+void plan_moments(const umbir_geometry& G, int pi, BatchProb& bp, std::vector<int4>* items, size_t* lds) {
+  const MomentShape& ms = G.mom;
+  bp.mom = ms;
+  bp.mom_start = G.mom_start;
+  bp.mom_rec4 = G.mom_rec4;
+  bp.mom_rec_hi = G.mom_rec_hi;
+  bp.mom_rec_off = G.mom_rec_off;
+  bp.mom_taps = G.mom_taps;
+  bp.mom_tiles = moment_tiles(G);
+  const int tt = (G.traces() + 31) / 32, nt = bp.mom_tiles;
+  auto grow = [&](int stage, size_t bytes) { lds[stage] = std::max(lds[stage], bytes); };
+  with_r(ms.R, [&](auto rc) { grow(kStMSplat, msplat_lds<decltype(rc)::value>(ms.ls)); });
+  grow(kStMConv, mconv_lds(ms.R, ms.LT, nt));
+  grow(kStMCorr, mcorr_lds(ms.R, ms.LT));
+  grow(kStMGather, size_t(2) * kMgBufBytes);
+  for (int z = 0; z < (G.P + 63) / 64; ++z)
+    for (int y = 0; y < ms.Ms / kMsBins; ++y)
+      for (int j = 0; j < G.K; ++j) items[kStMSplat].push_back(make_int4(pi, j, y, z));
+  for (int y = 0; y < (G.M + 32 * nt - 1) / (32 * nt); ++y)
+    for (int x = 0; x < tt; ++x) items[kStMConv].push_back(make_int4(pi, x, y, 0));
+  for (int y = 0; y < (ms.Ms / 32 + nt - 1) / nt; ++y)
+    for (int x = 0; x < tt; ++x) items[kStMCorr].push_back(make_int4(pi, x, y, 0));
+  const int nb = gather_lds_blocks(G.nx, G.nz, G.trace_groups, &bp.vpb);
+  for (int y = 0; y < nb; ++y)
+    for (int x = 0; x < G.trace_groups; ++x) items[kStMGather].push_back(make_int4(pi, x, y, 0));
+}
+
+int launch_moment_stage(int stage, const BatchProb* probs, const int* active, const StageLaunch& L, int which,
+                        hipStream_t s) {
+  const dim3 grid(unsigned(L.grid));
+  if (stage == kStMSplat)
+    UMBIR_LAUNCH("splat", k_msplat_list, grid, dim3(64 * kMsWaves), L.lds, s, probs, active, L.items, L.n_items, which);
+  else if (stage == kStMConv)
+    UMBIR_LAUNCH("conv", k_mconv_list, grid, dim3(64 * kMcWaves), L.lds, s, probs, active, L.items, L.n_items);
+  else if (stage == kStMCorr)
+    UMBIR_LAUNCH("corr", k_mcorr_list, grid, dim3(64 * kMcWaves), L.lds, s, probs, active, L.items, L.n_items);
+  else
+    UMBIR_LAUNCH("gather", k_mgather_list, grid, dim3(512), L.lds, s, probs, active, L.items, L.n_items);
+  return check_hip(hipGetLastError(), "moment work-list stage");
+}
+
+// ---- which geometries take the moment form
+
+// |f^(R)| a^R / (R! 2^(R-1)) bounds the remainder of a degree R - 1 fit at the
+// Chebyshev points over a half-width a; f's derivatives by its spectrum
+// (a Gaussian of width 1 / (2 pi sigma_t) around f_c, unit mass for a pulse of
+// unit peak).  The least-squares fit on Q + 1 equispaced points stays within
+// a small factor of it.
+static double fit_remainder(double f_c, double sigma_t, double half_width, int R) {
+  const double sf = 1.0 / (2.0 * M_PI * sigma_t);
+  double mean = 0.0, mass = 0.0;
+  for (int k = -60; k <= 60; ++k) {  // E (2 pi f a)^R over +- 6 sigma_f
+    const double z = 0.1 * k, w = std::exp(-0.5 * z * z);
+    mean += w * std::pow(std::fabs(2.0 * M_PI * (f_c + z * sf) * half_width), R);
+    mass += w;
+  }
+  double scale = 1.0;
+  for (int k = 2; k <= R; ++k) scale *= k;
+  return mean / mass / (scale * std::pow(2.0, R - 1));
+}
+
+MomentShape moment_shape(const MomentInput& in) {
+  MomentShape ms;
+  const int Q = in.Q;
+  // the dense part pays from Q >= 2 R on; longer records than the plan's LDS
+  // histograms keep the fine grid
+  if (in.n_gamma != 1 || Q < 16 || in.M > 16384) return ms;
+  // the window must end where the pulse is (numerically) zero: the table's
+  // forced zeros at its ends are then no step
+  const double tc = 0.5 * in.t_win;
+  if (std::fabs(std::sin(2.0 * M_PI * in.f_c * tc)) * std::exp(-tc * tc / (2.0 * in.sigma_t * in.sigma_t)) > 1e-9)
+    return ms;
+  int R = 0;
+  for (int c : {5, 6, 8})
+    if (!R && 2 * c <= Q && fit_remainder(in.f_c, in.sigma_t, 0.5 / in.fs, c) <= 1e-8) R = c;
+  if (!R) return ms;
+  // scan positions a constant whole number of voxels apart
+  const int P = in.P, K = in.K;
+  long pitch = 1;
+  if (P > 1) {
+    const long d = long(in.base[0]) - in.base[1];  // 2 x voxels to the right
+    if (d == 0 || d % 2) return ms;
+    for (int i = 0; i < P; ++i) {
+      if (long(in.base[0]) - in.base[i] != d * i) return ms;
+      for (int j = 0; j < K; ++j)
+        if (long(in.base[P + j]) - in.base[P + size_t(i) * K + j] != d * i) return ms;
+    }
+    pitch = std::labs(d / 2);
+    ms.reversed = d < 0;
+  }
+  const double NR = double(in.nx) + double(pitch) * (P - 1);
+  const double Lq = std::ceil(double(in.nx) / pitch) + 2.0 * (P - 1);
+  const double recs = double(K) * in.nz * NR;
+  if (recs * 4.0 * (R + 1) > 4e9 || recs > 1e9 || double(in.nz) * pitch * Lq > 1e8) return ms;
+  const int LT = in.Lh + 9;
+  if (size_t(R) * 3 * LT * 16 > 150u * 1024 || double(K) * in.M > 6.4e7) return ms;
+  if (gather_window_bytes(in.nx, in.nz, long(P) * K, long(in.M) * Q, in.storage) == 0) return ms;
+  ms.R = R;
+  ms.Ms = (in.M + 31) & ~31;
+  ms.LT = LT;
+  ms.pitch = int(pitch);
+  ms.Lq = int(Lq);
+  ms.NR = int(NR);
+  ms.rel0 = -int(pitch) * (P - 1);
+  ms.ls = 2;
+  while ((1 << ms.ls) < P && ms.ls < 6) ++ms.ls;
+  ms.u_bytes = (size_t(P) * K * R * ms.Ms * 4 + 255) & ~size_t(255);
+  // the image by phase, and the lanes past the last scan position of it
+  ms.work_bytes = ms.u_bytes + (size_t(in.nz) * ms.pitch * ms.Lq * 4 + 255 & ~size_t(255));
+  ms.records = size_t(K) * in.nz * ms.NR;
+  ms.table_bytes = ms.records * 4 * (R + 1) + size_t(K) * (in.M + 1) * 4 + size_t(R) * 3 * LT * 16;
+  return ms;
+}
+
+// Least-squares fit of degree R - 1 on z_t = 2 t / Q - 1, t = 0 .. Q: the
+// R x (Q + 1) matrix taking the values to the coefficients (normal equations
+// by Gaussian elimination with pivoting; they are well conditioned at R <= 8).
+static std::vector<double> fit_matrix(int R, int Q) {
+  std::vector<double> V(size_t(R) * (Q + 1)), A(size_t(R) * R, 0.0);
+  for (int t = 0; t <= Q; ++t) {
+    double z = 2.0 * t / Q - 1.0, p = 1.0;
+    for (int k = 0; k < R; ++k, p *= z) V[size_t(k) * (Q + 1) + t] = p;
+  }
+  for (int a = 0; a < R; ++a)
+    for (int b = 0; b < R; ++b)
+      for (int t = 0; t <= Q; ++t) A[a * R + b] += V[size_t(a) * (Q + 1) + t] * V[size_t(b) * (Q + 1) + t];
+  for (int c = 0; c < R; ++c) {
+    int piv = c;
+    for (int r = c + 1; r < R; ++r)
+      if (std::fabs(A[r * R + c]) > std::fabs(A[piv * R + c])) piv = r;
+    if (piv != c) {
+      for (int k = 0; k < R; ++k) std::swap(A[c * R + k], A[piv * R + k]);
+      for (int t = 0; t <= Q; ++t) std::swap(V[size_t(c) * (Q + 1) + t], V[size_t(piv) * (Q + 1) + t]);
+    }
+    for (int r = 0; r < R; ++r) {
+      if (r == c) continue;
+      const double f = A[r * R + c] / A[c * R + c];
+      for (int k = c; k < R; ++k) A[r * R + k] -= f * A[c * R + k];
+      for (int t = 0; t <= Q; ++t) V[size_t(r) * (Q + 1) + t] -= f * V[size_t(c) * (Q + 1) + t];
+    }
+  }
+  for (int r = 0; r < R; ++r)
+    for (int t = 0; t <= Q; ++t) V[size_t(r) * (Q + 1) + t] /= A[r * R + r];
+  return V;
+}
+
+// Queues the plan's kernels (G's legs, bases and tau are queued before on s);
+// scratch is allocated and freed in stream order, *max_bin (a host word that
+// lives until the stream was synchronized) receives the largest bin.
+int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s) {
+  const MomentShape& ms = G->mom;
+  const int R = ms.R, K = G->K, M = G->M, Q = G->Q;
+  const int chunks = (ms.NR + kPlanChunk - 1) / kPlanChunk;
+  const size_t n_count = size_t(K) * chunks * M;
+  const std::vector<double> fit = fit_matrix(R, Q);
+  const size_t fit_bytes = (fit.size() * sizeof(double) + 255) & ~size_t(255);
+  const size_t count_bytes = (n_count * sizeof(int) + 255) & ~size_t(255);
+  const size_t g_bytes = (size_t(R) * G->Lh * sizeof(float) + 255) & ~size_t(255);
+  char* tmp = nullptr;
+  int st = check_hip(hipMallocAsync(reinterpret_cast<void**>(&tmp),
+                                    fit_bytes + 256 + g_bytes + count_bytes + ms.records * sizeof(unsigned), s),
+                     "hipMallocAsync(plan)");
+  if (st) return st;
+  double* fit_dev = reinterpret_cast<double*>(tmp);
+  int* mb = reinterpret_cast<int*>(tmp + fit_bytes);
+  float* g = reinterpret_cast<float*>(tmp + fit_bytes + 256);
+  int* counts = reinterpret_cast<int*>(tmp + fit_bytes + 256 + g_bytes);
+  unsigned* keys = reinterpret_cast<unsigned*>(tmp + fit_bytes + 256 + g_bytes + count_bytes);
+  const int cap = G->nz * ms.NR;
+  const size_t lds = size_t(M) * sizeof(int);
+  const dim3 cg{unsigned(K), unsigned(chunks), 1u};
+  if (!(st = check_hip(hipMemcpyAsync(fit_dev, fit.data(), fit.size() * sizeof(double), hipMemcpyHostToDevice, s),
+                       "hipMemcpyAsync(fit)")) &&
+      !(st = check_hip(hipMemsetAsync(mb, 0, sizeof(int), s), "hipMemsetAsync(plan)"))) {
+    UMBIR_LAUNCH("moment_fit", k_moment_fit, dim3(unsigned((G->Lh + 3) / 4)), dim3(256), 0, s, R, Q, G->Lh,
+                 1.0 / (double(Q) * G->fs), G->f_c, 1.0 / (2.0 * G->sigma_t * G->sigma_t), 0.5 * G->t_win, fit_dev, g);
+    UMBIR_LAUNCH("moment_table", k_moment_table, dim3(unsigned((R * ms.LT + 255) / 256)), dim3(256), 0, s, R, G->Lh,
+                 ms.LT, g, G->mom_taps);
+    UMBIR_LAUNCH("plan_count", k_plan_count, cg, dim3(256), lds, s, G->legs, G->base, ms, G->P, K, G->nz, G->n_off, M,
+                 counts);
+    UMBIR_LAUNCH("plan_scan", k_plan_scan, dim3(unsigned(K)), dim3(1024), 0, s, M, chunks, cap, counts, G->mom_start,
+                 mb);
+    UMBIR_LAUNCH("plan_fill", k_plan_fill, cg, dim3(256), lds, s, G->legs, G->base, ms, G->P, K, G->nz, G->n_off, M,
+                 counts, keys);
+    with_r(R, [&](auto rc) {
+      UMBIR_LAUNCH("plan_emit", k_plan_emit<decltype(rc)::value>, dim3(unsigned(K), unsigned((M + 3) / 4)), dim3(256),
+                   0, s, G->legs, G->base, G->tau, ms, G->P, K, G->n_off, log2_int(Q), M, G->mom_start, keys, mb,
+                   G->mom_rec4, G->mom_rec_hi, G->mom_rec_off);
+    });
+    st = check_hip(hipGetLastError(), "moment plan");
+    if (!st) st = check_hip(hipMemcpyAsync(max_bin, mb, sizeof(int), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
+  }
+  (void)hipFreeAsync(tmp, s);
+  return st;
+}
+
+bool moment_plan_fits(int max_bin) { return max_bin <= kMaxBin; }
+
+}  // namespace umbir

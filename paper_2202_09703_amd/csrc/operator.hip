@@ -511,29 +511,6 @@ __device__ __forceinline__ void splat_body(int bx, int by,
   }
 }
 
-// CostFold's sums by the first 256 threads of a block of at least 256; sh:
-// 256 doubles of LDS, free before and after.
-__device__ void fold_cost(const CostFold& f, double* sh) {
-  const int t = threadIdx.x;
-  double v[2] = {0.0, 0.0};
-  if (t < 256) {
-    for (int i = t; i < f.n_ess; i += 256) v[0] += f.ess[i];
-    for (int i = t; i < f.n_p; i += 256) v[1] += f.pcost[i];
-  }
-  double r[2];
-  for (int k = 0; k < 2; ++k) {
-    if (t < 256) sh[t] = v[k];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if (t < w) sh[t] += sh[t + w];
-      __syncthreads();
-    }
-    r[k] = sh[0];
-    __syncthreads();
-  }
-  if (t == 0) *f.out = r[0] * f.inv_2s2 + r[1];
-}
-
 __global__ __launch_bounds__(256) void k_fold_cost(CostFold f) {
   __shared__ double sh[256];
   fold_cost(f, sh);
@@ -2437,7 +2414,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 
 }  // namespace
 
-void plan_sweeps(const umbir_geometry& G, int pi, BatchProb& bp, std::vector<int4>* items, size_t* lds) {
+void plan_sweeps(const umbir_geometry& G, bool mom, int pi, BatchProb& bp, std::vector<int4>* items, size_t* lds) {
   const int PK = G.traces(), N = G.voxels();
   bp.legs = G.legs;
   bp.legs_t = G.legs_t;
@@ -2462,6 +2439,11 @@ void plan_sweeps(const umbir_geometry& G, int pi, BatchProb& bp, std::vector<int
     bp.seg.lo[k] = G.seg_lo[k];
     bp.seg.hi[k] = G.seg_hi[k];
   }
+  bp.groups = G.trace_groups;
+  bp.tpg = (PK + G.trace_groups - 1) / G.trace_groups;
+  bp.gwin = G.gwin;
+  bp.mom = MomentShape{};
+  if (mom) return plan_moments(G, pi, bp, items, lds);
   // splat: as launch_splat_k without attenuation
   bp.chunk_bins = int(G.chunk_bins);
   bp.tile_bins = G.tile_bins;
@@ -2500,9 +2482,6 @@ void plan_sweeps(const umbir_geometry& G, int pi, BatchProb& bp, std::vector<int
   // gather: as run_adjoint_partial without attenuation, in the problem's
   // gather form
   {
-    bp.groups = G.trace_groups;
-    bp.tpg = (PK + G.trace_groups - 1) / G.trace_groups;
-    bp.gwin = G.gwin;
     const bool windowed = G.gather_form == 2 && G.gwin;
     int nb;
     if (windowed) {
@@ -2527,6 +2506,10 @@ int launch_sweep_stage(int stage, int Q, const BatchProb* probs, const int* acti
   if (L.n_items == 0) return UMBIR_OK;
   const dim3 grid(unsigned(L.grid));
   switch (stage) {
+    case kStMSplat:
+    case kStMConv:
+    case kStMCorr:
+    case kStMGather: return launch_moment_stage(stage, probs, active, L, which, s);
     case kStSplat:
       UMBIR_LAUNCH("splat", k_splat_list, grid, dim3(64 * kSplatWaves), L.lds, s, probs, active, L.items, L.n_items);
       break;
@@ -2589,12 +2572,13 @@ int run_prescale_blocks(const umbir_geometry& G, const float* x, void* fine, uns
 }
 
 int run_forward(const umbir_geometry& G, const float* x, void* out, const void* base, float sign,
-                const float* g, bool abs_op, void* fine, hipStream_t s, const unsigned* pre_max, int n_pre_max,
-                const CostFold* fold) {
+                const float* g, bool abs_op, bool mom, void* fine, hipStream_t s, const unsigned* pre_max,
+                int n_pre_max, const CostFold* fold) {
+  if (mom) return run_forward_moments(G, x, out, base, sign, g, fine, s, pre_max != nullptr, fold);
   // after the fine grid(s): the prescaled image tau x, then one 32-bit
   // scalar, the largest |tau x|
   float* xt = reinterpret_cast<float*>(static_cast<char*>(fine) + G.grids_bytes());
-  unsigned* xmax = reinterpret_cast<unsigned*>(static_cast<char*>(fine) + G.fine_bytes() - 4 * kPrescaleBlocks);
+  unsigned* xmax = reinterpret_cast<unsigned*>(static_cast<char*>(fine) + G.prescale_max_offset());
   int n_xmax = prescale_blocks(G);
   const int MQ = int(G.fine_per_trace());
   const int qs = log2_int(G.Q);
@@ -2689,8 +2673,9 @@ int run_forward(const umbir_geometry& G, const float* x, void* out, const void* 
   return UMBIR_OK;
 }
 
-int run_adjoint_partial(const umbir_geometry& G, const void* r, bool abs_op, void* fine, float* partial,
+int run_adjoint_partial(const umbir_geometry& G, const void* r, bool abs_op, bool mom, void* fine, float* partial,
                         hipStream_t s) {
+  if (mom) return run_adjoint_moments(G, static_cast<const float*>(r), fine, partial, s);
   const int MQ = int(G.fine_per_trace());
   const int qs = log2_int(G.Q);
   const int tpg = (G.traces() + G.trace_groups - 1) / G.trace_groups;
@@ -2776,9 +2761,9 @@ int run_adjoint_partial(const umbir_geometry& G, const void* r, bool abs_op, voi
   return UMBIR_OK;
 }
 
-int run_adjoint(const umbir_geometry& G, const void* r, float* out, float scale, bool abs_op,
+int run_adjoint(const umbir_geometry& G, const void* r, float* out, float scale, bool abs_op, bool mom,
                 void* fine, float* partial, hipStream_t s) {
-  int st = run_adjoint_partial(G, r, abs_op, fine, partial, s);
+  int st = run_adjoint_partial(G, r, abs_op, mom, fine, partial, s);
   if (st) return st;
   UMBIR_LAUNCH("reduce_groups", k_reduce_groups, dim3((G.voxels() + 255) / 256), dim3(256), 0, s, partial,
                G.trace_groups, G.voxels(), scale, out);
@@ -2838,7 +2823,7 @@ int umbir_forward(const umbir_geometry* G, const float* x, void* y, int accumula
   if (st) return st;
   Carve cv{static_cast<char*>(ws.ptr)};
   void* fine = cv.take<char>(G->fine_bytes());
-  return run_forward(*G, x, y, accumulate ? y : nullptr, 1.0f, nullptr, false, fine, s);
+  return run_forward(*G, x, y, accumulate ? y : nullptr, 1.0f, nullptr, false, forward_moments_on(*G), fine, s);
 }
 
 int umbir_adjoint(const umbir_geometry* G, const void* r, float* x, void* work, size_t work_bytes,
@@ -2851,7 +2836,7 @@ int umbir_adjoint(const umbir_geometry* G, const void* r, float* x, void* work, 
   Carve cv{static_cast<char*>(ws.ptr)};
   void* fine = cv.take<char>(G->fine_bytes());
   float* partial = cv.take<float>(size_t(G->trace_groups) * G->voxels());
-  return run_adjoint(*G, r, x, 1.0f, false, fine, partial, s);
+  return run_adjoint(*G, r, x, 1.0f, false, moments_on(*G), fine, partial, s);
 }
 
 int umbir_direct(const umbir_geometry* G, const float* g, void* y, int accumulate, void* stream) {
@@ -2872,8 +2857,8 @@ int umbir_sqs_denominator(const umbir_geometry* G, double sigma, float* d, void*
   void* fine = cv.take<char>(G->fine_bytes());
   float* partial = cv.take<float>(size_t(G->trace_groups) * G->voxels());
   void* col = cv.take<char>(G->trace_bytes());
-  if ((st = run_forward(*G, nullptr, col, nullptr, 1.0f, nullptr, true, fine, s))) return st;
-  return run_adjoint(*G, col, d, float(1.0 / (sigma * sigma)), true, fine, partial, s);
+  if ((st = run_forward(*G, nullptr, col, nullptr, 1.0f, nullptr, true, false, fine, s))) return st;
+  return run_adjoint(*G, col, d, float(1.0 / (sigma * sigma)), true, false, fine, partial, s);
 }
 
 int umbir_autotune(umbir_geometry* G, void* stream, umbir_tuning* chosen) {
@@ -2905,8 +2890,10 @@ int umbir_autotune(umbir_geometry* G, void* stream, umbir_tuning* chosen) {
     *ms /= 3.0f;
     return r;
   };
-  auto forward = [&]() { return run_forward(*G, nullptr, traces, nullptr, 1.0f, nullptr, false, fine, s); };
-  auto adjoint = [&]() { return run_adjoint(*G, traces, img, 1.0f, false, fine, partial, s); };
+  auto forward = [&]() {
+    return run_forward(*G, nullptr, traces, nullptr, 1.0f, nullptr, false, moments_on(*G), fine, s);
+  };
+  auto adjoint = [&]() { return run_adjoint(*G, traces, img, 1.0f, false, moments_on(*G), fine, partial, s); };
   // the operator's form: factored (splat + convolution, correlation +
   // gather) or direct, for an A + A^T pair with the current launch shapes
   if (direct_eligible(*G)) {

@@ -167,12 +167,15 @@ __global__ __launch_bounds__(256) void k_gstep(typename Store<ST>::T* __restrict
 // With xt set, the prior update also prepares the next forward: xt = tau
 // x_out by column (xt[col * nzp + row], the splat's layout), and per block
 // the largest |tau x_out| of its voxels into pmax[block] (as float bits),
-// from which the forward's splat takes the largest.
+// from which the forward's splat takes the largest.  For the moment form
+// (pitch > 0) xt instead receives x_out by phase of the pitch (moment.hip) and
+// there are no maxima; xt NULL: nothing to prepare.
 struct PriorFuse {
   const float* tau;
   float* xt;
   unsigned* pmax;
   int nzp;
+  int pitch, Lq, pad;
 };
 
 template <bool UPDATE>
@@ -240,7 +243,9 @@ __device__ __forceinline__ void prior_body(int bx, int by, const float* __restri
     const float grad = fmaf(-u, pc.inv_sigma2, slope);
     const float xn = xs - grad / (dv + curv);
     xout[v] = xn;
-    if (fz.xt) {
+    if (fz.pitch > 0) {
+      if (fz.xt) fz.xt[(size_t(row) * fz.pitch + col % fz.pitch) * fz.Lq + col / fz.pitch + fz.pad] = xn;
+    } else if (fz.xt) {
       const float t = fz.tau[row] * xn;
       fz.xt[size_t(col) * fz.nzp + row] = t;
       mbits = __float_as_uint(fabsf(t));
@@ -249,14 +254,15 @@ __device__ __forceinline__ void prior_body(int bx, int by, const float* __restri
   for (int off = 32; off > 0; off >>= 1) cost += __shfl_down(cost, off, 64);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = cost;
   __shared__ unsigned wmax[4];
-  if (UPDATE && fz.xt) {
+  const bool maxima = UPDATE && fz.xt && fz.pitch == 0;
+  if (maxima) {
     for (int off = 32; off >= 1; off >>= 1) mbits = max(mbits, unsigned(__shfl_xor(int(mbits), off)));
     if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = mbits;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     pcost[bx] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
-    if (UPDATE && fz.xt) fz.pmax[bx] = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+    if (maxima) fz.pmax[bx] = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
   }
 }
 
@@ -332,7 +338,7 @@ __global__ __launch_bounds__(4 * kPriorVox) void k_prior_list(const BatchProb* _
     const int4 w = items[it];
     if (!active[w.x]) continue;
     const BatchProb& p = probs[w.x];
-    const PriorFuse fz{p.tau, p.xt, p.pmax, p.nzp};
+    const PriorFuse fz{p.tau, p.xt, p.pmax, p.nzp, p.mom.pitch, p.mom.Lq, p.P - 1};
     prior_body<true>(w.y, 0, p.x[which], p.partial, p.groups, p.den, p.nx, p.nz, p.pc, p.x[which ^ 1], p.pcost, fz);
     __syncthreads();
   }
@@ -391,6 +397,7 @@ struct IterBuffers {
   double* pcost;
   unsigned* pmax;  // the prior update's per-block maxima of |tau x|
   int nblk;
+  bool mom;  // runs as moments, decided here once: the image the prior update leaves for the next forward is that form's
 };
 
 IterBuffers carve_iter(Carve& cv, const umbir_geometry& G) {
@@ -404,6 +411,7 @@ IterBuffers carve_iter(Carve& cv, const umbir_geometry& G) {
   b.ess = cv.take<double>(PK);
   b.pcost = cv.take<double>(b.nblk);
   b.pmax = cv.take<unsigned>(b.nblk);
+  b.mom = moments_on(G);
   return b;
 }
 
@@ -415,9 +423,9 @@ size_t iter_bytes(const umbir_geometry& G) {
 }
 
 int enqueue_curvature(const umbir_geometry& G, const IterBuffers& b, const PriorConst& pc, hipStream_t s) {
-  int st = run_forward(G, nullptr, b.e, nullptr, 1.0f, nullptr, true, b.fine, s);
+  int st = run_forward(G, nullptr, b.e, nullptr, 1.0f, nullptr, true, false, b.fine, s);
   if (st) return st;
-  return run_adjoint(G, b.e, b.den, pc.inv_sigma2, true, b.fine, b.partial, s);
+  return run_adjoint(G, b.e, b.den, pc.inv_sigma2, true, false, b.fine, b.partial, s);
 }
 
 // One surrogate iteration from x_in to x_out (or, with last, only the cost of
@@ -433,7 +441,7 @@ int enqueue_iteration(const umbir_geometry& G, const IterBuffers& b, const Prior
   // run_prescale_blocks before the first iteration, from the previous
   // iteration's prior update after that)
   const CostFold fold{b.ess, PK, b.pcost, b.nblk, inv_2s2, prev_cost};
-  int st = run_forward(G, x_in, b.e, y, -1.0f, g, false, b.fine, s, b.pmax, b.nblk, prev_cost ? &fold : nullptr);
+  int st = run_forward(G, x_in, b.e, y, -1.0f, g, false, b.mom, b.fine, s, b.pmax, b.nblk, prev_cost ? &fold : nullptr);
   if (st) return st;
   switch (G.storage) {
     case UMBIR_STORAGE_F16:
@@ -456,8 +464,11 @@ int enqueue_iteration(const umbir_geometry& G, const IterBuffers& b, const Prior
   } else {
     // the update also puts tau x_out and its block maxima in place for the
     // next iteration's forward
-    if ((st = run_adjoint_partial(G, b.e, false, b.fine, b.partial, s))) return st;
-    const PriorFuse fz{G.tau, reinterpret_cast<float*>(static_cast<char*>(b.fine) + G.grids_bytes()), b.pmax, G.nzp};
+    if ((st = run_adjoint_partial(G, b.e, false, b.mom, b.fine, b.partial, s))) return st;
+    const PriorFuse fz =
+        b.mom ? PriorFuse{G.tau, moment_image(G, b.fine), nullptr, G.nzp, G.mom.pitch, G.mom.Lq, G.P - 1}
+              : PriorFuse{G.tau, reinterpret_cast<float*>(static_cast<char*>(b.fine) + G.grids_bytes()), b.pmax, G.nzp,
+                          0, 0, 0};
     UMBIR_LAUNCH("prior", k_prior_fused<true>, dim3(b.nblk), dim3(4 * kPriorVox), 0, s, x_in, b.partial,
                  G.trace_groups, b.den, G.nx, G.nz, pc, x_out, b.pcost, fz);
   }
@@ -473,6 +484,7 @@ int enqueue_iteration(const umbir_geometry& G, const IterBuffers& b, const Prior
 // Before the first iteration from x: tau x and its block maxima into place
 // for the forward (the iterations' prior updates keep them in place after).
 int enqueue_start(const umbir_geometry& G, const IterBuffers& b, const float* x, hipStream_t s) {
+  if (b.mom) return run_phase_image(G, x, b.fine, s);
   return run_prescale_blocks(G, x, b.fine, b.pmax, b.nblk, s);
 }
 
@@ -975,11 +987,12 @@ int worklist_lane(umbir_batch* B, umbir_batch::Lane& L) {
     umbir_solver* S = B->s[L.members[i]];
     const umbir_geometry& G = *S->G;
     BatchProb& bp = probs[i];
-    plan_sweeps(G, i, bp, items, lds);
+    plan_sweeps(G, S->b.mom, i, bp, items, lds);
     bp.y = static_cast<const float*>(S->y);
     bp.e = static_cast<float*>(S->b.e);
     bp.fine = static_cast<float*>(S->b.fine);
-    bp.xt = reinterpret_cast<float*>(static_cast<char*>(S->b.fine) + G.grids_bytes());
+    bp.xt = S->b.mom ? moment_image(G, S->b.fine)
+                     : reinterpret_cast<float*>(static_cast<char*>(S->b.fine) + G.grids_bytes());
     bp.partial = S->b.partial;
     bp.den = S->b.den;
     bp.ess = S->b.ess;
@@ -1256,7 +1269,7 @@ int umbir_reconstruct_icd(const umbir_geometry* G, const umbir_prior* pr, const 
   }
   if ((st = check_hip(hipGetLastError(), "icd curvature"))) return st;
   // e = y - A x - D g
-  if ((st = run_forward(*G, x_io, e, y, -1.0f, g_io, false, fine, s))) return st;
+  if ((st = run_forward(*G, x_io, e, y, -1.0f, g_io, false, moments_on(*G), fine, s))) return st;
   for (int sw = 0; sw <= n_sweeps; ++sw) {
     const bool last = sw == n_sweeps;
     UMBIR_LAUNCH("gstep", k_gstep<UMBIR_STORAGE_F32>, dim3(unsigned(PK)), dim3(256), 0, s, e, G->dbasis, G->dnorm,

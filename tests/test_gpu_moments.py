@@ -1,0 +1,149 @@
+"""The moment form of the factored operator (the default with FP32 storage
+where the pulse and the scan positions allow it) against the FP64 oracle and
+against the fine-grid form (products = 1, which never runs as moments), on the
+shapes where it can go wrong: 5, 6 and 8 moments, one to many scan positions
+(lanes per record 4 to 64, and a second chunk of lanes), either scan
+direction, pitches of one voxel to more than the grid, ragged grids and
+records, records shorter than the window, traces beyond one tile.
+
+Tolerance: every result is a sum of FP32 terms through two FP32 roundings
+(moments, then samples or voxels) of relative size 2^-24 each and a remainder
+of the pulse's fit of at most 1e-8 of its peak; 2e-6 relative L2 leaves a
+factor of about 16 on the sum of their sizes, the bar the two product forms
+are held to."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from synth import tiny_card, random_vector
+from synth.cards import Acquisition, Array, Grid, MM, MHZ, US
+from oracle import operator as oo
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+umbir = pytest.importorskip("paper_2202_09703_amd.umbir")
+
+TOL = 2e-6
+
+
+def card(nx, nz, scans, rx, samples, mhz=20, pitch=1, f_c=0.5, layers=3, storage=0):
+    """1 mm x 0.5 mm voxels under `scans` positions `pitch` voxels apart (right
+    to left if negative); the 500 kHz pulse in a 12 us window (5 moments at 20
+    MHz, 6 at 10 MHz) or the 2 MHz pulse in a 3 us one (8 at 20 MHz)."""
+    c = tiny_card(n_layers=layers, nx=nx, nz=nz)
+    wide = f_c < 1
+    acq = Acquisition(n_samples=samples, fs=mhz * MHZ, f_c=f_c * MHZ, sigma_t=(1.25 if wide else 0.3) * US,
+                      t_win=(12 if wide else 3) * US, oversample=int(640 / mhz), storage=storage)
+    arr = Array(tx_x=tuple((pitch * (i - scans // 2) - 0.5 * (nx % 2 == 0)) * MM for i in range(scans)),
+                rx_offset=tuple((j - (rx - 1) / 2) * 2 * MM for j in range(rx)), beta=8)
+    return dataclasses.replace(c, acq=acq, array=arr, grid=Grid(nx=nx, nz=nz, dx=MM, dz=0.5 * MM, x0=-nx * MM / 2))
+
+
+CASES = {
+    "one-scan-r5": dict(nx=33, nz=20, scans=1, rx=3, samples=520),
+    "one-scan-r6": dict(nx=64, nz=31, scans=1, rx=8, samples=256, mhz=10),
+    "r8": dict(nx=40, nz=25, scans=6, rx=2, samples=300, pitch=3, f_c=2),
+    "two-scans-far": dict(nx=9, nz=14, scans=2, rx=2, samples=400, pitch=25),
+    "reversed": dict(nx=31, nz=18, scans=5, rx=3, samples=417, pitch=-2),
+    "16-lanes": dict(nx=37, nz=23, scans=13, rx=3, samples=301, pitch=4),
+    "64-lanes": dict(nx=29, nz=12, scans=37, rx=1, samples=333, pitch=1),
+    "two-chunks": dict(nx=70, nz=9, scans=70, rx=1, samples=290, pitch=1),
+    "short-record": dict(nx=20, nz=40, scans=3, rx=2, samples=100),
+    "one-sample": dict(nx=5, nz=3, scans=2, rx=1, samples=1),
+    "traces-over-a-tile": dict(nx=24, nz=10, scans=7, rx=11, samples=260, pitch=2),
+}
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def rel(a, b):
+    a, b = np.asarray(a, np.float64), np.asarray(b, np.float64)
+    return float(np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-300))
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_moments_match_oracle_and_fine_grid(dev, name):
+    c = card(**CASES[name])
+    geom = umbir.build_geometry(c)
+    x = random_vector((c.grid.nz, c.grid.nx), seed=5)
+    r = random_vector(geom.trace_shape, seed=6)
+    xt, rt = (torch.tensor(v, dtype=torch.float32, device=dev) for v in (x, r))
+    y, xa = umbir.forward(geom, xt), umbir.adjoint(geom, rt)
+    y2, xa2 = umbir.forward(geom, xt), umbir.adjoint(geom, rt)
+    assert torch.equal(y, y2) and torch.equal(xa, xa2)  # fixed order of every sum
+    acc = umbir.forward(geom, xt, rt.clone(), accumulate=True)
+    geom.set_tuning(products=1)
+    yf, xf = umbir.forward(geom, xt), umbir.adjoint(geom, rt)
+    x32, r32 = xt.cpu().numpy().astype(np.float64), rt.cpu().numpy().astype(np.float64)
+    yo, xo = oo.forward(c, x32), oo.adjoint(c, r32)
+    es = [rel(y.cpu(), yo), rel(xa.cpu(), xo), rel(yf.cpu(), yo), rel(xf.cpu(), xo)]
+    print(name, "forward, adjoint rel L2: moments %.2e %.2e, fine grid %.2e %.2e" % tuple(es))
+    if name != "one-sample":
+        assert np.linalg.norm(yo) > 0 and np.linalg.norm(xo) > 0
+        assert not torch.equal(y, yf) and not torch.equal(xa, xf)  # the moment form did run
+    assert max(es[:2]) <= TOL
+    assert rel(acc.cpu(), r32 + yo) <= TOL
+    geom.free()
+
+
+@pytest.mark.parametrize("kw", [dict(pitch=1.5), dict(tx=(-3.5, -1.5, 2.5))])
+def test_uneven_scan_positions_keep_the_fine_grid(dev, kw):
+    """Scan positions half a voxel or unevenly apart: the fine grid serves, to
+    the oracle."""
+    c = card(nx=20, nz=12, scans=3, rx=2, samples=300, pitch=kw.get("pitch", 1))
+    if "tx" in kw:
+        c = dataclasses.replace(c, array=dataclasses.replace(c.array, tx_x=tuple(t * MM for t in kw["tx"])))
+    geom = umbir.build_geometry(c)
+    x, r = random_vector((12, 20), seed=7), random_vector(geom.trace_shape, seed=8)
+    y = umbir.forward(geom, torch.tensor(x, dtype=torch.float32, device=dev))
+    xa = umbir.adjoint(geom, torch.tensor(r, dtype=torch.float32, device=dev))
+    assert rel(y.cpu(), oo.forward(c, x)) <= TOL and rel(xa.cpu(), oo.adjoint(c, r)) <= TOL
+    geom.free()
+
+
+@pytest.mark.parametrize("storage", [1, 2])
+def test_forward_with_16bit_traces(dev, storage):
+    """The forward alone runs as moments with 16-bit storage too: one rounding
+    of the result (half a unit of the last place at most), and of the base."""
+    c = card(nx=33, nz=20, scans=4, rx=3, samples=421, pitch=2, storage=storage)
+    geom = umbir.build_geometry(c)
+    x = random_vector((20, 33), seed=9)
+    xt = torch.tensor(x, dtype=torch.float32, device=dev)
+    yo = oo.forward(c, xt.cpu().numpy().astype(np.float64))
+    u = 2.0 ** -11 if storage == 1 else 2.0 ** -8
+    assert rel(umbir.forward(geom, xt).float().cpu(), yo) <= u
+    base = torch.tensor(random_vector(geom.trace_shape, seed=10), dtype=torch.float32, device=dev).to(geom.trace_dtype)
+    ref = base.double().cpu().numpy() + yo
+    assert rel(umbir.forward(geom, xt, base.clone(), accumulate=True).float().cpu(), ref) <= u
+    geom.free()
+
+
+@pytest.mark.parametrize("name", ["one-scan-r6", "16-lanes", "r8"])
+def test_worklist_and_session_equal_reconstruct(dev, name):
+    """Sessions and work-list batches (moment and fine-grid problems mixed) give
+    bitwise what umbir_reconstruct gives."""
+    c = card(**CASES[name])
+    uneven = dataclasses.replace(c, array=dataclasses.replace(c.array, tx_x=(-3.5 * MM, -2.5 * MM, 1.5 * MM)
+                                                              if c.grid.nx % 2 == 0 else (-3 * MM, -2 * MM, 2 * MM)))
+    runs = []
+    for k, cc in enumerate((c, uneven)):
+        geom = umbir.build_geometry(cc)
+        y = torch.tensor(random_vector(geom.trace_shape, seed=20 + k), dtype=torch.float32, device=dev)
+        ref = umbir.reconstruct(geom, cc.prior, 0.5, y, 4)
+        runs.append((geom, umbir.Solver(geom, cc.prior, 0.5, y, 4), ref))
+    batch = umbir.Batch([s for _, s, _ in runs], umbir.BATCH_WORKLIST)
+    batch.step(4)
+    for geom, s, (x, g, cost) in runs:
+        xs, gs, cs = s.read()
+        assert torch.equal(xs, x) and torch.equal(gs, g) and torch.equal(cs, cost)
+    batch.free()
+    for geom, s, _ in runs:
+        s.free()
+        geom.free()
