@@ -586,8 +586,7 @@ void umbir_geometry_free(umbir_geometry* G) {
   (void)hipGetDevice(&cur);
   if (G->device >= 0) (void)hipSetDevice(G->device);
   void* ptrs[] = {G->legs, G->legs_t, G->tau, G->base, G->bank, G->h, G->habs, G->dbasis, G->dnorm, G->gmask,
-                  G->gunit, G->gunit_t, G->gwin, G->mom_start, G->mom_rec4, G->mom_rec_hi, G->mom_rec_off,
-                  G->mom_taps};
+                  G->gunit, G->gunit_t, G->gwin, G->mom_start, G->mom_rec4, G->mom_rec_hi, G->mom_taps};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (cur >= 0) (void)hipSetDevice(cur);
@@ -837,8 +836,7 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
     const MomentShape& ms = G->mom;
     if ((st = alloc((void**)&G->mom_start, size_t(G->K) * (G->M + 1) * sizeof(int))) ||
         (st = alloc((void**)&G->mom_rec4, ms.records * sizeof(float4))) ||
-        (st = alloc((void**)&G->mom_rec_hi, ms.records * (ms.R - 4) * sizeof(float))) ||
-        (st = alloc((void**)&G->mom_rec_off, ms.records * sizeof(unsigned))) ||
+        (st = alloc((void**)&G->mom_rec_hi, ms.records * (ms.R - 3) * sizeof(float))) ||
         (st = alloc((void**)&G->mom_taps, size_t(ms.R) * 3 * ms.LT * sizeof(uint4))) ||
         (st = build_moments(G, &max_bin, s)))
       return bail(st);
@@ -851,12 +849,11 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
   if (!st) st = st2;
   if (!st && !moment_plan_fits(max_bin)) {  // the fine grid stays
     G->bytes -= G->mom.table_bytes;
-    void* tables[] = {G->mom_start, G->mom_rec4, G->mom_rec_hi, G->mom_rec_off, G->mom_taps};
+    void* tables[] = {G->mom_start, G->mom_rec4, G->mom_rec_hi, G->mom_taps};
     for (void* p : tables) (void)hipFree(p);
     G->mom_start = nullptr;
     G->mom_rec4 = nullptr;
     G->mom_rec_hi = nullptr;
-    G->mom_rec_off = nullptr;
     G->mom_taps = nullptr;
     G->mom = MomentShape{};
   }

@@ -277,8 +277,7 @@ struct umbir_geometry {
   umbir::MomentShape mom;
   int* mom_start = nullptr;         // [K][M + 1]
   float4* mom_rec4 = nullptr;       // [records] coefficients 0 .. 3
-  float* mom_rec_hi = nullptr;      // [records][R - 4] the others
-  unsigned* mom_rec_off = nullptr;  // [records] offset in the image by phase
+  float* mom_rec_hi = nullptr;      // [records][R - 3] the others, then the byte offset in the image by phase
   uint4* mom_taps = nullptr;        // [R][3][LT]
   size_t bytes = 0;
 
@@ -460,7 +459,6 @@ struct BatchProb {
   const int* mom_start;
   const float4* mom_rec4;
   const float* mom_rec_hi;
-  const unsigned* mom_rec_off;
   const uint4* mom_taps;
   int mom_tiles;                    // 32-sample tiles per block of its dense kernels
   int nblk;                         // prior-update blocks

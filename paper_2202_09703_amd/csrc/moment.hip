@@ -165,15 +165,15 @@ constexpr int kMaxBin = 8192;
 // One wave per (j, n): the bin's keys put in ascending order by counting the
 // smaller ones, and the records written in that order: coefficients
 // tau a_tx a_rx ((1 - phi) z_t^p + phi z_{t+1}^p) in double, rounded once, and
-// the offset of the voxel in the phase-major image (lane i of the splat adds
-// its scan position).
+// the byte offset of the voxel in the phase-major image (lane i of the splat
+// adds its scan position) in the word after them.
 template <int R>
 __global__ __launch_bounds__(256) void k_plan_emit(const Leg* __restrict__ legs, const int* __restrict__ base,
                                                    const float* __restrict__ tau, MomentShape ms, int P, int K,
                                                    int n_off, int qs, int M, const int* __restrict__ start,
                                                    const unsigned* __restrict__ keys,
                                                    const int* __restrict__ max_bin, float4* __restrict__ rec4,
-                                                   float* __restrict__ rec_hi, unsigned* __restrict__ rec_off) {
+                                                   float* __restrict__ rec_hi) {
   if (*max_bin > kMaxBin) return;
   const int j = blockIdx.x;
   const int n = blockIdx.y * 4 + (threadIdx.x >> 6);
@@ -210,10 +210,10 @@ __global__ __launch_bounds__(256) void k_plan_emit(const Leg* __restrict__ legs,
     }
     rec4[at] = make_float4(a[0], a[1], a[2], a[3]);
 #pragma unroll
-    for (int q = 4; q < R; ++q) rec_hi[size_t(at) * (R - 4) + (q - 4)] = a[q];
+    for (int q = 4; q < R; ++q) rec_hi[size_t(at) * (R - 3) + (q - 4)] = a[q];
     int rq = rel >= 0 ? rel / ms.pitch : -((-rel + ms.pitch - 1) / ms.pitch);  // floor
     const int phase = rel - rq * ms.pitch;
-    rec_off[at] = unsigned((row * ms.pitch + phase) * ms.Lq + rq + P - 1);
+    rec_hi[size_t(at) * (R - 3) + (R - 4)] = __uint_as_float(unsigned((row * ms.pitch + phase) * ms.Lq + rq + P - 1) * 4u);
   }
 }
 
@@ -273,90 +273,130 @@ __global__ void k_phase_image(const float* __restrict__ x, int nx, int nz, int P
 // ---- S
 
 // u of receiver bx, samples 16 by .. 16 by + 15, scan lanes 64 bz ...: a wave
-// takes a sample at a time, 64 of its records at a time: loaded one per lane,
-// parked in the wave's own LDS, then multiplied G = 64 / S records a step (S
-// lanes, a power of two >= 4, per record: one scan position each) on the
-// matrix cores, v_mfma_f32_4x4x1: lane l holds coefficient l % 4 of its
-// record (A) and the image element of its scan position (B), and the four
-// results of a lane are its moments 0 .. 3; higher moments take an FMA each.
-// Runs of 64 records sum in FP32, the runs in FP64.  The splat it replaces
-// (64-bit LDS atomics on the fine grid) was bound by address processing at
-// 118 clocks per 64 (trace, voxel) pairs and CU; a step here costs one
-// coalesced image load and three or four LDS reads.
+// takes four consecutive samples, 64 records of one at a time: loaded one per
+// lane (the next 64 are in flight meanwhile), parked in the wave's own LDS,
+// then multiplied G = 64 / S records a step (S lanes, a power of two >= 4, per
+// record: one scan position each) on the matrix cores, v_mfma_f32_4x4x1: lane l
+// holds coefficient l % 4 of its record (A) and the image element of its scan
+// position (B), and the four results of a lane are its moments 0 .. 3; higher
+// moments take an FMA each, or a second product.  Records past a sample's end
+// have coefficients zero, so steps need no masks and eight image loads are in
+// flight together.  Runs of 64 records sum in FP32, the runs in FP64.
+//
+// The splat this replaces (64-bit LDS atomics on the fine grid) was bound by
+// address processing at 118 clocks per 64 (trace, voxel) pairs and CU.  A step
+// here costs one coalesced image load (L1), two LDS reads and about five
+// vector instructions.
 constexpr int kMsBins = 16;   // samples per block
 constexpr int kMsWaves = 4;
 
+// LDS words of a parked record: R coefficients, the offset, padding
 template <int R>
-__host__ __device__ constexpr int msplat_chunk_words() { return 64 * (R + 1); }
+__host__ __device__ constexpr int msplat_rec_words() { return R < 8 ? 8 : 12; }
+
+template <int R, int LS>
+__device__ __forceinline__ void msplat_steps(const float* recs, int lane, unsigned xl4, __amdgpu_buffer_rsrc_t xrs,
+                                             int steps, floatx4& d, float (&dh)[4]) {
+  constexpr int W = msplat_rec_words<R>();
+  constexpr int G = 64 >> LS;
+  constexpr int U = 64 / G < 8 ? 64 / G : 8;  // 64 / G is a multiple of U
+  const float* mine = recs + (lane >> LS) * W;
+  for (int k0 = 0; k0 < steps; k0 += U) {
+    const float* r = mine + k0 * G * W;
+    float xv[U], a[U], hi[U][R - 4];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const float* rq = r + q * G * W;
+      a[q] = rq[lane & 3];
+      if constexpr (R < 8) {
+#pragma unroll
+        for (int w = 0; w < R - 4; ++w) hi[q][w] = rq[4 + w];
+      } else {
+        hi[q][0] = rq[4 + (lane & 3)];
+      }
+      xv[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                            xrs, int(__float_as_uint(rq[R]) + xl4), 0, 0));
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      d = __builtin_amdgcn_mfma_f32_4x4x1f32(a[q], xv[q], d, 0, 0, 0);
+      if constexpr (R < 8) {
+#pragma unroll
+        for (int w = 0; w < R - 4; ++w) dh[w] = fmaf(hi[q][w], xv[q], dh[w]);
+      } else {
+        floatx4 d2 = {dh[0], dh[1], dh[2], dh[3]};
+        d2 = __builtin_amdgcn_mfma_f32_4x4x1f32(hi[q][0], xv[q], d2, 0, 0, 0);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) dh[w] = d2[w];
+      }
+    }
+  }
+}
 
 template <int R>
 __device__ __forceinline__ void msplat_body(int bx, int by, int bz, const float* __restrict__ xp, int xp_bytes,
                                             const int* __restrict__ start, const float4* __restrict__ rec4,
-                                            const float* __restrict__ rec_hi, const unsigned* __restrict__ rec_off,
-                                            int P, int K, int M, int Ms, int ls, int reversed,
-                                            float* __restrict__ u) {
+                                            const float* __restrict__ rec_hi, int P, int K, int M, int Ms, int ls,
+                                            int reversed, float* __restrict__ u) {
   extern __shared__ __align__(16) float sm[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int S = 1 << ls, G = 64 >> ls;
-  float4* c4 = reinterpret_cast<float4*>(sm) + wave * 64;                       // [64] moments 0 .. 3
-  float* chi = sm + kMsWaves * 256 + wave * 64 * (R - 4);                       // [64][R - 4]
-  unsigned* cof = reinterpret_cast<unsigned*>(sm + kMsWaves * 64 * R) + wave * 64;  // [64]
-  float* outu = sm + kMsWaves * msplat_chunk_words<R>();                        // [R][S][kMsBins + 1]
+  constexpr int W = msplat_rec_words<R>();
+  constexpr int NB = kMsBins / kMsWaves;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int S = 1 << ls, sh = 6 - ls;
+  float* recs = sm + wave * 64 * W;           // [64][W]
+  float* outu = sm + kMsWaves * 64 * W;       // [R][S][kMsBins + 1]
   const __amdgpu_buffer_rsrc_t xrs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xp), 0, xp_bytes, kBufferWord3);
-  const int j = bx, n0 = by * kMsBins;
-  const int sl = lane & (S - 1), grp = lane >> ls;
-  const unsigned xl = unsigned(64 * bz + sl);  // this lane's scan position
-  const float* c4f = reinterpret_cast<const float*>(c4) + (lane & 3);
-  for (int b = wave; b < kMsBins; b += kMsWaves) {
-    const int n = n0 + b;
+  const int j = bx, n0 = by * kMsBins, nw = n0 + NB * wave;
+  const unsigned xl4 = unsigned(64 * bz + (lane & (S - 1))) * 4u;  // this lane's scan position
+  // the records of the wave's samples: [at[b], at[b + 1])
+  const int* sj = start + size_t(j) * (M + 1);
+  int at[NB + 1];
+#pragma unroll
+  for (int b = 0; b <= NB; ++b) at[b] = sj[min(nw + b, M)];
+  float4 v4;
+  float vh[R - 3];
+  auto load = [&](int c, int e) {  // records c .. c + 63 (past e: e - 1)
+    const int i = max(min(c + lane, e - 1), 0);
+    v4 = rec4[i];
+#pragma unroll
+    for (int q = 0; q < R - 3; ++q) vh[q] = rec_hi[size_t(i) * (R - 3) + q];
+  };
+  load(at[0], at[1]);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int e = at[b + 1];
     double acc[R];
 #pragma unroll
     for (int p = 0; p < R; ++p) acc[p] = 0.0;
-    if (n < M) {
-      const int s = start[size_t(j) * (M + 1) + n], e = start[size_t(j) * (M + 1) + n + 1];
-      for (int c = s; c < e; c += 64) {
-        {  // past the end: the bin's last record with coefficients zero
-          const int i = min(c + lane, e - 1);
-          const bool in = c + lane < e;
-          const float4 v = rec4[i];
-          float hi[R - 4];
+    if (at[b] == e && b + 1 < NB) load(e, at[b + 2]);
+    for (int c = at[b]; c < e; c += 64) {
+      {
+        const bool in = c + lane < e;
+        float* r = recs + lane * W;
+        __builtin_amdgcn_wave_barrier();
+        *reinterpret_cast<float4*>(r) = in ? v4 : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
-          for (int q = 0; q < R - 4; ++q) hi[q] = rec_hi[size_t(i) * (R - 4) + q];
-          const unsigned o = rec_off[i];
-          __builtin_amdgcn_wave_barrier();
-          c4[lane] = in ? v : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-          for (int q = 0; q < R - 4; ++q) chi[lane * (R - 4) + q] = in ? hi[q] : 0.0f;
-          cof[lane] = o;
-          __builtin_amdgcn_wave_barrier();
-        }
-        floatx4 d = {0.0f, 0.0f, 0.0f, 0.0f};
-        float dh[R - 4] = {};
-        const int steps = (min(64, e - c) + G - 1) >> (6 - ls);
-        constexpr int U = 8;
-        for (int k0 = 0; k0 < steps; k0 += U) {
-          float xv[U];
-#pragma unroll
-          for (int q = 0; q < U; ++q) {
-            const int r = (min(k0 + q, steps - 1) << (6 - ls)) + grp;
-            xv[q] = __builtin_bit_cast(
-                float, __builtin_amdgcn_raw_buffer_load_b32(xrs, int((cof[r] + xl) * 4u), 0, 0));
-          }
-#pragma unroll
-          for (int q = 0; q < U; ++q) {
-            if (k0 + q >= steps) break;
-            const int r = ((k0 + q) << (6 - ls)) + grp;
-            d = __builtin_amdgcn_mfma_f32_4x4x1f32(c4f[4 * r], xv[q], d, 0, 0, 0);
-#pragma unroll
-            for (int w = 0; w < R - 4; ++w) dh[w] = fmaf(chi[r * (R - 4) + w], xv[q], dh[w]);
-          }
-        }
-#pragma unroll
-        for (int p = 0; p < 4; ++p) acc[p] += double(d[p]);
-#pragma unroll
-        for (int p = 4; p < R; ++p) acc[p] += double(dh[p - 4]);
+        for (int q = 0; q < R - 4; ++q) r[4 + q] = in ? vh[q] : 0.0f;
+        r[R] = vh[R - 4];
+        __builtin_amdgcn_wave_barrier();
       }
+      if (c + 64 < e) load(c + 64, e);
+      else if (b + 1 < NB) load(e, at[b + 2]);
+      floatx4 d = {0.0f, 0.0f, 0.0f, 0.0f};
+      float dh[4] = {};
+      const int steps = (min(64, e - c) + (1 << sh) - 1) >> sh;
+      switch (ls) {
+        case 2: msplat_steps<R, 2>(recs, lane, xl4, xrs, steps, d, dh); break;
+        case 3: msplat_steps<R, 3>(recs, lane, xl4, xrs, steps, d, dh); break;
+        case 4: msplat_steps<R, 4>(recs, lane, xl4, xrs, steps, d, dh); break;
+        case 5: msplat_steps<R, 5>(recs, lane, xl4, xrs, steps, d, dh); break;
+        default: msplat_steps<R, 6>(recs, lane, xl4, xrs, steps, d, dh); break;
+      }
+#pragma unroll
+      for (int p = 0; p < 4; ++p) acc[p] += double(d[p]);
+#pragma unroll
+      for (int p = 4; p < R; ++p) acc[p] += double(dh[p - 4]);
     }
     for (int off = S; off < 64; off <<= 1) {
 #pragma unroll
@@ -364,7 +404,7 @@ __device__ __forceinline__ void msplat_body(int bx, int by, int bz, const float*
     }
     if (lane < S) {
 #pragma unroll
-      for (int p = 0; p < R; ++p) outu[(p * S + lane) * (kMsBins + 1) + b] = float(acc[p]);
+      for (int p = 0; p < R; ++p) outu[(p * S + lane) * (kMsBins + 1) + NB * wave + b] = float(acc[p]);
     }
   }
   __syncthreads();
@@ -382,23 +422,21 @@ static_assert(kMsBins == 16, "msplat_body's index shifts");
 
 template <int R>
 size_t msplat_lds(int ls) {
-  return size_t(kMsWaves * msplat_chunk_words<R>() + R * (1 << ls) * (kMsBins + 1)) * sizeof(float);
+  return size_t(kMsWaves * 64 * msplat_rec_words<R>() + R * (1 << ls) * (kMsBins + 1)) * sizeof(float);
 }
 
 template <int R>
 __global__ __launch_bounds__(64 * kMsWaves) void k_msplat(const float* __restrict__ xp, int xp_bytes,
                                                           const int* __restrict__ start,
                                                           const float4* __restrict__ rec4,
-                                                          const float* __restrict__ rec_hi,
-                                                          const unsigned* __restrict__ rec_off, int P, int K, int M,
+                                                          const float* __restrict__ rec_hi, int P, int K, int M,
                                                           int Ms, int ls, int reversed, float* __restrict__ u,
                                                           CostFold fold) {
   if (fold.out && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) {  // uniform
     extern __shared__ __align__(16) float sm[];
     fold_cost(fold, reinterpret_cast<double*>(sm));
   }
-  msplat_body<R>(blockIdx.x, blockIdx.y, blockIdx.z, xp, xp_bytes, start, rec4, rec_hi, rec_off, P, K, M, Ms, ls,
-                 reversed, u);
+  msplat_body<R>(blockIdx.x, blockIdx.y, blockIdx.z, xp, xp_bytes, start, rec4, rec_hi, P, K, M, Ms, ls, reversed, u);
 }
 
 // ---- C and C^T: banded Toeplitz products on the bf16 matrix cores, FP32
@@ -835,8 +873,7 @@ __global__ __launch_bounds__(64 * kMsWaves) void k_msplat_list(const BatchProb* 
     const float* xp = p.P == 1 ? p.x[which] : p.xt;
     with_r_device(p.mom.R, [&](auto rc) {
       msplat_body<decltype(rc)::value>(w.y, w.z, w.w, xp, p.nz * p.mom.pitch * p.mom.Lq * 4, p.mom_start, p.mom_rec4,
-                                       p.mom_rec_hi, p.mom_rec_off, p.P, p.K, p.M, p.mom.Ms, p.mom.ls, p.mom.reversed,
-                                       p.fine);
+                                       p.mom_rec_hi, p.P, p.K, p.M, p.mom.Ms, p.mom.ls, p.mom.reversed, p.fine);
     });
     __syncthreads();
   }
@@ -974,7 +1011,7 @@ int run_forward_moments(const umbir_geometry& G, const float* x, void* out, cons
     const size_t lds = std::max<size_t>(fold ? 256 * sizeof(double) : 0, msplat_lds<R>(G.mom.ls));
     const dim3 grid(unsigned(G.K), unsigned(G.mom.Ms / kMsBins), unsigned((G.P + 63) / 64));
     UMBIR_LAUNCH("splat", k_msplat<R>, grid, dim3(64 * kMsWaves), lds, s, xp, xp_bytes, G.mom_start, G.mom_rec4,
-                 G.mom_rec_hi, G.mom_rec_off, G.P, G.K, G.M, G.mom.Ms, G.mom.ls, G.mom.reversed, u, f);
+                 G.mom_rec_hi, G.P, G.K, G.M, G.mom.Ms, G.mom.ls, G.mom.reversed, u, f);
   });
   if ((st = check_hip(hipGetLastError(), "k_msplat"))) return st;
   with_r(G.mom.R, [&](auto rc) {
@@ -1013,7 +1050,6 @@ void plan_moments(const umbir_geometry& G, int pi, BatchProb& bp, std::vector<in
   bp.mom_start = G.mom_start;
   bp.mom_rec4 = G.mom_rec4;
   bp.mom_rec_hi = G.mom_rec_hi;
-  bp.mom_rec_off = G.mom_rec_off;
   bp.mom_taps = G.mom_taps;
   bp.mom_tiles = moment_tiles(G);
   const int tt = (G.traces() + 31) / 32, nt = bp.mom_tiles;
@@ -1194,7 +1230,7 @@ int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s) {
     with_r(R, [&](auto rc) {
       UMBIR_LAUNCH("plan_emit", k_plan_emit<decltype(rc)::value>, dim3(unsigned(K), unsigned((M + 3) / 4)), dim3(256),
                    0, s, G->legs, G->base, G->tau, ms, G->P, K, G->n_off, log2_int(Q), M, G->mom_start, keys, mb,
-                   G->mom_rec4, G->mom_rec_hi, G->mom_rec_off);
+                   G->mom_rec4, G->mom_rec_hi);
     });
     st = check_hip(hipGetLastError(), "moment plan");
     if (!st) st = check_hip(hipMemcpyAsync(max_bin, mb, sizeof(int), hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
