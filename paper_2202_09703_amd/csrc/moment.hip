@@ -679,10 +679,22 @@ __global__ __launch_bounds__(64 * kMcWaves) void k_mcorr(const float* __restrict
 // geometry's table of (tile, trace) windows) is copied into LDS with 16-byte
 // loads, one trace ahead, into the other of two buffers (one barrier per
 // trace), and every voxel evaluates its polynomial at its two table points
-// and interpolates.  A window longer than a buffer reads v from memory.  The
-// window is Q / R times smaller than the fine grid's, so almost every window
-// fits (of 1632 .. 2048 samples) and two buffers do.  One partial image per
-// group, traces in order.
+// and interpolates.  The window is Q / R times smaller than the fine grid's,
+// so two buffers fit.  One partial image per group, traces in order.
+//
+// A window longer than a buffer (2048 samples at R = 5) is staged into both,
+// without a trace in flight beside it, and one longer than both is read from
+// memory.  Such windows belong to tiles that straddle the top layer's face:
+// one row of tiles of 16 at 512 x 512, 4096 samples, where a third of them read
+// from memory paced the whole launch, 1345 us against 1088 us staged.  A
+// block's tiles lie a whole generation of blocks apart, so that no block has
+// two of them: 927 us.  (Tiles that stop at layers' faces instead: 1160 us, and
+// 12 % more of them.)  Bound by its vector instructions (38 per wave and
+// trace-voxel, 56 % of the cycles at 256 x 256), the load unit (55 %) and LDS
+// (35 %), which the barrier of each trace keeps from overlapping fully.
+// Sharing a record between voxels a pitch apart, four traces a barrier and
+// windows dealt to the waves piece by piece halved single shares of these but
+// not the time (57 .. 95 us against 57 at 256 x 256, 910 .. 1440 at 512 x 512).
 constexpr int kMgBufBytes = 40960;  // one window buffer; two per block, two blocks per CU
 
 template <int R>
@@ -702,14 +714,14 @@ __device__ __forceinline__ void mgather_body(int bx, int by, const float* __rest
   const int t0 = bx * tpg, t1 = min(t0 + tpg, PK);
   const int tiles_x = (nx + kGatherTileCols - 1) / kGatherTileCols;
   const int n_tiles = tiles_x * ((nz + kGatherTileRows - 1) / kGatherTileRows);
-  const int tile_end = min(n_tiles, (by + 1) * tiles_per_block);
+  const int blocks = (n_tiles + tiles_per_block - 1) / tiles_per_block;
   const int half = n_off / 2;
   const int wave = int(threadIdx.x >> 6), lane = int(threadIdx.x & 63);
   const float h = 2.0f / float(1 << qs);
   const __amdgpu_buffer_rsrc_t leg_rs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<Leg*>(legs), 0, nz * n_off * int(sizeof(Leg)), kBufferWord3);
   struct Legs { int64_t d[VPT]; float p[VPT]; };
-  for (int tile = by * tiles_per_block; tile < tile_end; ++tile) {
+  for (int tile = by; tile < n_tiles; tile += blocks) {
     const int tz = tile / tiles_x;
     const int tx = tile - tz * tiles_x;
     int col2[VPT], rowoff[VPT], vox[VPT];
@@ -764,24 +776,40 @@ __device__ __forceinline__ void mgather_body(int bx, int by, const float* __rest
       }
     };
     Legs TX, La, Lb;
-    auto add = [&](const Legs& L, int2 W, int t, const float* buf) {
+    // a window of up to both buffers, planes 2 kCap apart
+    auto stage_long = [&](int2 W, int t) {
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<float*>(v + size_t(t) * R * Ms), 0, R * Ms * 4, kBufferWord3);
+#pragma unroll 1
+      for (int x = x4; x < W.y; x += 4 * 512) {
+        uint4 q[R];
+#pragma unroll
+        for (int p = 0; p < R; ++p) {
+          const auto d = __builtin_amdgcn_raw_buffer_load_b128(rs, (p * Ms + W.x + x) * 4, 0, 0);
+          q[p] = make_uint4(d[0], d[1], d[2], d[3]);
+        }
+#pragma unroll
+        for (int p = 0; p < R; ++p) *reinterpret_cast<uint4*>(sm + p * 2 * kCap + x) = q[p];
+      }
+    };
+    auto add = [&](const Legs& L, int2 W, int t, const float* buf, int plane) {
       if (W.y == 0) return;
-      const bool fits = W.y <= kCap;
+      const bool fits = W.y <= plane;
       const float* vt = v + size_t(t) * R * Ms;
 #pragma unroll
       for (int q = 0; q < VPT; ++q) {
         const uint64_t D = uint64_t(TX.d[q] + L.d[q]);
-        const unsigned n = unsigned(min(D >> 32, uint64_t(M)));
+        const unsigned n = unsigned(D >> 32);
         const bool in = n < unsigned(M);
         const unsigned fr = unsigned(D);
-        const float w = in ? TX.p[q] * L.p[q] : 0.0f;
+        const float w = TX.p[q] * L.p[q];
         const float z0 = fmaf(float(fr >> (32 - qs)), h, -1.0f), z1 = z0 + h;
         const float phi = float(fr << qs) * 2.3283064365386963e-10f;
         float c[R];
         if (fits) {
           const float* s = buf + (in ? int(n) - W.x : 0);
 #pragma unroll
-          for (int p = 0; p < R; ++p) c[p] = s[p * kCap];
+          for (int p = 0; p < R; ++p) c[p] = s[p * plane];
         } else {
           const float* s = vt + (in ? n : 0u);
 #pragma unroll
@@ -793,7 +821,8 @@ __device__ __forceinline__ void mgather_body(int bx, int by, const float* __rest
           f0 = fmaf(f0, z0, c[p]);
           f1 = fmaf(f1, z1, c[p]);
         }
-        acc[q] = fmaf(w, fmaf(phi, f1 - f0, f0), acc[q]);
+        const float sum = fmaf(w, fmaf(phi, f1 - f0, f0), acc[q]);
+        acc[q] = in ? sum : acc[q];
       }
     };
     if (t0 < t1) {
@@ -818,7 +847,16 @@ __device__ __forceinline__ void mgather_body(int bx, int by, const float* __rest
           load_leg(base[scan], TX);
         }
         const int2 W2 = window(t + 2);
-        add(L, Wc, t, cur);
+        if (Wc.y > kCap) {  // uniform
+          if (Wc.y <= 2 * kCap) {
+            stage_long(Wc, t);
+            __syncthreads();
+          }
+          add(L, Wc, t, sm, 2 * kCap);
+          __syncthreads();
+        } else {
+          add(L, Wc, t, cur, kCap);
+        }
         stage_store(Wn, nxt, rg);
         stage_load(W2, t + 2, rg);
         Wc = Wn;

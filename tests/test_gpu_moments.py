@@ -18,6 +18,7 @@ import pytest
 
 from synth import tiny_card, random_vector
 from synth.cards import Acquisition, Array, Grid, MM, MHZ, US
+from oracle import geometry as og
 from oracle import operator as oo
 
 pytestmark = pytest.mark.gpu
@@ -90,6 +91,27 @@ def test_moments_match_oracle_and_fine_grid(dev, name):
         assert not torch.equal(y, yf) and not torch.equal(xa, xf)  # the moment form did run
     assert max(es[:2]) <= TOL
     assert rel(acc.cpu(), r32 + yo) <= TOL
+    geom.free()
+
+
+@pytest.mark.parametrize("scale, lo, hi", [(3, 2048, 4096), (5, 3500, 4800), (8, 5600, 7700)])
+def test_long_gather_windows(dev, scale, lo, hi):
+    """Voxels of 3, 5 and 8 mm under a slow top layer: the top tiles' windows
+    take both LDS buffers (2048 samples each), either, or neither."""
+    c = card(nx=70, nz=34, scans=3, rx=2, samples=9000)
+    arr = dataclasses.replace(c.array, beta=0, tx_x=tuple(scale * t for t in c.array.tx_x),
+                              rx_offset=tuple(scale * t for t in c.array.rx_offset))
+    c = dataclasses.replace(c, array=arr, grid=dataclasses.replace(c.grid, dx=scale * MM, x0=scale * c.grid.x0))
+    for i in range(3):
+        for j in range(2):
+            d = og.trace_geometry(c, i, j, np.arange(70 * 34))[0].reshape(34, 70)[:32]
+            for tile in (d[:, :64], d[:, 64:]):
+                assert lo < np.ptp(tile) < hi and tile.max() < 9000
+    geom = umbir.build_geometry(c)
+    r = torch.tensor(random_vector(geom.trace_shape, seed=11), dtype=torch.float32, device=dev)
+    xa = umbir.adjoint(geom, r)
+    assert torch.equal(umbir.adjoint(geom, r), xa)
+    assert rel(xa.cpu(), oo.adjoint(c, r.cpu().numpy().astype(np.float64))) <= TOL
     geom.free()
 
 
