@@ -379,6 +379,29 @@ int run_forward_moments(const umbir_geometry& G, const float* x, void* out, cons
                         const float* g, void* fine, hipStream_t s, bool in_place, const CostFold* fold);
 int run_adjoint_moments(const umbir_geometry& G, const float* r, void* fine, float* partial, hipStream_t s);
 
+// A group of ICD's voxels (solver.hip): the class (row % Sr, col % Sc).
+struct IcdGroup {
+  int r0, c0;  // first row and column of the class
+  int gr;      // rows in the group
+  int size;    // members
+};
+
+// Member i of a group, rows fastest: neighbouring lanes take members of one
+// column Sr rows apart, whose delays differ by far more than those of
+// neighbouring columns, so their windows meet fewer common samples at once.
+__device__ __forceinline__ void icd_member(const IcdGroup& gp, int Sr, int Sc, int i, int* row, int* col) {
+  const int cc = i / gp.gr;
+  *row = gp.r0 + (i - cc * gp.gr) * Sr;
+  *col = gp.c0 + cc * Sc;
+}
+
+// Its trace sums A_t^T e_t and its residual update as moments; mom: u_bytes of
+// workspace each.
+int run_icd_dots_moments(const umbir_geometry& G, const float* e, const IcdGroup& gp, int Sr, int Sc, float* mom,
+                         float* partial, hipStream_t s);
+int run_icd_update_moments(const umbir_geometry& G, const IcdGroup& gp, int Sr, int Sc, const float* delta, float* mom,
+                           float* e, hipStream_t s);
+
 // Queues the building of the moment tables (allocated by the caller); the
 // largest number of records of one sample goes to *max_bin, and the tables
 // hold only if moment_plan_fits(*max_bin) once the stream was synchronized.

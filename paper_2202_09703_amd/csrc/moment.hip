@@ -883,6 +883,112 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(R < 8 ? 4 :
                   tiles_per_block, partial);
 }
 
+// ---- grouped ICD: one group's columns of A against e, and their sum
+
+// delay (Q32.32 samples), weight and the two table points of member i of a
+// group in trace t
+struct IcdMember {
+  unsigned n;
+  float z0, phi, w;
+};
+__device__ __forceinline__ IcdMember icd_moment_member(const Leg* __restrict__ legs, int n_off,
+                                                       const float* __restrict__ tau, int bt, int br,
+                                                       const IcdGroup& gp, int Sr, int Sc, int qs, int i) {
+  int row, col;
+  icd_member(gp, Sr, Sc, i, &row, &col);
+  const PairLegs p = pair_legs(legs, n_off, bt, br, row, col);
+  const unsigned fr = unsigned(p.D);
+  const float h = 2.0f / float(1 << qs);
+  return {unsigned(p.D >> 32), fmaf(float(fr >> (32 - qs)), h, -1.0f), float(fr << qs) * 2.3283064365386963e-10f,
+          tau[row] * p.w};
+}
+
+// partial[i][t] = A_{t, v_i}^T e_t from v (v_p[n] of e): a block per trace, one
+// thread per member, v of the trace in LDS as far as planes fit (`planes`; the
+// others are read from memory).
+template <int R>
+__global__ __launch_bounds__(1024) void k_icd_mdots(const float* __restrict__ v, int Ms, int planes,
+                                                    const Leg* __restrict__ legs, int n_off,
+                                                    const float* __restrict__ tau, const int* __restrict__ base,
+                                                    int P, int K, int qs, int M, IcdGroup gp, int Sr, int Sc,
+                                                    float* __restrict__ partial) {
+  extern __shared__ __align__(16) float sm[];  // [planes][Ms]
+  const int t = blockIdx.x;
+  const float* vt = v + size_t(t) * R * Ms;
+  for (int k = threadIdx.x; k < planes * Ms / 4; k += blockDim.x)
+    reinterpret_cast<float4*>(sm)[k] = reinterpret_cast<const float4*>(vt)[k];
+  const int bt = base[t / K], br = base[P + t];
+  const float h = 2.0f / float(1 << qs);
+  __syncthreads();
+  for (int i = blockIdx.y * blockDim.x + threadIdx.x; i < gp.size; i += gridDim.y * blockDim.x) {
+    const IcdMember mb = icd_moment_member(legs, n_off, tau, bt, br, gp, Sr, Sc, qs, i);
+    float f0 = 0.0f, f1 = 0.0f;
+    if (mb.n < unsigned(M)) {
+      const float z1 = mb.z0 + h;
+#pragma unroll
+      for (int p = R - 1; p >= 0; --p) {
+        const float c = p < planes ? sm[p * Ms + mb.n] : vt[size_t(p) * Ms + mb.n];
+        f0 = fmaf(f0, mb.z0, c);
+        f1 = fmaf(f1, z1, c);
+      }
+    }
+    partial[size_t(i) * gridDim.x + t] = mb.w * fmaf(mb.phi, f1 - f0, f0);
+  }
+}
+
+// u_p[n] = sum_i delta_i w a_p of the group's members, `planes` of the R at a
+// time in 64-bit fixed point in LDS (bitwise reproducible).  |a_p|, |w| <= 1,
+// so the scale of k_icd_scatter keeps every sum below 2^62.
+template <int R>
+__global__ __launch_bounds__(1024) void k_icd_msplat(float* __restrict__ u, int Ms, int planes,
+                                                     const Leg* __restrict__ legs, int n_off,
+                                                     const float* __restrict__ tau, const int* __restrict__ base,
+                                                     int P, int K, int qs, int M, IcdGroup gp, int Sr, int Sc,
+                                                     const float* __restrict__ delta) {
+  extern __shared__ __align__(16) unsigned long long sums[];  // [planes][Ms]
+  __shared__ float wmax[16];
+  const int t = blockIdx.x;
+  float mx = 0.0f;
+  for (int i = threadIdx.x; i < gp.size; i += blockDim.x) mx = fmaxf(mx, fabsf(delta[i]));
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = mx;
+  __syncthreads();
+  float dmax = 0.0f;
+  for (int k = 0; k < int(blockDim.x >> 6); ++k) dmax = fmaxf(dmax, wmax[k]);
+  int lg = 0;
+  while ((1 << lg) < gp.size) ++lg;
+  const int kx = dmax > 0.0f ? 61 - lg - ilogbf(dmax) : 0;
+  const double scale = ldexp(1.0, kx);
+  const int bt = base[t / K], br = base[P + t];
+  const float h = 2.0f / float(1 << qs);
+  float* ut = u + size_t(t) * R * Ms;
+  for (int p0 = 0; p0 < R; p0 += planes) {
+    const int np = min(planes, R - p0);
+    for (int k = threadIdx.x; k < np * Ms; k += blockDim.x) sums[k] = 0ull;
+    __syncthreads();
+    for (int i = threadIdx.x; i < gp.size; i += blockDim.x) {
+      const float dl = delta[i];
+      if (dl == 0.0f) continue;
+      const IcdMember mb = icd_moment_member(legs, n_off, tau, bt, br, gp, Sr, Sc, qs, i);
+      if (mb.n >= unsigned(M)) continue;
+      const float z1 = mb.z0 + h;
+      float a1 = dl * mb.w * mb.phi, a0 = dl * mb.w * (1.0f - mb.phi);
+#pragma unroll
+      for (int p = 0; p < R; ++p) {
+        if (p >= p0 && p < p0 + np)
+          atomicAdd(&sums[(p - p0) * Ms + mb.n],
+                    static_cast<unsigned long long>(__double2ll_rn((double(a0) + double(a1)) * scale)));
+        a0 *= mb.z0;
+        a1 *= z1;
+      }
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < np * Ms; k += blockDim.x)
+      ut[size_t(p0) * Ms + k] = float(ldexp(double(static_cast<long long>(sums[k])), -kx));
+    __syncthreads();
+  }
+}
+
 // ---- work-list forms (see the sweeps' in operator.hip): an item runs the
 // block (y, z, w) of its problem's own launch.
 
@@ -1080,6 +1186,41 @@ int run_adjoint_moments(const umbir_geometry& G, const float* r, void* fine, flo
                  G.n_off, G.legs, G.tau, G.base, G.P, G.K, log2_int(G.Q), G.M, tpg, G.gwin, tpb, partial);
   });
   return check_hip(hipGetLastError(), "k_mgather");
+}
+
+// Planes of a trace's moments that an ICD block holds in kIcdMomentLds bytes.
+constexpr size_t kIcdMomentLds = 81920;  // two blocks per CU
+int icd_planes(const umbir_geometry& G, size_t bytes_per_value) {
+  return int(std::min<size_t>(G.mom.R, std::max<size_t>(1, kIcdMomentLds / (bytes_per_value * G.mom.Ms))));
+}
+
+int run_icd_dots_moments(const umbir_geometry& G, const float* e, const IcdGroup& gp, int Sr, int Sc, float* mom,
+                         float* partial, hipStream_t s) {
+  const int planes = icd_planes(G, sizeof(float));
+  const int ych = std::max(1, std::min((gp.size + 1023) / 1024, 512 / std::max(G.traces(), 1)));
+  with_r(G.mom.R, [&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    with_tiles(moment_tiles(G), [&](auto nc) { launch_mcorr<R, decltype(nc)::value>(G, e, mom, s); });
+    UMBIR_LAUNCH("icd_dots", k_icd_mdots<R>, dim3(unsigned(G.traces()), unsigned(ych)), dim3(1024),
+                 size_t(planes) * G.mom.Ms * sizeof(float), s, mom, G.mom.Ms, planes, G.legs, G.n_off, G.tau, G.base,
+                 G.P, G.K, log2_int(G.Q), G.M, gp, Sr, Sc, partial);
+  });
+  return check_hip(hipGetLastError(), "icd moment dots");
+}
+
+int run_icd_update_moments(const umbir_geometry& G, const IcdGroup& gp, int Sr, int Sc, const float* delta, float* mom,
+                           float* e, hipStream_t s) {
+  const int planes = icd_planes(G, sizeof(unsigned long long));
+  with_r(G.mom.R, [&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    UMBIR_LAUNCH("icd_scatter", k_icd_msplat<R>, dim3(unsigned(G.traces())), dim3(1024),
+                 size_t(planes) * G.mom.Ms * sizeof(unsigned long long), s, mom, G.mom.Ms, planes, G.legs, G.n_off,
+                 G.tau, G.base, G.P, G.K, log2_int(G.Q), G.M, gp, Sr, Sc, delta);
+    with_tiles(moment_tiles(G), [&](auto nc) {
+      launch_mconv<R, decltype(nc)::value, UMBIR_STORAGE_F32>(G, mom, e, -1.0f, nullptr, e, s);
+    });
+  });
+  return check_hip(hipGetLastError(), "icd moment update");
 }
 
 void plan_moments(const umbir_geometry& G, int pi, BatchProb& bp, std::vector<int4>* items, size_t* lds) {

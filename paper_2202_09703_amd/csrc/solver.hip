@@ -499,25 +499,11 @@ int enqueue_start(const umbir_geometry& G, const IterBuffers& b, const float* x,
 // the group's block of A^T A, so every group step lowers the cost.  Then
 // e -= A (step on the group).  Per group three kernels: window dot products
 // per trace, the step per member (trace sums in a fixed order), and the
-// residual update per trace (integer LDS accumulation: bitwise reproducible).
+// residual update per trace (integer LDS accumulation: bitwise reproducible);
+// for large groups the dots and the update run as moments (moment.hip).
 // A member's column in trace t is W * I_b(m Q - D Q): with J = floor(D Q) and
 // phi = D Q - J, sample m holds W (phi b[k - 1] + (1 - phi) b[k]), k = m Q - J,
 // nonzero for 1 <= k <= Q L_h.
-struct IcdGroup {
-  int r0, c0;  // first row and column of the class
-  int gr;      // rows in the group
-  int size;    // members
-};
-
-// Member i of a group, rows fastest: neighbouring lanes take members of one
-// column Sr rows apart, whose delays differ by far more than those of
-// neighbouring columns, so their windows meet fewer common samples at once.
-__device__ __forceinline__ void icd_member(const IcdGroup& gp, int Sr, int Sc, int i, int* row, int* col) {
-  const int cc = i / gp.gr;
-  *row = gp.r0 + (i - cc * gp.gr) * Sr;
-  *col = gp.c0 + cc * Sc;
-}
-
 // delay (Q32.32 samples) and weight of voxel (row, col) in trace t
 __device__ __forceinline__ void icd_pair(const Leg* __restrict__ legs, int n_off, const int* __restrict__ base, int P,
                                          int K, const float* __restrict__ tau, int t, int row, int col, int64_t* D,
@@ -1229,6 +1215,15 @@ int umbir_reconstruct_icd(const umbir_geometry* G, const umbir_prior* pr, const 
   const double inv_2s2 = 0.5 / (pr->sigma * pr->sigma);
   const int est = pr->estimate_direct ? 1 : 0;
   const int n_groups = Sr * Sc;
+  // The sweeps as moments from 768 members in the largest group on: the dense
+  // products cost the same for any group, the window dots and updates a
+  // member's window each.  Per group, moments against windows: 79 against 114
+  // us with 1024 members at 256 x 256 voxels, 512 traces of 2048 samples (70
+  // against 66 with 441, 117 against 374 with 4096), 42 against 62 us with 1024
+  // at 128 x 128, 128 traces (39 against 38 with 441), 33 against 38 us with
+  // 1024 at 64 x 64, 8 traces (30 against 25 with 441).  The curvatures stay:
+  // |b| is no polynomial where the pulse changes sign.
+  const bool mom = moments_on(*G) && gmax >= 768;
 
   const size_t lds_dots = (size_t(M) + QLh + 2) * sizeof(float);
   const size_t lds_scatter = size_t(M) * sizeof(unsigned long long) + (size_t(QLh) + 2) * sizeof(float);
@@ -1283,10 +1278,18 @@ int umbir_reconstruct_icd(const umbir_geometry* G, const umbir_prior* pr, const 
     for (int k = 0; k < n_groups; ++k) {
       const IcdGroup gp = icd_group(*G, Sr, Sc, k);
       if (gp.size == 0) continue;
-      dots(false, gp, e);
+      if (mom) {
+        if ((st = run_icd_dots_moments(*G, e, gp, Sr, Sc, static_cast<float*>(fine), part, s))) return st;
+      } else {
+        dots(false, gp, e);
+      }
       UMBIR_LAUNCH("icd_step", k_icd_step<false>, sgrid(gp), sblk, 0, s, part, PK, gp, Sr, Sc, G->nx, G->nz, pc,
                    ms_row, den, x_io, delta);
-      scatter(false, gp, e);
+      if (mom) {
+        if ((st = run_icd_update_moments(*G, gp, Sr, Sc, delta, static_cast<float*>(fine), e, s))) return st;
+      } else {
+        scatter(false, gp, e);
+      }
     }
     if ((st = check_hip(hipGetLastError(), "icd sweep"))) return st;
   }

@@ -130,6 +130,35 @@ def test_uneven_scan_positions_keep_the_fine_grid(dev, kw):
     geom.free()
 
 
+@pytest.mark.parametrize("kw, group", [
+    (dict(nx=56, nz=56, scans=5, rx=3, samples=417, pitch=-2), (2, 2)),             # 784 members, 5 moments
+    (dict(nx=81, nz=58, scans=1, rx=2, samples=230, mhz=10), (3, 2)),               # 783, ragged groups, 6 moments
+    (dict(nx=57, nz=84, scans=3, rx=2, samples=2900, f_c=2), (2, 3)),               # 812, some of 8 planes in LDS
+])
+def test_icd_sweeps_of_large_groups(dev, kw, group):
+    """Grouped ICD's sweeps run as moments from 768 members on; the fine-grid
+    tuning (products = 1) keeps the window dots.  Each step divides by the
+    group's curvature and moves by at most a few noise levels, so the two agree
+    as two FP32 evaluations of the same sums do: the bar of the parity tests of
+    grouped ICD, 1e-5."""
+    c = card(**kw)
+    geom = umbir.build_geometry(c)
+    x_true = random_vector((c.grid.nz, c.grid.nx), seed=31)
+    y = oo.forward(c, x_true)
+    sigma = 0.05 * float(np.sqrt(np.mean(y ** 2)))
+    y = torch.tensor(y + sigma * random_vector(geom.trace_shape, seed=32), dtype=torch.float32, device=dev)
+    x, g, cost = umbir.reconstruct_icd(geom, c.prior, sigma, y, 2, group=group)
+    again = umbir.reconstruct_icd(geom, c.prior, sigma, y, 2, group=group)
+    assert all(torch.equal(a, b) for a, b in zip((x, g, cost), again))
+    geom.set_tuning(products=1)
+    xw, gw, cw = umbir.reconstruct_icd(geom, c.prior, sigma, y, 2, group=group)
+    assert not torch.equal(x, xw)  # the moments did run
+    errs = rel(x.cpu(), xw.cpu()), rel(g.cpu(), gw.cpu()), rel(cost.cpu(), cw.cpu())
+    print("image, direct weights, cost rel L2 %.2e %.2e %.2e" % errs)
+    assert max(errs) <= 1e-5
+    geom.free()
+
+
 @pytest.mark.parametrize("storage", [1, 2])
 def test_forward_with_16bit_traces(dev, storage):
     """The forward alone runs as moments with 16-bit storage too: one rounding
