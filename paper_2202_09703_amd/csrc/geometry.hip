@@ -586,7 +586,7 @@ void umbir_geometry_free(umbir_geometry* G) {
   (void)hipGetDevice(&cur);
   if (G->device >= 0) (void)hipSetDevice(G->device);
   void* ptrs[] = {G->legs, G->legs_t, G->tau, G->base, G->bank, G->h, G->habs, G->dbasis, G->dnorm, G->gmask,
-                  G->gunit, G->gunit_t, G->gwin, G->mom_start, G->mom_rec4, G->mom_rec_hi, G->mom_taps};
+                  G->gunit, G->gunit_t, G->gwin, G->mom_start, G->mom_rec4, G->mom_rec_hi, G->mom_taps, G->mom_span};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (cur >= 0) (void)hipSetDevice(cur);
@@ -830,14 +830,15 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
                  G->K, G->nx, G->voxels(), qs, MQ, NG - 1, G->mask_blocks, G->gmask);
   }
   // the moment form's tables, where the geometry takes it
-  G->mom = moment_shape(moment_input(pb, dv));
+  if (NG == dv.n_gamma) G->mom = moment_shape(moment_input(pb, dv));
   int max_bin = 0;
   if (G->mom.R) {
     const MomentShape& ms = G->mom;
-    if ((st = alloc((void**)&G->mom_start, size_t(G->K) * (G->M + 1) * sizeof(int))) ||
+    if ((st = alloc((void**)&G->mom_start, size_t(G->K) * (size_t(ms.NG) * G->M + 1) * sizeof(int))) ||
         (st = alloc((void**)&G->mom_rec4, ms.records * sizeof(float4))) ||
         (st = alloc((void**)&G->mom_rec_hi, ms.records * (ms.R - 3) * sizeof(float))) ||
-        (st = alloc((void**)&G->mom_taps, size_t(ms.R) * 3 * ms.LT * sizeof(uint4))) ||
+        (st = alloc((void**)&G->mom_taps, size_t(ms.NG) * ms.R * 3 * ms.LT * sizeof(uint4))) ||
+        (ms.NG > 1 && (st = alloc((void**)&G->mom_span, size_t(ms.NG) * sizeof(int2)))) ||
         (st = build_moments(G, &max_bin, s)))
       return bail(st);
   }
@@ -849,12 +850,14 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
   if (!st) st = st2;
   if (!st && !moment_plan_fits(max_bin)) {  // the fine grid stays
     G->bytes -= G->mom.table_bytes;
-    void* tables[] = {G->mom_start, G->mom_rec4, G->mom_rec_hi, G->mom_taps};
-    for (void* p : tables) (void)hipFree(p);
+    void* tables[] = {G->mom_start, G->mom_rec4, G->mom_rec_hi, G->mom_taps, G->mom_span};
+    for (void* p : tables)
+      if (p) (void)hipFree(p);
     G->mom_start = nullptr;
     G->mom_rec4 = nullptr;
     G->mom_rec_hi = nullptr;
     G->mom_taps = nullptr;
+    G->mom_span = nullptr;
     G->mom = MomentShape{};
   }
   if (st) {

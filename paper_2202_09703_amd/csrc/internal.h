@@ -176,6 +176,7 @@ struct Carve {
 // (or v) and of the whole workspace it needs; records and table bytes.
 struct MomentShape {
   int R = 0, Ms = 0, LT = 0;
+  int NG = 1;  // attenuation templates: each has its own u, [template][trace][R][Ms]
   int pitch = 0, Lq = 0, NR = 0, rel0 = 0, ls = 0, reversed = 0;
   size_t u_bytes = 0, work_bytes = 0, records = 0, table_bytes = 0;
 };
@@ -275,10 +276,11 @@ struct umbir_geometry {
   // the moment form (mom.R > 0): the splat's records sorted by sample per
   // receiver, where each sample's begin, and the dense kernels' table
   umbir::MomentShape mom;
-  int* mom_start = nullptr;         // [K][M + 1]
+  int* mom_start = nullptr;         // [K][NG M + 1]
   float4* mom_rec4 = nullptr;       // [records] coefficients 0 .. 3
   float* mom_rec_hi = nullptr;      // [records][R - 3] the others, then the byte offset in the image by phase
-  uint4* mom_taps = nullptr;        // [R][3][LT]
+  uint4* mom_taps = nullptr;        // [NG][R][3][LT]
+  int2* mom_span = nullptr;         // [NG] first sample with a record and the one past the last (attenuation)
   size_t bytes = 0;
 
   int traces() const { return P * K; }
@@ -366,9 +368,11 @@ __device__ __forceinline__ void fold_cost(const CostFold& f, double* sh) {
 // in that type by contract, and the image of an adjoint or a reconstruction
 // (FP32) shows those roundings.  A forward alone may (forward_moments_on): its
 // result is rounded to the 16-bit type anyway, and comes out nearer the exact
-// one.
+// one.  A forward and an adjoint alone may with attenuation too
+// (adjoint_moments_on).
 bool moments_on(const umbir_geometry& G);
 bool forward_moments_on(const umbir_geometry& G);
+bool adjoint_moments_on(const umbir_geometry& G);
 
 // The moment form's counterparts of run_forward and run_adjoint_partial.
 // in_place: the workspace holds x by phase already (run_phase_image, or the

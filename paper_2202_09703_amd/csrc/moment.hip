@@ -63,6 +63,24 @@ __device__ __forceinline__ PairLegs pair_legs(const Leg* __restrict__ legs, int 
   return {uint64_t(a.delay + b.delay), a.apod * b.apod};
 }
 
+// Its attenuation template.
+__device__ __forceinline__ int pair_template(const double* __restrict__ gunit, int n_off, int bt, int br, int row,
+                                             int rel, int glast) {
+  if (!gunit) return 0;
+  const int half = n_off / 2;
+  const double* u = gunit + size_t(row) * n_off;
+  return gamma_bin(u[leg_slot(abs(bt + 2 * rel), half)] + u[leg_slot(abs(br + 2 * rel), half)], glast);
+}
+
+// The bin of a pair: its sample, after the bins of the templates before its
+// own; NG M past the record.
+__device__ __forceinline__ int plan_bin(const PairLegs& p, const double* __restrict__ gunit, const MomentShape& ms,
+                                        int n_off, int bt, int br, int row, int rel, int M) {
+  const uint64_t n = p.D >> 32;
+  if (n >= uint64_t(M)) return ms.NG * M;
+  return pair_template(gunit, n_off, bt, br, row, rel, ms.NG - 1) * M + int(n);
+}
+
 // Lattice bases of scan lane 0 (the leftmost position) for receiver j.
 __device__ __forceinline__ void plan_bases(const int* __restrict__ base, const MomentShape& ms, int P, int K, int j,
                                            int* bt, int* br) {
@@ -74,14 +92,14 @@ __device__ __forceinline__ void plan_bases(const int* __restrict__ base, const M
 // Relative columns per plan block: one histogram of samples per (j, chunk).
 constexpr int kPlanChunk = 64;
 
-// counts[j][chunk][n]: records of receiver j and the chunk's relative columns
-// in sample n.
-__global__ __launch_bounds__(256) void k_plan_count(const Leg* __restrict__ legs, const int* __restrict__ base,
-                                                    MomentShape ms, int P, int K, int nz, int n_off, int M,
-                                                    int* __restrict__ counts) {
+// counts[j][chunk][b]: records of receiver j and the chunk's relative columns
+// in bin b (of NB = NG M).
+__global__ __launch_bounds__(256) void k_plan_count(const Leg* __restrict__ legs, const double* __restrict__ gunit,
+                                                    const int* __restrict__ base, MomentShape ms, int P, int K, int nz,
+                                                    int n_off, int M, int* __restrict__ counts) {
   extern __shared__ int hist[];
-  const int j = blockIdx.x, ch = blockIdx.y;
-  for (int i = threadIdx.x; i < M; i += blockDim.x) hist[i] = 0;
+  const int j = blockIdx.x, ch = blockIdx.y, NB = ms.NG * M;
+  for (int i = threadIdx.x; i < NB; i += blockDim.x) hist[i] = 0;
   __syncthreads();
   int bt, br;
   plan_bases(base, ms, P, K, j, &bt, &br);
@@ -90,15 +108,15 @@ __global__ __launch_bounds__(256) void k_plan_count(const Leg* __restrict__ legs
     const int row = i / kPlanChunk, rc = i - row * kPlanChunk;
     if (rc >= rn) continue;
     const PairLegs p = pair_legs(legs, n_off, bt, br, row, ms.rel0 + r0 + rc);
-    const uint64_t n = p.D >> 32;
-    if (n < uint64_t(M)) atomicAdd(&hist[int(n)], 1);
+    const int b = plan_bin(p, gunit, ms, n_off, bt, br, row, ms.rel0 + r0 + rc, M);
+    if (b < NB) atomicAdd(&hist[b], 1);
   }
   __syncthreads();
-  int* out = counts + (size_t(j) * gridDim.y + ch) * M;
-  for (int i = threadIdx.x; i < M; i += blockDim.x) out[i] = hist[i];
+  int* out = counts + (size_t(j) * gridDim.y + ch) * NB;
+  for (int i = threadIdx.x; i < NB; i += blockDim.x) out[i] = hist[i];
 }
 
-// Per receiver: start[j][n] (the first record of sample n, start[j][M] the
+// Per receiver: start[j][n] (the first record of bin n of M, start[j][M] the
 // end) and, in place of each count, the first record of (chunk, n).  Records
 // of receiver j begin at j * cap.  max_bin receives the largest bin.
 __global__ __launch_bounds__(1024) void k_plan_scan(int M, int chunks, int cap, int* __restrict__ counts,
@@ -137,13 +155,14 @@ __global__ __launch_bounds__(1024) void k_plan_scan(int M, int chunks, int cap, 
 }
 
 // Keys row * NR + (rel - rel0) of every record into its bin, in any order.
-__global__ __launch_bounds__(256) void k_plan_fill(const Leg* __restrict__ legs, const int* __restrict__ base,
-                                                   MomentShape ms, int P, int K, int nz, int n_off, int M,
-                                                   const int* __restrict__ first, unsigned* __restrict__ keys) {
+__global__ __launch_bounds__(256) void k_plan_fill(const Leg* __restrict__ legs, const double* __restrict__ gunit,
+                                                   const int* __restrict__ base, MomentShape ms, int P, int K, int nz,
+                                                   int n_off, int M, const int* __restrict__ first,
+                                                   unsigned* __restrict__ keys) {
   extern __shared__ int cursor[];
-  const int j = blockIdx.x, ch = blockIdx.y;
-  const int* f = first + (size_t(j) * gridDim.y + ch) * M;
-  for (int i = threadIdx.x; i < M; i += blockDim.x) cursor[i] = f[i];
+  const int j = blockIdx.x, ch = blockIdx.y, NB = ms.NG * M;
+  const int* f = first + (size_t(j) * gridDim.y + ch) * NB;
+  for (int i = threadIdx.x; i < NB; i += blockDim.x) cursor[i] = f[i];
   __syncthreads();
   int bt, br;
   plan_bases(base, ms, P, K, j, &bt, &br);
@@ -152,8 +171,8 @@ __global__ __launch_bounds__(256) void k_plan_fill(const Leg* __restrict__ legs,
     const int row = i / kPlanChunk, rc = i - row * kPlanChunk;
     if (rc >= rn) continue;
     const PairLegs p = pair_legs(legs, n_off, bt, br, row, ms.rel0 + r0 + rc);
-    const uint64_t n = p.D >> 32;
-    if (n < uint64_t(M)) keys[atomicAdd(&cursor[int(n)], 1)] = unsigned(row) * unsigned(ms.NR) + unsigned(r0 + rc);
+    const int b = plan_bin(p, gunit, ms, n_off, bt, br, row, ms.rel0 + r0 + rc, M);
+    if (b < NB) keys[atomicAdd(&cursor[b], 1)] = unsigned(row) * unsigned(ms.NR) + unsigned(r0 + rc);
   }
 }
 
@@ -162,11 +181,39 @@ __global__ __launch_bounds__(256) void k_plan_fill(const Leg* __restrict__ legs,
 // grid (the host reads max_bin after the build).
 constexpr int kMaxBin = 8192;
 
+// span[g]: the first sample with a record of template g in any receiver, and
+// the one past the last ({0, 0}: none).  One block per template.
+__global__ __launch_bounds__(256) void k_plan_span(const int* __restrict__ start, int K, int M, int NB,
+                                                   int2* __restrict__ span) {
+  __shared__ int lo, hi;
+  const int g = blockIdx.x;
+  if (threadIdx.x == 0) {
+    lo = M;
+    hi = 0;
+  }
+  __syncthreads();
+  for (int n = threadIdx.x; n < M; n += blockDim.x) {
+    bool any = false;
+    for (int j = 0; j < K; ++j) {
+      const int* s = start + size_t(j) * (NB + 1) + g * M + n;
+      any = any || s[1] > s[0];
+    }
+    if (any) {
+      atomicMin(&lo, n);
+      atomicMax(&hi, n + 1);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) span[g] = hi > 0 ? make_int2(lo, hi) : make_int2(0, 0);
+}
+
 // One wave per (j, n): the bin's keys put in ascending order by counting the
 // smaller ones, and the records written in that order: coefficients
 // tau a_tx a_rx ((1 - phi) z_t^p + phi z_{t+1}^p) in double, rounded once, and
 // the byte offset of the voxel in the phase-major image (lane i of the splat
-// adds its scan position) in the word after them.
+// adds its scan position) in the word after them.  With attenuation (R = 8) the
+// last two coefficients are the weights the pair puts on the table's first and
+// last point (see k_moment_fit).
 template <int R>
 __global__ __launch_bounds__(256) void k_plan_emit(const Leg* __restrict__ legs, const int* __restrict__ base,
                                                    const float* __restrict__ tau, MomentShape ms, int P, int K,
@@ -208,6 +255,11 @@ __global__ __launch_bounds__(256) void k_plan_emit(const Leg* __restrict__ legs,
       p0 *= z0;
       p1 *= z1;
     }
+    if (R == 8 && ms.NG > 1) {
+      const int ti = int(frac >> (32 - qs));
+      a[R - 2] = ti == (1 << qs) - 1 ? float(w * phi) : 0.0f;
+      a[R - 1] = ti == 0 ? float(w * (1.0 - phi)) : 0.0f;
+    }
     rec4[at] = make_float4(a[0], a[1], a[2], a[3]);
 #pragma unroll
     for (int q = 4; q < R; ++q) rec_hi[size_t(at) * (R - 3) + (q - 4)] = a[q];
@@ -238,6 +290,39 @@ __global__ __launch_bounds__(256) void k_moment_fit(int R, int Q, int Lh, double
   for (int p = 0; p < 8; ++p) {
     for (int off = 32; off > 0; off >>= 1) acc[p] += __shfl_xor(acc[p], off, 64);
     if (lane == 0 && p < R) g[p * Lh + k] = float(acc[p]);
+  }
+}
+
+// The same for the attenuated templates: six coefficients per template and
+// window cell from its row of the bank, and a seventh and eighth function.  The
+// rows are forced to zero at their ends, where an attenuated response is not:
+// the fits of the first and the last cell leave that point out (fit: the three
+// matrices without none, the last and the first of the Q + 1 points), and the
+// weight a pair puts on it takes the fit's value there away again.
+__global__ __launch_bounds__(256) void k_template_fit(int Q, int Lh, const float* __restrict__ bank,
+                                                      const double* __restrict__ fit, float* __restrict__ g_all) {
+  const int k = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (k >= Lh) return;
+  const float* b = bank + size_t(blockIdx.y) * (Q * Lh + 2);
+  float* g = g_all + size_t(blockIdx.y) * 8 * Lh;
+  const double* f = fit + (k == 0 ? 1 : k == Lh - 1 ? 2 : 0) * 6 * (Q + 1);
+  double acc[6] = {};
+  for (int t = lane; t <= Q; t += 64) {
+    const double v = double(b[(k + 1) * Q - t]);
+#pragma unroll
+    for (int p = 0; p < 6; ++p) acc[p] += f[p * (Q + 1) + t] * v;
+  }
+  double at_one = 0.0, at_minus = 0.0;  // the fit at t = Q and t = 0
+#pragma unroll
+  for (int p = 0; p < 6; ++p) {
+    for (int off = 32; off > 0; off >>= 1) acc[p] += __shfl_xor(acc[p], off, 64);
+    at_one += acc[p];
+    at_minus += p & 1 ? -acc[p] : acc[p];
+    if (lane == 0) g[p * Lh + k] = float(acc[p]);
+  }
+  if (lane == 0) {
+    g[6 * Lh + k] = k == 0 ? float(-at_one) : 0.0f;
+    g[7 * Lh + k] = k == Lh - 1 ? float(-at_minus) : 0.0f;
   }
 }
 
@@ -336,8 +421,8 @@ __device__ __forceinline__ void msplat_steps(const float* recs, int lane, unsign
 template <int R>
 __device__ __forceinline__ void msplat_body(int bx, int by, int bz, const float* __restrict__ xp, int xp_bytes,
                                             const int* __restrict__ start, const float4* __restrict__ rec4,
-                                            const float* __restrict__ rec_hi, int P, int K, int M, int Ms, int ls,
-                                            int reversed, float* __restrict__ u) {
+                                            const float* __restrict__ rec_hi, int P, int K, int M, int sstride, int Ms,
+                                            int ls, int reversed, float* __restrict__ u) {
   extern __shared__ __align__(16) float sm[];
   constexpr int W = msplat_rec_words<R>();
   constexpr int NB = kMsBins / kMsWaves;
@@ -350,7 +435,7 @@ __device__ __forceinline__ void msplat_body(int bx, int by, int bz, const float*
   const int j = bx, n0 = by * kMsBins, nw = n0 + NB * wave;
   const unsigned xl4 = unsigned(64 * bz + (lane & (S - 1))) * 4u;  // this lane's scan position
   // the records of the wave's samples: [at[b], at[b + 1])
-  const int* sj = start + size_t(j) * (M + 1);
+  const int* sj = start + size_t(j) * sstride;
   int at[NB + 1];
 #pragma unroll
   for (int b = 0; b <= NB; ++b) at[b] = sj[min(nw + b, M)];
@@ -436,7 +521,29 @@ __global__ __launch_bounds__(64 * kMsWaves) void k_msplat(const float* __restric
     extern __shared__ __align__(16) float sm[];
     fold_cost(fold, reinterpret_cast<double*>(sm));
   }
-  msplat_body<R>(blockIdx.x, blockIdx.y, blockIdx.z, xp, xp_bytes, start, rec4, rec_hi, P, K, M, Ms, ls, reversed, u);
+  msplat_body<R>(blockIdx.x, blockIdx.y, blockIdx.z, xp, xp_bytes, start, rec4, rec_hi, P, K, M, M + 1, Ms, ls,
+                 reversed, u);
+}
+
+// Every template's u (grid z: scan chunks of template 0, of template 1, ...),
+// of the samples its span reaches.  A record belongs to one template, so the
+// bins are (template, sample) and the records are no more than without
+// attenuation.  The fine-grid form fills one dense grid per template: 512
+// traces of 65536 positions in 16 templates are 2.1 GB, and writing and reading
+// them took 1158 and 1328 us at 256 x 256; u (0.5 GB at most, the spans' share
+// of it) takes 137 and 275 us.
+__global__ __launch_bounds__(64 * kMsWaves) void k_msplat_att(const float* __restrict__ xp, int xp_bytes,
+                                                              const int* __restrict__ start,
+                                                              const float4* __restrict__ rec4,
+                                                              const float* __restrict__ rec_hi, int P, int K, int M,
+                                                              MomentShape ms, const int2* __restrict__ span,
+                                                              float* __restrict__ u) {
+  const int chunks = (P + 63) / 64, gb = blockIdx.z / chunks;
+  const int2 sp = span[gb];
+  const int n0 = blockIdx.y * kMsBins;
+  if (n0 >= sp.y || n0 + kMsBins <= sp.x) return;  // uniform
+  msplat_body<8>(blockIdx.x, blockIdx.y, blockIdx.z - gb * chunks, xp, xp_bytes, start + size_t(gb) * M, rec4, rec_hi,
+                 P, K, M, ms.NG * M + 1, ms.Ms, ms.ls, ms.reversed, u + size_t(gb) * P * K * 8 * ms.Ms);
 }
 
 // ---- C and C^T: banded Toeplitz products on the bf16 matrix cores, FP32
@@ -455,19 +562,24 @@ __device__ __forceinline__ void stage_table(uint4* tab, const uint4* __restrict_
 // C: a block computes 32 traces x 32 NTC samples; its eight waves take the
 // (16 samples of u, moment) items of the window in turn, each item split into
 // pieces once and multiplied into every tile it reaches; the waves' sums are
-// added in LDS, two tiles at a time, in wave order.
-template <int R, int NTC, int ST>
+// added in LDS, two tiles at a time, in wave order.  ATT: the templates one
+// after the other, each over the samples its span reaches, into the same sums.
+struct MomentTemplates {
+  const int2* span;  // [n]
+  int n;
+};
+template <int R, int NTC, int ST, bool ATT = false>
 __device__ __forceinline__ void mconv_body(int bx, int by, const float* __restrict__ u, int Ms,
                                            const uint4* __restrict__ F, int LT, int M, int Lh, int PK,
                                            const typename Store<ST>::T* base, float sign,
                                            const float* __restrict__ g, const float* __restrict__ dbasis,
-                                           typename Store<ST>::T* out) {
+                                           typename Store<ST>::T* out, MomentTemplates mt = {}) {
   extern __shared__ __align__(16) float sm[];
   uint4* tab = reinterpret_cast<uint4*>(sm);
   const int tr0 = bx * 32, m0 = by * 32 * NTC;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int li = lane & 31, lk = lane >> 5;
-  stage_table(tab, F, R * 3 * LT);
+  if constexpr (!ATT) stage_table(tab, F, R * 3 * LT);
   // the epilogue's inputs, fetched while the window multiplies: thread
   // (wave, lane) finishes registers wave and wave + 8 of every tile
   constexpr int E = 2 * NTC;
@@ -491,9 +603,9 @@ __device__ __forceinline__ void mconv_body(int bx, int by, const float* __restri
   // rows n of the window [m0 - Lh, m0 + 32 NTC - 2], in steps of 16 from a
   // multiple of 8 (a group of 8 lies wholly before sample 0 or not at all)
   const int ns = (m0 - Lh) & ~7;
-  const int s_lo = ns < 0 ? (-ns) >> 4 : 0;
-  const int s_hi = min((m0 + 32 * NTC - 1 - ns + 15) >> 4, (Ms - ns + 15) >> 4);
-  const int items = (s_hi - s_lo) * R;
+  int s_lo = ns < 0 ? (-ns) >> 4 : 0;
+  int s_hi = min((m0 + 32 * NTC - 1 - ns + 15) >> 4, (Ms - ns + 15) >> 4);
+  int n_lo = 0, n_hi = Ms;  // rows that hold u (ATT: the groups of 16 written)
   auto fetch = [&](int q, float4& x, float4& y) {
     const int s = s_lo + q / R, p = q - (q / R) * R;
     const int n = ns + 16 * s + 8 * lk;
@@ -503,8 +615,8 @@ __device__ __forceinline__ void mconv_body(int bx, int by, const float* __restri
   };
   auto multiply = [&](int q, float4 x, float4 y) {
     const int s = s_lo + q / R, p = q - (q / R) * R;
-    const int n0 = ns + 16 * s;
-    if (n0 + 8 * lk < 0) x = y = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const int n0 = ns + 16 * s, n = n0 + 8 * lk;
+    if (n < n_lo || (ATT && n >= n_hi)) x = y = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     const Pieces8 a = split8_bf16x3(x, y);
     const uint4* tp = tab + p * 3 * LT + 1;
 #pragma unroll
@@ -516,16 +628,38 @@ __device__ __forceinline__ void mconv_body(int bx, int by, const float* __restri
       acc[j] = mfma_bf16x3(a.p, b, acc[j]);
     }
   };
-  __syncthreads();
-  float4 x0, y0, x1, y1;
-  if (wave < items) fetch(wave, x0, y0);
-  for (int q = wave; q < items; q += 2 * kMcWaves) {
-    if (q + kMcWaves < items) fetch(q + kMcWaves, x1, y1);
-    multiply(q, x0, y0);
-    if (q + kMcWaves < items) {
-      if (q + 2 * kMcWaves < items) fetch(q + 2 * kMcWaves, x0, y0);
-      multiply(q + kMcWaves, x1, y1);
+  auto window = [&]() {
+    const int items = (s_hi - s_lo) * R;
+    float4 x0, y0, x1, y1;
+    if (wave < items) fetch(wave, x0, y0);
+    for (int q = wave; q < items; q += 2 * kMcWaves) {
+      if (q + kMcWaves < items) fetch(q + kMcWaves, x1, y1);
+      multiply(q, x0, y0);
+      if (q + kMcWaves < items) {
+        if (q + 2 * kMcWaves < items) fetch(q + 2 * kMcWaves, x0, y0);
+        multiply(q + kMcWaves, x1, y1);
+      }
     }
+  };
+  if constexpr (ATT) {
+    const int w_lo = s_lo, w_hi = s_hi;
+    for (int gb = 0; gb < mt.n; ++gb) {
+      const int2 sp = mt.span[gb];
+      n_lo = sp.x & ~15;
+      n_hi = (sp.y + 15) & ~15;
+      s_lo = max(w_lo, (n_lo - ns) >> 4);
+      s_hi = min(w_hi, (n_hi - ns + 15) >> 4);
+      if (sp.y > 0 && s_hi > s_lo) {  // uniform
+        __syncthreads();  // the table before is read
+        stage_table(tab, F + size_t(gb) * R * 3 * LT, R * 3 * LT);
+        __syncthreads();
+        window();
+      }
+      ut += size_t(PK) * R * Ms;
+    }
+  } else {
+    __syncthreads();
+    window();
   }
   // red[tile of the pair][wave][register][lane]
   constexpr int NP = NTC < 2 ? 1 : 2;
@@ -585,10 +719,12 @@ __device__ __forceinline__ void load8(const float* row, int m, int M, bool insid
 // sample tiles and 8 / NT waves on each, which share the window's steps and
 // add their sums in LDS, halving.  The eight samples of a lane go in reversed,
 // so that C's table serves.
-template <int R, int NT>
+// PAIR: v of one template for the gather of pairs, [..][n][R] in place of
+// [..][R][n] (vstride: floats between traces).
+template <int R, int NT, bool PAIR = false>
 __device__ __forceinline__ void mcorr_body(int bx, int by, const float* __restrict__ r,
                                            const uint4* __restrict__ F, int LT, int M, int Lh, int PK, int Ms,
-                                           float* __restrict__ v) {
+                                           float* __restrict__ v, size_t vstride = 0) {
   extern __shared__ __align__(16) float sm[];
   constexpr int KS = kMcWaves / NT;
   uint4* tab = reinterpret_cast<uint4*>(sm);
@@ -651,6 +787,17 @@ __device__ __forceinline__ void mcorr_body(int bx, int by, const float* __restri
     }
   }
   if (ks != 0 || n0 >= Ms) return;
+  if constexpr (PAIR) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int tr = tr0 + 8 * (i >> 2) + 4 * lk + (i & 3);
+      if (tr >= PK) continue;
+      float4* o = reinterpret_cast<float4*>(v + tr * vstride + size_t(n0 + li) * R);
+#pragma unroll
+      for (int p = 0; p < R; p += 4) o[p / 4] = make_float4(acc[p][i], acc[p + 1][i], acc[p + 2][i], acc[p + 3][i]);
+    }
+    return;
+  }
 #pragma unroll
   for (int p = 0; p < R; ++p)
 #pragma unroll
@@ -669,6 +816,20 @@ __global__ __launch_bounds__(64 * kMcWaves) void k_mcorr(const float* __restrict
                                                          int LT, int M, int Lh, int PK, int Ms,
                                                          float* __restrict__ v) {
   mcorr_body<R, NT>(blockIdx.x, blockIdx.y, r, F, LT, M, Lh, PK, Ms, v);
+}
+
+// Every template's v (grid z), over the samples its span reaches: 182 us for 512
+// traces of 2048 samples in 16 templates (960 us to the fine grids).
+template <int NT>
+__global__ __launch_bounds__(64 * kMcWaves) void k_mcorr_att(const float* __restrict__ r,
+                                                             const uint4* __restrict__ F, int LT, int M, int Lh,
+                                                             int PK, int Ms, int NG, const int2* __restrict__ span,
+                                                             float* __restrict__ v) {
+  const int gb = blockIdx.z, n0 = int(blockIdx.y) * 32 * NT;
+  const int2 sp = span[gb];
+  if (n0 >= sp.y || n0 + 32 * NT <= sp.x) return;  // uniform
+  mcorr_body<8, NT, true>(blockIdx.x, blockIdx.y, r, F + size_t(gb) * 24 * LT, LT, M, Lh, PK, Ms,
+                          v + size_t(gb) * Ms * 8, size_t(NG) * Ms * 8);
 }
 
 // ---- S^T
@@ -883,6 +1044,135 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(R < 8 ? 4 :
                   tiles_per_block, partial);
 }
 
+// The gather with attenuation: v is [trace][template][n][8], so that a pair's
+// eight values are two 16-byte loads of one 32-byte sector, from L2.  Threads
+// take voxels in row-major order, VPT a thread; the legs of trace t + 2 and the
+// values of trace t + 1 are in flight while trace t accumulates.  One partial
+// image per trace group, traces in order.  Bound by the load unit, a line per
+// lane: 158 us at 256 x 256, 512 traces (2 x 139 us from the fine grids, whose
+// batches of traces had to fit an L2).
+constexpr int kMgAttVpt = 2;
+__global__ __launch_bounds__(256) void k_mgather_att(const float* __restrict__ v, MomentShape ms, int nx, int nz,
+                                                     int n_off, const Leg* __restrict__ legs,
+                                                     const double* __restrict__ gunit, const float* __restrict__ tau,
+                                                     const int* __restrict__ base, int P, int K, int qs, int M,
+                                                     int tpg, int vox_per_block, float* __restrict__ partial) {
+  constexpr int V = kMgAttVpt;
+  const int N = nx * nz, PK = P * K;
+  const int v_begin = blockIdx.y * vox_per_block, v_end = min(N, v_begin + vox_per_block);
+  const int t0 = blockIdx.x * tpg, t1 = min(t0 + tpg, PK);
+  const int half = n_off / 2;
+  const float h = 2.0f / float(1 << qs);
+  const __amdgpu_buffer_rsrc_t leg_rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<Leg*>(legs), 0, nz * n_off * int(sizeof(Leg)), kBufferWord3);
+  const __amdgpu_buffer_rsrc_t gu_rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(gunit), 0, nz * n_off * 8, kBufferWord3);
+  const int v_floats = ms.NG * ms.Ms * 8;  // of one trace
+  struct Legs { int64_t d[V]; float p[V]; double u[V]; };
+  struct Pairs { int at[V]; unsigned fr[V]; float w[V]; };
+  struct Values { float4 lo[V], hi[V]; };
+  for (int vc = v_begin; vc < v_end; vc += 256 * V) {
+    int col2[V], rowoff[V];
+    float acc[V];
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+      const int vox = min(vc + q * 256 + int(threadIdx.x), v_end - 1);  // past the end: a voxel of the block, unused
+      const int row = vox / nx;
+      col2[q] = 2 * (vox - row * nx);
+      rowoff[q] = row * n_off;
+      acc[q] = 0.0f;
+    }
+    auto load_leg = [&](int bt, Legs& L) {
+#pragma unroll
+      for (int q = 0; q < V; ++q) {
+        const int o = (rowoff[q] + leg_slot(abs(bt + col2[q]), half)) * int(sizeof(Leg));
+        const auto a = __builtin_amdgcn_raw_buffer_load_b64(leg_rs, o, 0, 0);
+        L.p[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(leg_rs, o + 8, 0, 0));
+        L.u[q] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(gu_rs, o >> 1, 0, 0));
+        L.d[q] = int64_t((uint64_t(a[1]) << 32) | a[0]);
+      }
+    };
+    Legs TX;
+    int scan = -1;
+    auto pairs = [&](const Legs& L, int t, Pairs& T) {
+      t = min(t, t1 - 1);
+      if (t / K != scan) {  // uniform
+        scan = t / K;
+        load_leg(base[scan], TX);
+      }
+#pragma unroll
+      for (int q = 0; q < V; ++q) {
+        const uint64_t D = uint64_t(TX.d[q] + L.d[q]);
+        const unsigned n = unsigned(D >> 32);
+        const int gb = gamma_bin(TX.u[q] + L.u[q], ms.NG - 1);
+        T.at[q] = n < unsigned(M) ? (gb * ms.Ms + int(n)) * 32 : 0x7fffff00;  // past the record: reads zero
+        T.fr[q] = unsigned(D);
+        T.w[q] = TX.p[q] * L.p[q];
+      }
+    };
+    auto values = [&](const Pairs& T, int t, Values& S) {
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<float*>(v + size_t(min(t, t1 - 1)) * v_floats), 0, v_floats * 4, kBufferWord3);
+#pragma unroll
+      for (int q = 0; q < V; ++q) {
+        const auto a = __builtin_amdgcn_raw_buffer_load_b128(rs, T.at[q], 0, 0);
+        const auto b = __builtin_amdgcn_raw_buffer_load_b128(rs, T.at[q] + 16, 0, 0);
+        S.lo[q] = __builtin_bit_cast(float4, a);
+        S.hi[q] = __builtin_bit_cast(float4, b);
+      }
+    };
+    auto add = [&](const Pairs& T, const Values& S) {
+#pragma unroll
+      for (int q = 0; q < V; ++q) {
+        const unsigned fr = T.fr[q], ti = fr >> (32 - qs);
+        const float z0 = fmaf(float(ti), h, -1.0f), z1 = z0 + h;
+        const float phi = float(fr << qs) * 2.3283064365386963e-10f;
+        const float c[6] = {S.lo[q].x, S.lo[q].y, S.lo[q].z, S.lo[q].w, S.hi[q].x, S.hi[q].y};
+        float f0 = c[5], f1 = c[5];
+#pragma unroll
+        for (int p = 4; p >= 0; --p) {
+          f0 = fmaf(f0, z0, c[p]);
+          f1 = fmaf(f1, z1, c[p]);
+        }
+        // the forced zeros at the ends of the bank's rows
+        if (ti == 0u) f0 += S.hi[q].w;
+        if (ti == (1u << qs) - 1u) f1 += S.hi[q].z;
+        acc[q] = fmaf(T.w[q], fmaf(phi, f1 - f0, f0), acc[q]);
+      }
+    };
+    if (t0 < t1) {
+      Legs L;
+      Pairs T0, T1;
+      Values S0, S1;
+      load_leg(base[P + t0], L);
+      pairs(L, t0, T0);
+      load_leg(base[P + min(t0 + 1, t1 - 1)], L);
+      values(T0, t0, S0);
+      for (int t = t0; t < t1; t += 2) {
+        // trace t: T0 / S0 (in flight); the legs of t + 1 in L (in flight)
+        pairs(L, t + 1, T1);
+        load_leg(base[P + min(t + 2, t1 - 1)], L);
+        values(T1, t + 1, S1);
+        __builtin_amdgcn_sched_barrier(0);
+        add(T0, S0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 1 >= t1) break;
+        pairs(L, t + 2, T0);
+        load_leg(base[P + min(t + 3, t1 - 1)], L);
+        values(T0, t + 2, S0);
+        __builtin_amdgcn_sched_barrier(0);
+        add(T1, S1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < V; ++q) {
+      const int vox = vc + q * 256 + int(threadIdx.x);
+      if (vox < v_end) partial[size_t(blockIdx.x) * N + vox] = acc[q] * tau[vox / nx];
+    }
+  }
+}
+
 // ---- grouped ICD: one group's columns of A against e, and their sum
 
 // delay (Q32.32 samples), weight and the two table points of member i of a
@@ -1017,7 +1307,7 @@ __global__ __launch_bounds__(64 * kMsWaves) void k_msplat_list(const BatchProb* 
     const float* xp = p.P == 1 ? p.x[which] : p.xt;
     with_r_device(p.mom.R, [&](auto rc) {
       msplat_body<decltype(rc)::value>(w.y, w.z, w.w, xp, p.nz * p.mom.pitch * p.mom.Lq * 4, p.mom_start, p.mom_rec4,
-                                       p.mom_rec_hi, p.P, p.K, p.M, p.mom.Ms, p.mom.ls, p.mom.reversed, p.fine);
+                                       p.mom_rec_hi, p.P, p.K, p.M, p.M + 1, p.mom.Ms, p.mom.ls, p.mom.reversed, p.fine);
     });
     __syncthreads();
   }
@@ -1071,6 +1361,17 @@ __global__ __launch_bounds__(512) void k_mgather_list(const BatchProb* __restric
     });
     __syncthreads();
   }
+}
+
+template <int NTC>
+__global__ __launch_bounds__(64 * kMcWaves) void k_mconv_att(const float* __restrict__ u, int Ms,
+                                                             const uint4* __restrict__ F, int LT, int M, int Lh,
+                                                             int PK, const float* base, float sign,
+                                                             const float* __restrict__ g,
+                                                             const float* __restrict__ dbasis, float* out,
+                                                             MomentTemplates mt) {
+  mconv_body<8, NTC, UMBIR_STORAGE_F32, true>(blockIdx.x, blockIdx.y, u, Ms, F, LT, M, Lh, PK, base, sign, g, dbasis,
+                                              out, mt);
 }
 
 // ---- launches
@@ -1127,7 +1428,11 @@ float* phase_image(const umbir_geometry& G, void* fine) {
 
 bool forward_moments_on(const umbir_geometry& G) { return G.form == 1 && G.split && G.mom.R > 0; }
 
-bool moments_on(const umbir_geometry& G) { return forward_moments_on(G) && G.storage == UMBIR_STORAGE_F32; }
+bool adjoint_moments_on(const umbir_geometry& G) {
+  return forward_moments_on(G) && G.storage == UMBIR_STORAGE_F32;
+}
+
+bool moments_on(const umbir_geometry& G) { return adjoint_moments_on(G) && G.mom.NG == 1; }
 
 // One scan position reads the image as it is.
 float* moment_image(const umbir_geometry& G, void* fine) {
@@ -1149,6 +1454,20 @@ int run_forward_moments(const umbir_geometry& G, const float* x, void* out, cons
   float* u = static_cast<float*>(fine);
   const float* xp = G.P == 1 && x ? x : phase_image(G, fine);
   const int xp_bytes = int(size_t(G.nz) * G.mom.pitch * G.mom.Lq * 4);  // P == 1: the image's own bytes
+  if (G.mom.NG > 1) {  // (a forward alone: no fold)
+    const MomentShape& ms = G.mom;
+    const dim3 grid(unsigned(G.K), unsigned(ms.Ms / kMsBins), unsigned((G.P + 63) / 64 * ms.NG));
+    UMBIR_LAUNCH("splat", k_msplat_att, grid, dim3(64 * kMsWaves), msplat_lds<8>(ms.ls), s, xp, xp_bytes, G.mom_start,
+                 G.mom_rec4, G.mom_rec_hi, G.P, G.K, G.M, ms, G.mom_span, u);
+    with_tiles(moment_tiles(G), [&](auto nc) {
+      constexpr int NTC = decltype(nc)::value;
+      const dim3 cgrid(unsigned((G.traces() + 31) / 32), unsigned((G.M + 32 * NTC - 1) / (32 * NTC)));
+      UMBIR_LAUNCH("conv", (k_mconv_att<NTC>), cgrid, dim3(64 * kMcWaves), mconv_lds(8, ms.LT, NTC), s, u, ms.Ms,
+                   G.mom_taps, ms.LT, G.M, G.Lh, G.traces(), static_cast<const float*>(base), sign, g, G.dbasis,
+                   static_cast<float*>(out), MomentTemplates{G.mom_span, ms.NG});
+    });
+    return check_hip(hipGetLastError(), "attenuated moments");
+  }
   const CostFold f = fold ? *fold : CostFold{};
   with_r(G.mom.R, [&](auto rc) {
     constexpr int R = decltype(rc)::value;
@@ -1170,6 +1489,24 @@ int run_forward_moments(const umbir_geometry& G, const float* x, void* out, cons
 
 int run_adjoint_moments(const umbir_geometry& G, const float* r, void* fine, float* partial, hipStream_t s) {
   float* v = static_cast<float*>(fine);
+  if (G.mom.NG > 1) {
+    const MomentShape& ms = G.mom;
+    with_tiles(moment_tiles(G), [&](auto nc) {
+      constexpr int NT = decltype(nc)::value;
+      const dim3 grid(unsigned((G.traces() + 31) / 32), unsigned((ms.Ms / 32 + NT - 1) / NT), unsigned(ms.NG));
+      UMBIR_LAUNCH("corr", (k_mcorr_att<NT>), grid, dim3(64 * kMcWaves), mcorr_lds(8, ms.LT), s, r, G.mom_taps, ms.LT,
+                   G.M, G.Lh, G.traces(), ms.Ms, ms.NG, G.mom_span, v);
+    });
+    const int tpg = (G.traces() + G.trace_groups - 1) / G.trace_groups;
+    // one generation: at most 1024 blocks (four per CU)
+    const int chunk = 256 * kMgAttVpt;
+    int nb = (G.voxels() + chunk - 1) / chunk;
+    nb = std::max(1, std::min(nb, 1024 / G.trace_groups));
+    const int vpb = (G.voxels() + nb - 1) / nb;
+    UMBIR_LAUNCH("gather", k_mgather_att, dim3(unsigned(G.trace_groups), unsigned(nb)), dim3(256), 0, s, v, ms, G.nx,
+                 G.nz, G.n_off, G.legs, G.gunit, G.tau, G.base, G.P, G.K, log2_int(G.Q), G.M, tpg, vpb, partial);
+    return check_hip(hipGetLastError(), "attenuated moments");
+  }
   with_r(G.mom.R, [&](auto rc) {
     with_tiles(moment_tiles(G), [&](auto nc) {
       launch_mcorr<decltype(rc)::value, decltype(nc)::value>(G, r, v, s);
@@ -1288,7 +1625,7 @@ MomentShape moment_shape(const MomentInput& in) {
   const int Q = in.Q;
   // the dense part pays from Q >= 2 R on; longer records than the plan's LDS
   // histograms keep the fine grid
-  if (in.n_gamma != 1 || Q < 16 || in.M > 16384) return ms;
+  if (Q < 16 || long(in.M) * in.n_gamma > (in.n_gamma == 1 ? 16384 : 36864)) return ms;
   // the window must end where the pulse is (numerically) zero: the table's
   // forced zeros at its ends are then no step
   const double tc = 0.5 * in.t_win;
@@ -1297,6 +1634,14 @@ MomentShape moment_shape(const MomentInput& in) {
   int R = 0;
   for (int c : {5, 6, 8})
     if (!R && 2 * c <= Q && fit_remainder(in.f_c, in.sigma_t, 0.5 / in.fs, c) <= 1e-8) R = c;
+  if (in.n_gamma > 1) {
+    // six coefficients (an attenuated response is smoother than the pulse, so
+    // the same remainder relative to its own, smaller peak) and the two ends
+    if (Q < 16 || in.Lh < 2 || in.storage != UMBIR_STORAGE_F32 ||
+        fit_remainder(in.f_c, in.sigma_t, 0.5 / in.fs, 6) > 1e-8)
+      return ms;
+    R = 8;
+  }
   if (!R) return ms;
   // scan positions a constant whole number of voxels apart
   const int P = in.P, K = in.K;
@@ -1317,9 +1662,10 @@ MomentShape moment_shape(const MomentInput& in) {
   const double recs = double(K) * in.nz * NR;
   if (recs * 4.0 * (R + 1) > 4e9 || recs > 1e9 || double(in.nz) * pitch * Lq > 1e8) return ms;
   const int LT = in.Lh + 9;
-  if (size_t(R) * 3 * LT * 16 > 150u * 1024 || double(K) * in.M > 6.4e7) return ms;
-  if (gather_window_bytes(in.nx, in.nz, long(P) * K, long(in.M) * Q, in.storage) == 0) return ms;
+  if (size_t(R) * 3 * LT * 16 > 150u * 1024 || double(K) * in.M * in.n_gamma > 6.4e7) return ms;
+  if (in.n_gamma == 1 && gather_window_bytes(in.nx, in.nz, long(P) * K, long(in.M) * Q, in.storage) == 0) return ms;
   ms.R = R;
+  ms.NG = in.n_gamma;
   ms.Ms = (in.M + 31) & ~31;
   ms.LT = LT;
   ms.pitch = int(pitch);
@@ -1328,22 +1674,24 @@ MomentShape moment_shape(const MomentInput& in) {
   ms.rel0 = -int(pitch) * (P - 1);
   ms.ls = 2;
   while ((1 << ms.ls) < P && ms.ls < 6) ++ms.ls;
-  ms.u_bytes = (size_t(P) * K * R * ms.Ms * 4 + 255) & ~size_t(255);
+  ms.u_bytes = (size_t(ms.NG) * P * K * R * ms.Ms * 4 + 255) & ~size_t(255);
   // the image by phase, and the lanes past the last scan position of it
   ms.work_bytes = ms.u_bytes + (size_t(in.nz) * ms.pitch * ms.Lq * 4 + 255 & ~size_t(255));
   ms.records = size_t(K) * in.nz * ms.NR;
-  ms.table_bytes = ms.records * 4 * (R + 1) + size_t(K) * (in.M + 1) * 4 + size_t(R) * 3 * LT * 16;
+  ms.table_bytes = ms.records * 4 * (R + 1) + size_t(K) * (size_t(ms.NG) * in.M + 1) * 4 +
+                   size_t(ms.NG) * R * 3 * LT * 16 + (ms.NG > 1 ? size_t(ms.NG) * 8 : 0);
   return ms;
 }
 
 // Least-squares fit of degree R - 1 on z_t = 2 t / Q - 1, t = 0 .. Q: the
 // R x (Q + 1) matrix taking the values to the coefficients (normal equations
 // by Gaussian elimination with pivoting; they are well conditioned at R <= 8).
-static std::vector<double> fit_matrix(int R, int Q) {
+// Point `skip` is left out.
+static std::vector<double> fit_matrix(int R, int Q, int skip = -1) {
   std::vector<double> V(size_t(R) * (Q + 1)), A(size_t(R) * R, 0.0);
   for (int t = 0; t <= Q; ++t) {
     double z = 2.0 * t / Q - 1.0, p = 1.0;
-    for (int k = 0; k < R; ++k, p *= z) V[size_t(k) * (Q + 1) + t] = p;
+    for (int k = 0; k < R; ++k, p *= z) V[size_t(k) * (Q + 1) + t] = t == skip ? 0.0 : p;
   }
   for (int a = 0; a < R; ++a)
     for (int b = 0; b < R; ++b)
@@ -1375,11 +1723,17 @@ int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s) {
   const MomentShape& ms = G->mom;
   const int R = ms.R, K = G->K, M = G->M, Q = G->Q;
   const int chunks = (ms.NR + kPlanChunk - 1) / kPlanChunk;
-  const size_t n_count = size_t(K) * chunks * M;
-  const std::vector<double> fit = fit_matrix(R, Q);
+  const int NB = ms.NG * M;
+  const size_t n_count = size_t(K) * chunks * NB;
+  std::vector<double> fit = fit_matrix(ms.NG > 1 ? 6 : R, Q);
+  if (ms.NG > 1)
+    for (int skip : {Q, 0}) {
+      const std::vector<double> f = fit_matrix(6, Q, skip);
+      fit.insert(fit.end(), f.begin(), f.end());
+    }
   const size_t fit_bytes = (fit.size() * sizeof(double) + 255) & ~size_t(255);
   const size_t count_bytes = (n_count * sizeof(int) + 255) & ~size_t(255);
-  const size_t g_bytes = (size_t(R) * G->Lh * sizeof(float) + 255) & ~size_t(255);
+  const size_t g_bytes = (size_t(ms.NG) * R * G->Lh * sizeof(float) + 255) & ~size_t(255);
   char* tmp = nullptr;
   int st = check_hip(hipMallocAsync(reinterpret_cast<void**>(&tmp),
                                     fit_bytes + 256 + g_bytes + count_bytes + ms.records * sizeof(unsigned), s),
@@ -1391,24 +1745,31 @@ int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s) {
   int* counts = reinterpret_cast<int*>(tmp + fit_bytes + 256 + g_bytes);
   unsigned* keys = reinterpret_cast<unsigned*>(tmp + fit_bytes + 256 + g_bytes + count_bytes);
   const int cap = G->nz * ms.NR;
-  const size_t lds = size_t(M) * sizeof(int);
+  const size_t lds = size_t(NB) * sizeof(int);
   const dim3 cg{unsigned(K), unsigned(chunks), 1u};
   if (!(st = check_hip(hipMemcpyAsync(fit_dev, fit.data(), fit.size() * sizeof(double), hipMemcpyHostToDevice, s),
                        "hipMemcpyAsync(fit)")) &&
       !(st = check_hip(hipMemsetAsync(mb, 0, sizeof(int), s), "hipMemsetAsync(plan)"))) {
-    UMBIR_LAUNCH("moment_fit", k_moment_fit, dim3(unsigned((G->Lh + 3) / 4)), dim3(256), 0, s, R, Q, G->Lh,
-                 1.0 / (double(Q) * G->fs), G->f_c, 1.0 / (2.0 * G->sigma_t * G->sigma_t), 0.5 * G->t_win, fit_dev, g);
-    UMBIR_LAUNCH("moment_table", k_moment_table, dim3(unsigned((R * ms.LT + 255) / 256)), dim3(256), 0, s, R, G->Lh,
-                 ms.LT, g, G->mom_taps);
-    UMBIR_LAUNCH("plan_count", k_plan_count, cg, dim3(256), lds, s, G->legs, G->base, ms, G->P, K, G->nz, G->n_off, M,
-                 counts);
-    UMBIR_LAUNCH("plan_scan", k_plan_scan, dim3(unsigned(K)), dim3(1024), 0, s, M, chunks, cap, counts, G->mom_start,
+    if (ms.NG > 1)
+      UMBIR_LAUNCH("moment_fit", k_template_fit, dim3(unsigned((G->Lh + 3) / 4), unsigned(ms.NG)), dim3(256), 0, s, Q,
+                   G->Lh, G->bank, fit_dev, g);
+    else
+      UMBIR_LAUNCH("moment_fit", k_moment_fit, dim3(unsigned((G->Lh + 3) / 4)), dim3(256), 0, s, R, Q, G->Lh,
+                   1.0 / (double(Q) * G->fs), G->f_c, 1.0 / (2.0 * G->sigma_t * G->sigma_t), 0.5 * G->t_win, fit_dev, g);
+    // (the templates' rows follow one another in g and in the table)
+    UMBIR_LAUNCH("moment_table", k_moment_table, dim3(unsigned((ms.NG * R * ms.LT + 255) / 256)), dim3(256), 0, s,
+                 ms.NG * R, G->Lh, ms.LT, g, G->mom_taps);
+    UMBIR_LAUNCH("plan_count", k_plan_count, cg, dim3(256), lds, s, G->legs, G->gunit, G->base, ms, G->P, K, G->nz,
+                 G->n_off, M, counts);
+    UMBIR_LAUNCH("plan_scan", k_plan_scan, dim3(unsigned(K)), dim3(1024), 0, s, NB, chunks, cap, counts, G->mom_start,
                  mb);
-    UMBIR_LAUNCH("plan_fill", k_plan_fill, cg, dim3(256), lds, s, G->legs, G->base, ms, G->P, K, G->nz, G->n_off, M,
-                 counts, keys);
+    if (ms.NG > 1)
+      UMBIR_LAUNCH("plan_span", k_plan_span, dim3(unsigned(ms.NG)), dim3(256), 0, s, G->mom_start, K, M, NB, G->mom_span);
+    UMBIR_LAUNCH("plan_fill", k_plan_fill, cg, dim3(256), lds, s, G->legs, G->gunit, G->base, ms, G->P, K, G->nz,
+                 G->n_off, M, counts, keys);
     with_r(R, [&](auto rc) {
-      UMBIR_LAUNCH("plan_emit", k_plan_emit<decltype(rc)::value>, dim3(unsigned(K), unsigned((M + 3) / 4)), dim3(256),
-                   0, s, G->legs, G->base, G->tau, ms, G->P, K, G->n_off, log2_int(Q), M, G->mom_start, keys, mb,
+      UMBIR_LAUNCH("plan_emit", k_plan_emit<decltype(rc)::value>, dim3(unsigned(K), unsigned((NB + 3) / 4)), dim3(256),
+                   0, s, G->legs, G->base, G->tau, ms, G->P, K, G->n_off, log2_int(Q), NB, G->mom_start, keys, mb,
                    G->mom_rec4, G->mom_rec_hi);
     });
     st = check_hip(hipGetLastError(), "moment plan");

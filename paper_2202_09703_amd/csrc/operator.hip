@@ -2836,7 +2836,7 @@ int umbir_adjoint(const umbir_geometry* G, const void* r, float* x, void* work, 
   Carve cv{static_cast<char*>(ws.ptr)};
   void* fine = cv.take<char>(G->fine_bytes());
   float* partial = cv.take<float>(size_t(G->trace_groups) * G->voxels());
-  return run_adjoint(*G, r, x, 1.0f, false, moments_on(*G), fine, partial, s);
+  return run_adjoint(*G, r, x, 1.0f, false, adjoint_moments_on(*G), fine, partial, s);
 }
 
 int umbir_direct(const umbir_geometry* G, const float* g, void* y, int accumulate, void* stream) {

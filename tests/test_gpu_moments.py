@@ -18,6 +18,7 @@ import pytest
 
 from synth import tiny_card, random_vector
 from synth.cards import Acquisition, Array, Grid, MM, MHZ, US
+from oracle import attenuation as oa
 from oracle import geometry as og
 from oracle import operator as oo
 
@@ -29,14 +30,15 @@ umbir = pytest.importorskip("paper_2202_09703_amd.umbir")
 TOL = 2e-6
 
 
-def card(nx, nz, scans, rx, samples, mhz=20, pitch=1, f_c=0.5, layers=3, storage=0):
+def card(nx, nz, scans, rx, samples, mhz=20, pitch=1, f_c=0.5, layers=3, storage=0, templates=0):
     """1 mm x 0.5 mm voxels under `scans` positions `pitch` voxels apart (right
     to left if negative); the 500 kHz pulse in a 12 us window (5 moments at 20
     MHz, 6 at 10 MHz) or the 2 MHz pulse in a 3 us one (8 at 20 MHz)."""
-    c = tiny_card(n_layers=layers, nx=nx, nz=nz)
+    c = tiny_card(n_layers=layers, nx=nx, nz=nz, atten=(2e-5, 0.0, 4e-5) if templates else None)
     wide = f_c < 1
     acq = Acquisition(n_samples=samples, fs=mhz * MHZ, f_c=f_c * MHZ, sigma_t=(1.25 if wide else 0.3) * US,
-                      t_win=(12 if wide else 3) * US, oversample=int(640 / mhz), storage=storage)
+                      t_win=(12 if wide else 3) * US, oversample=int(640 / mhz), storage=storage,
+                      **(dict(n_gamma=templates) if templates else {}))
     arr = Array(tx_x=tuple((pitch * (i - scans // 2) - 0.5 * (nx % 2 == 0)) * MM for i in range(scans)),
                 rx_offset=tuple((j - (rx - 1) / 2) * 2 * MM for j in range(rx)), beta=8)
     return dataclasses.replace(c, acq=acq, array=arr, grid=Grid(nx=nx, nz=nz, dx=MM, dz=0.5 * MM, x0=-nx * MM / 2))
@@ -112,6 +114,39 @@ def test_long_gather_windows(dev, scale, lo, hi):
     xa = umbir.adjoint(geom, r)
     assert torch.equal(umbir.adjoint(geom, r), xa)
     assert rel(xa.cpu(), oo.adjoint(c, r.cpu().numpy().astype(np.float64))) <= TOL
+    geom.free()
+
+
+@pytest.mark.parametrize("kw", [
+    dict(nx=33, nz=40, scans=1, rx=3, samples=600, templates=2),
+    dict(nx=31, nz=48, scans=5, rx=3, samples=700, pitch=-2, templates=16),
+    dict(nx=40, nz=32, scans=6, rx=2, samples=310, pitch=3, mhz=10, templates=8),
+    dict(nx=70, nz=30, scans=70, rx=1, samples=515, templates=4),             # a second chunk of scan lanes
+    dict(nx=24, nz=33, scans=3, rx=11, samples=576, pitch=2, templates=64),   # the largest plan: 36864 bins
+    dict(nx=20, nz=40, scans=3, rx=2, samples=90, templates=16),              # records shorter than the window
+])
+def test_attenuated_templates_as_moments(dev, kw):
+    """A and A^T with attenuation: six moments per template (of its row of the
+    bank, rounded to FP32: 2^-25 of its peak) and the two ends of the window,
+    where the rows are forced to zero."""
+    c = card(**kw)
+    assert oa.near_ties(c, 1e-9) == []
+    geom = umbir.build_geometry(c)
+    assert geom.n_gamma == kw["templates"]
+    x = random_vector((c.grid.nz, c.grid.nx), seed=41)
+    r = random_vector(geom.trace_shape, seed=42)
+    xt, rt = (torch.tensor(v, dtype=torch.float32, device=dev) for v in (x, r))
+    x32, r32 = xt.cpu().numpy().astype(np.float64), rt.cpu().numpy().astype(np.float64)
+    y, xa = umbir.forward(geom, xt), umbir.adjoint(geom, rt)
+    assert torch.equal(y, umbir.forward(geom, xt)) and torch.equal(xa, umbir.adjoint(geom, rt))
+    acc = umbir.forward(geom, xt, rt.clone(), accumulate=True)
+    geom.set_tuning(products=1)
+    yf, xf = umbir.forward(geom, xt), umbir.adjoint(geom, rt)
+    assert not torch.equal(y, yf) and not torch.equal(xa, xf)  # the moment form did run
+    yo, xo = oo.forward(c, x32), oo.adjoint(c, r32)
+    es = [rel(y.cpu(), yo), rel(xa.cpu(), xo), rel(yf.cpu(), yo), rel(xf.cpu(), xo)]
+    print("forward, adjoint rel L2: moments %.2e %.2e, fine grid %.2e %.2e" % tuple(es))
+    assert max(es[:2]) <= TOL and rel(acc.cpu(), r32 + yo) <= TOL
     geom.free()
 
 
