@@ -357,8 +357,8 @@ __global__ void k_phase_image(const float* __restrict__ x, int nx, int nz, int P
 
 // ---- S
 
-// u of receiver bx, samples 16 by .. 16 by + 15, scan lanes 64 bz ...: a wave
-// takes four consecutive samples, 64 records of one at a time: loaded one per
+// u of receiver bx, samples BINS by .. BINS by + BINS - 1, scan lanes 64 bz ...: a
+// wave takes BINS / 4 consecutive samples, 64 records of one at a time: loaded one per
 // lane (the next 64 are in flight meanwhile), parked in the wave's own LDS,
 // then multiplied G = 64 / S records a step (S lanes, a power of two >= 4, per
 // record: one scan position each) on the matrix cores, v_mfma_f32_4x4x1: lane l
@@ -372,8 +372,14 @@ __global__ void k_phase_image(const float* __restrict__ x, int nx, int nz, int P
 // address processing at 118 clocks per 64 (trace, voxel) pairs and CU.  A step
 // here costs one coalesced image load (L1), two LDS reads and about five
 // vector instructions.
-constexpr int kMsBins = 16;   // samples per block
 constexpr int kMsWaves = 4;
+constexpr int kMsBins = 16;  // samples per block of a full grid: a wave's four follow one another
+// With few blocks a wave takes one sample, four times the blocks: the chain of
+// record and image loads of one sample, not four, is what a small call waits
+// for (8 receivers, 256 samples, 64 x 64 voxels, 128 blocks of 16: 6.2 against
+// 9.3 us between events around the launch).  From two blocks of 16 per CU on the longer runs of stores win.
+constexpr int kMsBinsFew = 4;
+int msplat_bins(long blocks16) { return blocks16 < 512 ? kMsBinsFew : kMsBins; }
 
 // LDS words of a parked record: R coefficients, the offset, padding
 template <int R>
@@ -418,21 +424,21 @@ __device__ __forceinline__ void msplat_steps(const float* recs, int lane, unsign
   }
 }
 
-template <int R>
+template <int R, int BINS>
 __device__ __forceinline__ void msplat_body(int bx, int by, int bz, const float* __restrict__ xp, int xp_bytes,
                                             const int* __restrict__ start, const float4* __restrict__ rec4,
                                             const float* __restrict__ rec_hi, int P, int K, int M, int sstride, int Ms,
                                             int ls, int reversed, float* __restrict__ u) {
   extern __shared__ __align__(16) float sm[];
   constexpr int W = msplat_rec_words<R>();
-  constexpr int NB = kMsBins / kMsWaves;
+  constexpr int NB = BINS / kMsWaves;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int S = 1 << ls, sh = 6 - ls;
   float* recs = sm + wave * 64 * W;           // [64][W]
-  float* outu = sm + kMsWaves * 64 * W;       // [R][S][kMsBins + 1]
+  float* outu = sm + kMsWaves * 64 * W;       // [R][S][BINS + 1]
   const __amdgpu_buffer_rsrc_t xrs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(xp), 0, xp_bytes, kBufferWord3);
-  const int j = bx, n0 = by * kMsBins, nw = n0 + NB * wave;
+  const int j = bx, n0 = by * BINS, nw = n0 + NB * wave;
   const unsigned xl4 = unsigned(64 * bz + (lane & (S - 1))) * 4u;  // this lane's scan position
   // the records of the wave's samples: [at[b], at[b + 1])
   const int* sj = start + size_t(j) * sstride;
@@ -489,28 +495,27 @@ __device__ __forceinline__ void msplat_body(int bx, int by, int bz, const float*
     }
     if (lane < S) {
 #pragma unroll
-      for (int p = 0; p < R; ++p) outu[(p * S + lane) * (kMsBins + 1) + NB * wave + b] = float(acc[p]);
+      for (int p = 0; p < R; ++p) outu[(p * S + lane) * (BINS + 1) + NB * wave + b] = float(acc[p]);
     }
   }
   __syncthreads();
-  // runs of 16 samples of one (trace, moment)
-  for (int i = threadIdx.x; i < R * S * kMsBins; i += blockDim.x) {
-    const int b = i & (kMsBins - 1), ps = i >> 4;
+  // runs of BINS samples of one (trace, moment)
+  for (int i = threadIdx.x; i < R * S * BINS; i += blockDim.x) {
+    const int b = i & (BINS - 1), ps = i / BINS;
     const int p = ps >> ls, sc = 64 * bz + (ps & (S - 1));
     if (sc < P) {
       const int t = (reversed ? P - 1 - sc : sc) * K + j;
-      u[(size_t(t) * R + p) * Ms + n0 + b] = outu[ps * (kMsBins + 1) + b];
+      u[(size_t(t) * R + p) * Ms + n0 + b] = outu[ps * (BINS + 1) + b];
     }
   }
 }
-static_assert(kMsBins == 16, "msplat_body's index shifts");
 
-template <int R>
+template <int R, int BINS = kMsBins>
 size_t msplat_lds(int ls) {
-  return size_t(kMsWaves * 64 * msplat_rec_words<R>() + R * (1 << ls) * (kMsBins + 1)) * sizeof(float);
+  return size_t(kMsWaves * 64 * msplat_rec_words<R>() + R * (1 << ls) * (BINS + 1)) * sizeof(float);
 }
 
-template <int R>
+template <int R, int BINS>
 __global__ __launch_bounds__(64 * kMsWaves) void k_msplat(const float* __restrict__ xp, int xp_bytes,
                                                           const int* __restrict__ start,
                                                           const float4* __restrict__ rec4,
@@ -521,8 +526,8 @@ __global__ __launch_bounds__(64 * kMsWaves) void k_msplat(const float* __restric
     extern __shared__ __align__(16) float sm[];
     fold_cost(fold, reinterpret_cast<double*>(sm));
   }
-  msplat_body<R>(blockIdx.x, blockIdx.y, blockIdx.z, xp, xp_bytes, start, rec4, rec_hi, P, K, M, M + 1, Ms, ls,
-                 reversed, u);
+  msplat_body<R, BINS>(blockIdx.x, blockIdx.y, blockIdx.z, xp, xp_bytes, start, rec4, rec_hi, P, K, M, M + 1, Ms, ls,
+                       reversed, u);
 }
 
 // Every template's u (grid z: scan chunks of template 0, of template 1, ...),
@@ -542,7 +547,7 @@ __global__ __launch_bounds__(64 * kMsWaves) void k_msplat_att(const float* __res
   const int2 sp = span[gb];
   const int n0 = blockIdx.y * kMsBins;
   if (n0 >= sp.y || n0 + kMsBins <= sp.x) return;  // uniform
-  msplat_body<8>(blockIdx.x, blockIdx.y, blockIdx.z - gb * chunks, xp, xp_bytes, start + size_t(gb) * M, rec4, rec_hi,
+  msplat_body<8, kMsBins>(blockIdx.x, blockIdx.y, blockIdx.z - gb * chunks, xp, xp_bytes, start + size_t(gb) * M, rec4, rec_hi,
                  P, K, M, ms.NG * M + 1, ms.Ms, ms.ls, ms.reversed, u + size_t(gb) * P * K * 8 * ms.Ms);
 }
 
@@ -714,17 +719,18 @@ __device__ __forceinline__ void load8(const float* row, int m, int M, bool insid
   }
 }
 
-// C^T: a wave computes 32 traces x 32 samples x all R moments (the trace
-// samples are split into pieces once for the R products); a block has NT
-// sample tiles and 8 / NT waves on each, which share the window's steps and
-// add their sums in LDS, halving.  The eight samples of a lane go in reversed,
-// so that C's table serves.
+// C^T: a block computes NT tiles of 32 traces x 32 samples x all R moments, with
+// 8 / NT waves on each tile; the eight samples of a lane go in reversed, so that
+// C's table serves.
 // PAIR: v of one template for the gather of pairs, [..][n][R] in place of
 // [..][R][n] (vstride: floats between traces).
-template <int R, int NT, bool PAIR = false>
-__device__ __forceinline__ void mcorr_body(int bx, int by, const float* __restrict__ r,
-                                           const uint4* __restrict__ F, int LT, int M, int Lh, int PK, int Ms,
-                                           float* __restrict__ v, size_t vstride = 0) {
+//
+// Four tiles: a tile's two waves share the window's steps (the samples are
+// split into pieces once for the R products) and add their sums in LDS.
+template <int R, int NT, bool PAIR>
+__device__ __forceinline__ void mcorr_shared_steps(int bx, int by, const float* __restrict__ r,
+                                                   const uint4* __restrict__ F, int LT, int M, int Lh, int PK, int Ms,
+                                                   float* __restrict__ v, size_t vstride) {
   extern __shared__ __align__(16) float sm[];
   constexpr int KS = kMcWaves / NT;
   uint4* tab = reinterpret_cast<uint4*>(sm);
@@ -807,6 +813,89 @@ __device__ __forceinline__ void mcorr_body(int bx, int by, const float* __restri
     }
 }
 
+// One or two tiles (few traces or samples: the time of one block is the
+// launch's): the waves share the moments, ceil(R NT / 8) each over all of the
+// window, so that there are no sums to add up between them; each splits the
+// samples for itself.  8.8 against 12.9 us for 8 traces of 256 samples (10 MHz,
+// between events around the launch).  With four tiles the running sum of a
+// whole window in one wave rounds more (2.5e-7 against 2.0e-7 relative L2 of the
+// adjoint at 256 x 256); adding each step by itself, as here, takes registers
+// that halve the blocks of a CU (165 against 142 us at 512 x 512).
+template <int R, int NT, bool PAIR>
+__device__ __forceinline__ void mcorr_shared_moments(int bx, int by, const float* __restrict__ r,
+                                                     const uint4* __restrict__ F, int LT, int M, int Lh, int PK,
+                                                     int Ms, float* __restrict__ v, size_t vstride) {
+  extern __shared__ __align__(16) float sm[];
+  constexpr int KS = kMcWaves / NT;
+  constexpr int NP = (R + KS - 1) / KS;  // moments per wave
+  uint4* tab = reinterpret_cast<uint4*>(sm);
+  const int tr0 = bx * 32;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 31, lk = lane >> 5;
+  const int jt = wave % NT, p0 = wave / NT * NP;
+  const int n0 = (by * NT + jt) * 32;
+  stage_table(tab, F, R * 3 * LT);
+  floatx16 acc[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[p][i] = 0.0f;
+  const float* row = r + size_t(min(tr0 + li, PK - 1)) * M;
+  // samples m of [n0 + 1, n0 + 31 + Lh], in steps of 16 from n0
+  const int steps = n0 < M && p0 < R ? min((Lh + 32 + 15) >> 4, (M - n0 + 15) >> 4) : 0;
+  auto multiply = [&](int s, const float (&x)[8]) {
+    const Pieces8 a = split8_bf16x3(make_float4(x[7], x[6], x[5], x[4]), make_float4(x[3], x[2], x[1], x[0]));
+    const int D = min(max(16 * s + 8 * lk + 6 - li, -1), LT - 2);
+    const uint4* tp = tab + 1 + D + 3 * p0 * LT;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      if (R % NP != 0 && p0 + p >= R) continue;  // uniform
+      const uint4 b[3] = {tp[(3 * p) * LT], tp[(3 * p + 1) * LT], tp[(3 * p + 2) * LT]};
+      // a step's six products by themselves: one rounding of the running sum
+      // per step, not six
+      floatx16 t;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) t[i] = 0.0f;
+      acc[p] += mfma_bf16x3(a.p, b, t);
+    }
+  };
+  auto fetch = [&](int s, float (&x)[8]) {
+    load8(row, n0 + 16 * s + 8 * lk, M, n0 + 16 * s + 16 <= M, x);
+  };
+  float x0[8], x1[8];
+  if (steps > 0) fetch(0, x0);
+  __syncthreads();
+  for (int s = 0; s < steps; s += 2) {
+    if (s + 1 < steps) fetch(s + 1, x1);
+    multiply(s, x0);
+    if (s + 1 < steps) {
+      if (s + 2 < steps) fetch(s + 2, x0);
+      multiply(s + 1, x1);
+    }
+  }
+  if (n0 >= Ms) return;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int tr = tr0 + 8 * (i >> 2) + 4 * lk + (i & 3);
+    if (tr >= PK) continue;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      if (p0 + p >= R) continue;
+      if constexpr (PAIR) v[tr * vstride + size_t(n0 + li) * R + p0 + p] = acc[p][i];
+      else v[(size_t(tr) * R + p0 + p) * Ms + n0 + li] = acc[p][i];
+    }
+  }
+}
+
+template <int R, int NT, bool PAIR = false>
+__device__ __forceinline__ void mcorr_body(int bx, int by, const float* __restrict__ r,
+                                           const uint4* __restrict__ F, int LT, int M, int Lh, int PK, int Ms,
+                                           float* __restrict__ v, size_t vstride = 0) {
+  if constexpr (NT == 4) mcorr_shared_steps<R, NT, PAIR>(bx, by, r, F, LT, M, Lh, PK, Ms, v, vstride);
+  else mcorr_shared_moments<R, NT, PAIR>(bx, by, r, F, LT, M, Lh, PK, Ms, v, vstride);
+}
+
+// the table, then the sums of one of two waves per tile
 size_t mcorr_lds(int R, int LT) {
   return std::max(size_t(R) * 3 * LT * sizeof(uint4), size_t(kMcWaves / 2) * R * 1024 * sizeof(float));
 }
@@ -1306,7 +1395,7 @@ __global__ __launch_bounds__(64 * kMsWaves) void k_msplat_list(const BatchProb* 
     const BatchProb& p = probs[w.x];
     const float* xp = p.P == 1 ? p.x[which] : p.xt;
     with_r_device(p.mom.R, [&](auto rc) {
-      msplat_body<decltype(rc)::value>(w.y, w.z, w.w, xp, p.nz * p.mom.pitch * p.mom.Lq * 4, p.mom_start, p.mom_rec4,
+      msplat_body<decltype(rc)::value, kMsBins>(w.y, w.z, w.w, xp, p.nz * p.mom.pitch * p.mom.Lq * 4, p.mom_start, p.mom_rec4,
                                        p.mom_rec_hi, p.P, p.K, p.M, p.M + 1, p.mom.Ms, p.mom.ls, p.mom.reversed, p.fine);
     });
     __syncthreads();
@@ -1471,10 +1560,18 @@ int run_forward_moments(const umbir_geometry& G, const float* x, void* out, cons
   const CostFold f = fold ? *fold : CostFold{};
   with_r(G.mom.R, [&](auto rc) {
     constexpr int R = decltype(rc)::value;
-    const size_t lds = std::max<size_t>(fold ? 256 * sizeof(double) : 0, msplat_lds<R>(G.mom.ls));
-    const dim3 grid(unsigned(G.K), unsigned(G.mom.Ms / kMsBins), unsigned((G.P + 63) / 64));
-    UMBIR_LAUNCH("splat", k_msplat<R>, grid, dim3(64 * kMsWaves), lds, s, xp, xp_bytes, G.mom_start, G.mom_rec4,
-                 G.mom_rec_hi, G.P, G.K, G.M, G.mom.Ms, G.mom.ls, G.mom.reversed, u, f);
+    const unsigned chunks = unsigned((G.P + 63) / 64);
+    auto launch = [&](auto bc) {
+      constexpr int BINS = decltype(bc)::value;
+      const size_t lds = std::max<size_t>(fold ? 256 * sizeof(double) : 0, msplat_lds<R, BINS>(G.mom.ls));
+      UMBIR_LAUNCH("splat", (k_msplat<R, BINS>), dim3(unsigned(G.K), unsigned(G.mom.Ms / BINS), chunks),
+                   dim3(64 * kMsWaves), lds, s, xp, xp_bytes, G.mom_start, G.mom_rec4, G.mom_rec_hi, G.P, G.K, G.M,
+                   G.mom.Ms, G.mom.ls, G.mom.reversed, u, f);
+    };
+    if (msplat_bins(long(G.K) * (G.mom.Ms / kMsBins) * chunks) == kMsBins)
+      launch(std::integral_constant<int, kMsBins>());
+    else
+      launch(std::integral_constant<int, kMsBinsFew>());
   });
   if ((st = check_hip(hipGetLastError(), "k_msplat"))) return st;
   with_r(G.mom.R, [&](auto rc) {
