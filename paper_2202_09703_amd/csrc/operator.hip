@@ -907,7 +907,7 @@ __device__ __forceinline__ void gather_lds_body(int bx, int by,
   if (t0 >= t1 && t_off > 0) return;  // uniform over the block: nothing to add
   const int tiles_x = (nx + kGatherTileCols - 1) / kGatherTileCols;
   const int n_tiles = tiles_x * ((nz + kGatherTileRows - 1) / kGatherTileRows);
-  const int tile_end = min(n_tiles, (by + 1) * tiles_per_block);
+  const int blocks = (n_tiles + tiles_per_block - 1) / tiles_per_block;
   const int sh = 32 - qs;
   const int half = n_off / 2;
   const int wave = int(threadIdx.x >> 6), lane = int(threadIdx.x & 63);
@@ -915,7 +915,9 @@ __device__ __forceinline__ void gather_lds_body(int bx, int by,
       __builtin_amdgcn_make_buffer_rsrc(const_cast<Leg*>(legs), 0, nz * n_off * int(sizeof(Leg)), kBufferWord3);
   struct Legs { int64_t d[VPT]; float p[VPT]; };
   struct Taps { unsigned J[VPT]; float phi[VPT], w[VPT]; };
-  for (int tile = by * tiles_per_block; tile < tile_end; ++tile) {
+  // a block's tiles lie a generation of blocks apart: the slow ones (windows too
+  // long for LDS, near the array) are neighbours
+  for (int tile = by; tile < n_tiles; tile += blocks) {
     const int tz = tile / tiles_x;
     const int tx = tile - tz * tiles_x;
     int col2[VPT], rowoff[VPT], vox[VPT];
@@ -1060,12 +1062,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
                              t_cnt, gwin, tiles_per_block, partial);
 }
 
+// Sixteen images in flight, added in order (64 groups of 10^4 voxels one after
+// another: 18 us between events, 6 us so).
 __global__ void k_reduce_groups(const float* __restrict__ partial, int groups, int N, float scale,
                                 float* __restrict__ out) {
   const int v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= N) return;
   float acc = 0.0f;
-  for (int g = 0; g < groups; ++g) acc += partial[size_t(g) * N + v];
+  int g = 0;
+  for (; g + 16 <= groups; g += 16) {
+    float p[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) p[k] = partial[size_t(g + k) * N + v];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) acc += p[k];
+  }
+  for (; g < groups; ++g) acc += partial[size_t(g) * N + v];
   out[v] = acc * scale;
 }
 

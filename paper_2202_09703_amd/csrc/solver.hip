@@ -202,7 +202,15 @@ __device__ __forceinline__ void prior_body(int bx, int by, const float* __restri
   // loaded first so that they arrive while the prior terms are computed
   float u = 0.0f, dv = 0.0f;
   if (UPDATE && v < N) {
-    for (int g = q; g < groups; g += 4) u += part[size_t(g) * N + v];
+    int g = q;
+    for (; g + 28 < groups; g += 32) {  // eight images in flight, added in order
+      float p[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) p[k] = part[size_t(g + 4 * k) * N + v];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) u += p[k];
+    }
+    for (; g < groups; g += 4) u += part[size_t(g) * N + v];
     if (q == 0) dv = den[v];
   }
   int row = 0, col = 0;
