@@ -92,6 +92,9 @@ __device__ __forceinline__ void plan_bases(const int* __restrict__ base, const M
 // Relative columns per plan block: one histogram of samples per (j, chunk).
 constexpr int kPlanChunk = 64;
 
+// Bins a plan block holds in LDS at a time; a block takes slice blockIdx.z.
+constexpr int kPlanSlice = 36864;
+
 // counts[j][chunk][b]: records of receiver j and the chunk's relative columns
 // in bin b (of NB = NG M).
 __global__ __launch_bounds__(256) void k_plan_count(const Leg* __restrict__ legs, const double* __restrict__ gunit,
@@ -99,7 +102,8 @@ __global__ __launch_bounds__(256) void k_plan_count(const Leg* __restrict__ legs
                                                     int n_off, int M, int* __restrict__ counts) {
   extern __shared__ int hist[];
   const int j = blockIdx.x, ch = blockIdx.y, NB = ms.NG * M;
-  for (int i = threadIdx.x; i < NB; i += blockDim.x) hist[i] = 0;
+  const int b0 = blockIdx.z * kPlanSlice, nb = min(NB - b0, kPlanSlice);
+  for (int i = threadIdx.x; i < nb; i += blockDim.x) hist[i] = 0;
   __syncthreads();
   int bt, br;
   plan_bases(base, ms, P, K, j, &bt, &br);
@@ -109,11 +113,11 @@ __global__ __launch_bounds__(256) void k_plan_count(const Leg* __restrict__ legs
     if (rc >= rn) continue;
     const PairLegs p = pair_legs(legs, n_off, bt, br, row, ms.rel0 + r0 + rc);
     const int b = plan_bin(p, gunit, ms, n_off, bt, br, row, ms.rel0 + r0 + rc, M);
-    if (b < NB) atomicAdd(&hist[b], 1);
+    if (b >= b0 && b < b0 + nb) atomicAdd(&hist[b - b0], 1);
   }
   __syncthreads();
-  int* out = counts + (size_t(j) * gridDim.y + ch) * NB;
-  for (int i = threadIdx.x; i < NB; i += blockDim.x) out[i] = hist[i];
+  int* out = counts + (size_t(j) * gridDim.y + ch) * NB + b0;
+  for (int i = threadIdx.x; i < nb; i += blockDim.x) out[i] = hist[i];
 }
 
 // Per receiver: start[j][n] (the first record of bin n of M, start[j][M] the
@@ -121,36 +125,42 @@ __global__ __launch_bounds__(256) void k_plan_count(const Leg* __restrict__ legs
 // of receiver j begin at j * cap.  max_bin receives the largest bin.
 __global__ __launch_bounds__(1024) void k_plan_scan(int M, int chunks, int cap, int* __restrict__ counts,
                                                     int* __restrict__ start, int* __restrict__ max_bin) {
-  __shared__ int part[1024];
-  const int j = blockIdx.x, t = threadIdx.x;
-  const int per = (M + 1023) / 1024;
-  const int n0 = min(t * per, M), n1 = min(n0 + per, M);
+  __shared__ int waves[16];
+  const int j = blockIdx.x, t = threadIdx.x, lane = t & 63;
   int* cj = counts + size_t(j) * chunks * M;
-  int sum = 0, big = 0;
-  for (int n = n0; n < n1; ++n) {
+  int at = j * cap, big = 0;
+  for (int n0 = 0; n0 < M; n0 += 1024) {  // 1024 bins at a time, neighbours in neighbouring threads
+    const int n = n0 + t;
     int c = 0;
-    for (int k = 0; k < chunks; ++k) c += cj[size_t(k) * M + n];
-    sum += c;
+    if (n < M)
+      for (int k = 0; k < chunks; ++k) c += cj[size_t(k) * M + n];
     big = max(big, c);
-  }
-  part[t] = sum;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int v = t >= off ? part[t - off] : 0;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  int at = j * cap + part[t] - sum;
-  for (int n = n0; n < n1; ++n) {
-    start[size_t(j) * (M + 1) + n] = at;
-    for (int k = 0; k < chunks; ++k) {
-      const int c = cj[size_t(k) * M + n];
-      cj[size_t(k) * M + n] = at;
-      at += c;
+    int before = c;  // inclusive over the wave, then exclusive over the block
+    for (int off = 1; off < 64; off <<= 1) {
+      const int v = __shfl_up(before, off, 64);
+      if (lane >= off) before += v;
     }
+    if (lane == 63) waves[t >> 6] = before;
+    __syncthreads();
+    before -= c;
+    int total = 0;
+    for (int w = 0; w < 16; ++w) {
+      if (w < t >> 6) before += waves[w];
+      total += waves[w];
+    }
+    __syncthreads();
+    if (n < M) {
+      int p = at + before;
+      start[size_t(j) * (M + 1) + n] = p;
+      for (int k = 0; k < chunks; ++k) {
+        const int v = cj[size_t(k) * M + n];
+        cj[size_t(k) * M + n] = p;
+        p += v;
+      }
+    }
+    at += total;
   }
-  if (t == 1023) start[size_t(j) * (M + 1) + M] = j * cap + part[1023];
+  if (t == 0) start[size_t(j) * (M + 1) + M] = at;
   if (big > 0) atomicMax(max_bin, big);
 }
 
@@ -161,8 +171,9 @@ __global__ __launch_bounds__(256) void k_plan_fill(const Leg* __restrict__ legs,
                                                    unsigned* __restrict__ keys) {
   extern __shared__ int cursor[];
   const int j = blockIdx.x, ch = blockIdx.y, NB = ms.NG * M;
-  const int* f = first + (size_t(j) * gridDim.y + ch) * NB;
-  for (int i = threadIdx.x; i < NB; i += blockDim.x) cursor[i] = f[i];
+  const int b0 = blockIdx.z * kPlanSlice, nb = min(NB - b0, kPlanSlice);
+  const int* f = first + (size_t(j) * gridDim.y + ch) * NB + b0;
+  for (int i = threadIdx.x; i < nb; i += blockDim.x) cursor[i] = f[i];
   __syncthreads();
   int bt, br;
   plan_bases(base, ms, P, K, j, &bt, &br);
@@ -172,7 +183,8 @@ __global__ __launch_bounds__(256) void k_plan_fill(const Leg* __restrict__ legs,
     if (rc >= rn) continue;
     const PairLegs p = pair_legs(legs, n_off, bt, br, row, ms.rel0 + r0 + rc);
     const int b = plan_bin(p, gunit, ms, n_off, bt, br, row, ms.rel0 + r0 + rc, M);
-    if (b < NB) keys[atomicAdd(&cursor[b], 1)] = unsigned(row) * unsigned(ms.NR) + unsigned(r0 + rc);
+    if (b >= b0 && b < b0 + nb)
+      keys[atomicAdd(&cursor[b - b0], 1)] = unsigned(row) * unsigned(ms.NR) + unsigned(r0 + rc);
   }
 }
 
@@ -1722,7 +1734,7 @@ MomentShape moment_shape(const MomentInput& in) {
   const int Q = in.Q;
   // the dense part pays from Q >= 2 R on; longer records than the plan's LDS
   // histograms keep the fine grid
-  if (Q < 16 || long(in.M) * in.n_gamma > (in.n_gamma == 1 ? 16384 : 36864)) return ms;
+  if (Q < 16 || in.M > 16384 || long(in.M) * in.n_gamma > 262140) return ms;  // (plan_emit's grid)
   // the window must end where the pulse is (numerically) zero: the table's
   // forced zeros at its ends are then no step
   const double tc = 0.5 * in.t_win;
@@ -1842,8 +1854,8 @@ int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s) {
   int* counts = reinterpret_cast<int*>(tmp + fit_bytes + 256 + g_bytes);
   unsigned* keys = reinterpret_cast<unsigned*>(tmp + fit_bytes + 256 + g_bytes + count_bytes);
   const int cap = G->nz * ms.NR;
-  const size_t lds = size_t(NB) * sizeof(int);
-  const dim3 cg{unsigned(K), unsigned(chunks), 1u};
+  const size_t lds = size_t(std::min(NB, kPlanSlice)) * sizeof(int);
+  const dim3 cg{unsigned(K), unsigned(chunks), unsigned((NB + kPlanSlice - 1) / kPlanSlice)};
   if (!(st = check_hip(hipMemcpyAsync(fit_dev, fit.data(), fit.size() * sizeof(double), hipMemcpyHostToDevice, s),
                        "hipMemcpyAsync(fit)")) &&
       !(st = check_hip(hipMemsetAsync(mb, 0, sizeof(int), s), "hipMemsetAsync(plan)"))) {

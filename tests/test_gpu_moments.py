@@ -122,7 +122,8 @@ def test_long_gather_windows(dev, scale, lo, hi):
     dict(nx=31, nz=48, scans=5, rx=3, samples=700, pitch=-2, templates=16),
     dict(nx=40, nz=32, scans=6, rx=2, samples=310, pitch=3, mhz=10, templates=8),
     dict(nx=70, nz=30, scans=70, rx=1, samples=515, templates=4),             # a second chunk of scan lanes
-    dict(nx=24, nz=33, scans=3, rx=11, samples=576, pitch=2, templates=64),   # the largest plan: 36864 bins
+    dict(nx=24, nz=33, scans=3, rx=11, samples=576, pitch=2, templates=64),   # one full slice of plan bins
+    dict(nx=24, nz=33, scans=3, rx=11, samples=581, pitch=2, templates=64),   # and 320 bins of a second one
     dict(nx=20, nz=40, scans=3, rx=2, samples=90, templates=16),              # records shorter than the window
 ])
 def test_attenuated_templates_as_moments(dev, kw):
