@@ -502,7 +502,7 @@ size_t table_bytes(int nz, int n_off, int P, int K, int M, int Q, int Lh, int n_
 
 MomentInput moment_input(const umbir_problem* pb, const Derived& dv) {
   return {pb->grid.nx,   pb->grid.nz, pb->array.n_scans, pb->array.n_rx, pb->acq.n_samples,
-          pb->acq.oversample, dv.Lh,  pb->acq.storage,   dv.n_gamma,     pb->acq.fs,
+          pb->acq.oversample, dv.Lh,  pb->acq.storage,   dv.n_gamma,     pb->array.beta, pb->acq.fs,
           pb->acq.f_c,   pb->acq.sigma_t, pb->acq.t_win, dv.base.data()};
 }
 
@@ -839,7 +839,7 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
     if ((st = alloc((void**)&G->mom_start, size_t(G->K) * (size_t(ms.NG) * G->M + 1) * sizeof(int))) ||
         (st = alloc((void**)&G->mom_rec4, ms.records * sizeof(float4))) ||
         (st = alloc((void**)&G->mom_rec_hi, ms.records * (ms.R - 3) * sizeof(float))) ||
-        (st = alloc((void**)&G->mom_taps, size_t(ms.NG) * ms.R * 3 * ms.LT * sizeof(uint4))) ||
+        (st = alloc((void**)&G->mom_taps, (1 + ms.absolute) * ms.taps_words() * sizeof(uint4))) ||
         (ms.NG > 1 && (st = alloc((void**)&G->mom_span, size_t(ms.NG) * sizeof(int2)))) ||
         (st = build_moments(G, &max_bin, s)))
       return bail(st);

@@ -177,13 +177,15 @@ struct Carve {
 struct MomentShape {
   int R = 0, Ms = 0, LT = 0;
   int NG = 1;  // attenuation templates: each has its own u, [template][trace][R][Ms]
+  int absolute = 0;  // the tables of |b| too (|A| runs as moments)
   int pitch = 0, Lq = 0, NR = 0, rel0 = 0, ls = 0, reversed = 0;
+  size_t taps_words() const { return size_t(NG) * R * 3 * LT; }
   size_t u_bytes = 0, work_bytes = 0, records = 0, table_bytes = 0;
 };
 
 // What decides it.
 struct MomentInput {
-  int nx, nz, P, K, M, Q, Lh, storage, n_gamma;
+  int nx, nz, P, K, M, Q, Lh, storage, n_gamma, beta;
   double fs, f_c, sigma_t, t_win;
   const int* base;  // [P + P K] lattice bases
 };
@@ -279,7 +281,7 @@ struct umbir_geometry {
   int* mom_start = nullptr;         // [K][NG M + 1]
   float4* mom_rec4 = nullptr;       // [records] coefficients 0 .. 3
   float* mom_rec_hi = nullptr;      // [records][R - 3] the others, then the byte offset in the image by phase
-  uint4* mom_taps = nullptr;        // [NG][R][3][LT]
+  uint4* mom_taps = nullptr;        // [NG][R][3][LT], with mom.absolute then those of |b|
   int2* mom_span = nullptr;         // [NG] first sample with a record and the one past the last (attenuation)
   size_t bytes = 0;
 
@@ -373,6 +375,8 @@ __device__ __forceinline__ void fold_cost(const CostFold& f, double* sh) {
 bool moments_on(const umbir_geometry& G);
 bool forward_moments_on(const umbir_geometry& G);
 bool adjoint_moments_on(const umbir_geometry& G);
+// Does |A| (the curvatures' operator) run as moments?
+bool abs_moments_on(const umbir_geometry& G);
 
 // The moment form's counterparts of run_forward and run_adjoint_partial.
 // in_place: the workspace holds x by phase already (run_phase_image, or the
@@ -380,8 +384,9 @@ bool adjoint_moments_on(const umbir_geometry& G);
 int run_phase_image(const umbir_geometry& G, const float* x, void* fine, hipStream_t s);
 float* moment_image(const umbir_geometry& G, void* fine);  // NULL with one scan position
 int run_forward_moments(const umbir_geometry& G, const float* x, void* out, const void* base, float sign,
-                        const float* g, void* fine, hipStream_t s, bool in_place, const CostFold* fold);
-int run_adjoint_moments(const umbir_geometry& G, const float* r, void* fine, float* partial, hipStream_t s);
+                        const float* g, bool abs_op, void* fine, hipStream_t s, bool in_place, const CostFold* fold);
+int run_adjoint_moments(const umbir_geometry& G, const float* r, bool abs_op, void* fine, float* partial,
+                        hipStream_t s);
 
 // A group of ICD's voxels (solver.hip): the class (row % Sr, col % Sc).
 struct IcdGroup {
@@ -399,12 +404,12 @@ __device__ __forceinline__ void icd_member(const IcdGroup& gp, int Sr, int Sc, i
   *col = gp.c0 + cc * Sc;
 }
 
-// Its trace sums A_t^T e_t and its residual update as moments; mom: u_bytes of
-// workspace each.
-int run_icd_dots_moments(const umbir_geometry& G, const float* e, const IcdGroup& gp, int Sr, int Sc, float* mom,
-                         float* partial, hipStream_t s);
-int run_icd_update_moments(const umbir_geometry& G, const IcdGroup& gp, int Sr, int Sc, const float* delta, float* mom,
-                           float* e, hipStream_t s);
+// Its trace sums A_t^T e_t and its residual update e = base - A delta as moments
+// (abs_op: of |A|; base may be NULL); mom: u_bytes of workspace each.
+int run_icd_dots_moments(const umbir_geometry& G, const float* e, bool abs_op, const IcdGroup& gp, int Sr, int Sc,
+                         float* mom, float* partial, hipStream_t s);
+int run_icd_update_moments(const umbir_geometry& G, bool abs_op, const IcdGroup& gp, int Sr, int Sc,
+                           const float* delta, float* mom, const float* base, float* e, hipStream_t s);
 
 // Queues the building of the moment tables (allocated by the caller); the
 // largest number of records of one sample goes to *max_bin, and the tables
@@ -413,7 +418,7 @@ int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s);
 bool moment_plan_fits(int max_bin);
 
 // y = base + sign * A x - g D   (base, g may be NULL; x NULL means all ones).
-// `mom` runs it as moments (never with abs_op, whose |h| is not smooth).
+// `mom` runs it as moments (with abs_op only where abs_moments_on).
 // `abs_op` builds the operator from |W| and |h|.  Trace buffers (out, base) hold
 // the geometry's storage type; fine: G.fine_bytes() of workspace.  With
 // pre_max the workspace already holds tau x for this x (as

@@ -283,8 +283,10 @@ __global__ __launch_bounds__(256) void k_plan_emit(const Leg* __restrict__ legs,
 
 // G_p[k] = sum_t fit[p][t] b[(k + 1) Q - t] (fit: least squares on the Q + 1
 // points, R x (Q + 1) doubles), b evaluated in double.  One wave per k.
+// absolute: then the same for |b|, which is b or -b over a whole cell (the pulse
+// changes sign on the samples only).
 __global__ __launch_bounds__(256) void k_moment_fit(int R, int Q, int Lh, double dt, double f_c, double inv2s2,
-                                                    double t_c, const double* __restrict__ fit,
+                                                    double t_c, const double* __restrict__ fit, int absolute,
                                                     float* __restrict__ g) {
   const int k = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (k >= Lh) return;
@@ -301,7 +303,13 @@ __global__ __launch_bounds__(256) void k_moment_fit(int R, int Q, int Lh, double
 #pragma unroll
   for (int p = 0; p < 8; ++p) {
     for (int off = 32; off > 0; off >>= 1) acc[p] += __shfl_xor(acc[p], off, 64);
-    if (lane == 0 && p < R) g[p * Lh + k] = float(acc[p]);
+    if (lane == 0 && p < R) {
+      g[p * Lh + k] = float(acc[p]);
+      if (absolute) {
+        const bool neg = sin(2.0 * M_PI * f_c * ((k + 0.5) * Q * dt - t_c)) < 0.0;
+        g[(R + p) * Lh + k] = float(neg ? -acc[p] : acc[p]);
+      }
+    }
   }
 }
 
@@ -1477,21 +1485,25 @@ __global__ __launch_bounds__(64 * kMcWaves) void k_mconv_att(const float* __rest
 
 // ---- launches
 
+const uint4* taps_of(const umbir_geometry& G, bool abs_op) {
+  return G.mom_taps + (abs_op ? G.mom.taps_words() : 0);
+}
+
 template <int R, int NTC, int ST>
-void launch_mconv(const umbir_geometry& G, const float* u, const void* base, float sign, const float* g, void* out,
-                  hipStream_t s) {
+void launch_mconv(const umbir_geometry& G, const float* u, const void* base, float sign, const float* g, bool abs_op,
+                  void* out, hipStream_t s) {
   using T = typename Store<ST>::T;
   const dim3 grid(unsigned((G.traces() + 31) / 32), unsigned((G.M + 32 * NTC - 1) / (32 * NTC)));
   UMBIR_LAUNCH("conv", (k_mconv<R, NTC, ST>), grid, dim3(64 * kMcWaves), mconv_lds(R, G.mom.LT, NTC), s, u,
-               G.mom.Ms, G.mom_taps, G.mom.LT, G.M, G.Lh, G.traces(), static_cast<const T*>(base), sign, g, G.dbasis,
+               G.mom.Ms, taps_of(G, abs_op), G.mom.LT, G.M, G.Lh, G.traces(), static_cast<const T*>(base), sign, g, G.dbasis,
                static_cast<T*>(out));
 }
 
 template <int R, int NT>
-void launch_mcorr(const umbir_geometry& G, const float* r, float* v, hipStream_t s) {
+void launch_mcorr(const umbir_geometry& G, const float* r, bool abs_op, float* v, hipStream_t s) {
   const dim3 grid(unsigned((G.traces() + 31) / 32), unsigned((G.mom.Ms / 32 + NT - 1) / NT));
-  UMBIR_LAUNCH("corr", (k_mcorr<R, NT>), grid, dim3(64 * kMcWaves), mcorr_lds(R, G.mom.LT), s, r, G.mom_taps,
-               G.mom.LT, G.M, G.Lh, G.traces(), G.mom.Ms, v);
+  UMBIR_LAUNCH("corr", (k_mcorr<R, NT>), grid, dim3(64 * kMcWaves), mcorr_lds(R, G.mom.LT), s, r,
+               taps_of(G, abs_op), G.mom.LT, G.M, G.Lh, G.traces(), G.mom.Ms, v);
 }
 
 // Calls f(integral_constant R, integral_constant storage).
@@ -1535,6 +1547,8 @@ bool adjoint_moments_on(const umbir_geometry& G) {
 
 bool moments_on(const umbir_geometry& G) { return adjoint_moments_on(G) && G.mom.NG == 1; }
 
+bool abs_moments_on(const umbir_geometry& G) { return moments_on(G) && G.mom.absolute; }
+
 // One scan position reads the image as it is.
 float* moment_image(const umbir_geometry& G, void* fine) {
   return G.P == 1 ? nullptr : phase_image(G, fine);
@@ -1549,7 +1563,7 @@ int run_phase_image(const umbir_geometry& G, const float* x, void* fine, hipStre
 }
 
 int run_forward_moments(const umbir_geometry& G, const float* x, void* out, const void* base, float sign,
-                        const float* g, void* fine, hipStream_t s, bool in_place, const CostFold* fold) {
+                        const float* g, bool abs_op, void* fine, hipStream_t s, bool in_place, const CostFold* fold) {
   int st = UMBIR_OK;
   if (!in_place && (st = run_phase_image(G, x, fine, s))) return st;
   float* u = static_cast<float*>(fine);
@@ -1589,14 +1603,15 @@ int run_forward_moments(const umbir_geometry& G, const float* x, void* out, cons
   with_r(G.mom.R, [&](auto rc) {
     with_tiles(moment_tiles(G), [&](auto nc) {
       with_storage(G.storage, [&](auto sc) {
-        launch_mconv<decltype(rc)::value, decltype(nc)::value, decltype(sc)::value>(G, u, base, sign, g, out, s);
+        launch_mconv<decltype(rc)::value, decltype(nc)::value, decltype(sc)::value>(G, u, base, sign, g, abs_op, out, s);
       });
     });
   });
   return check_hip(hipGetLastError(), "k_mconv");
 }
 
-int run_adjoint_moments(const umbir_geometry& G, const float* r, void* fine, float* partial, hipStream_t s) {
+int run_adjoint_moments(const umbir_geometry& G, const float* r, bool abs_op, void* fine, float* partial,
+                        hipStream_t s) {
   float* v = static_cast<float*>(fine);
   if (G.mom.NG > 1) {
     const MomentShape& ms = G.mom;
@@ -1618,7 +1633,7 @@ int run_adjoint_moments(const umbir_geometry& G, const float* r, void* fine, flo
   }
   with_r(G.mom.R, [&](auto rc) {
     with_tiles(moment_tiles(G), [&](auto nc) {
-      launch_mcorr<decltype(rc)::value, decltype(nc)::value>(G, r, v, s);
+      launch_mcorr<decltype(rc)::value, decltype(nc)::value>(G, r, abs_op, v, s);
     });
   });
   int st = check_hip(hipGetLastError(), "k_mcorr");
@@ -1640,13 +1655,13 @@ int icd_planes(const umbir_geometry& G, size_t bytes_per_value) {
   return int(std::min<size_t>(G.mom.R, std::max<size_t>(1, kIcdMomentLds / (bytes_per_value * G.mom.Ms))));
 }
 
-int run_icd_dots_moments(const umbir_geometry& G, const float* e, const IcdGroup& gp, int Sr, int Sc, float* mom,
-                         float* partial, hipStream_t s) {
+int run_icd_dots_moments(const umbir_geometry& G, const float* e, bool abs_op, const IcdGroup& gp, int Sr, int Sc,
+                         float* mom, float* partial, hipStream_t s) {
   const int planes = icd_planes(G, sizeof(float));
   const int ych = std::max(1, std::min((gp.size + 1023) / 1024, 512 / std::max(G.traces(), 1)));
   with_r(G.mom.R, [&](auto rc) {
     constexpr int R = decltype(rc)::value;
-    with_tiles(moment_tiles(G), [&](auto nc) { launch_mcorr<R, decltype(nc)::value>(G, e, mom, s); });
+    with_tiles(moment_tiles(G), [&](auto nc) { launch_mcorr<R, decltype(nc)::value>(G, e, abs_op, mom, s); });
     UMBIR_LAUNCH("icd_dots", k_icd_mdots<R>, dim3(unsigned(G.traces()), unsigned(ych)), dim3(1024),
                  size_t(planes) * G.mom.Ms * sizeof(float), s, mom, G.mom.Ms, planes, G.legs, G.n_off, G.tau, G.base,
                  G.P, G.K, log2_int(G.Q), G.M, gp, Sr, Sc, partial);
@@ -1654,8 +1669,8 @@ int run_icd_dots_moments(const umbir_geometry& G, const float* e, const IcdGroup
   return check_hip(hipGetLastError(), "icd moment dots");
 }
 
-int run_icd_update_moments(const umbir_geometry& G, const IcdGroup& gp, int Sr, int Sc, const float* delta, float* mom,
-                           float* e, hipStream_t s) {
+int run_icd_update_moments(const umbir_geometry& G, bool abs_op, const IcdGroup& gp, int Sr, int Sc,
+                           const float* delta, float* mom, const float* base, float* e, hipStream_t s) {
   const int planes = icd_planes(G, sizeof(unsigned long long));
   with_r(G.mom.R, [&](auto rc) {
     constexpr int R = decltype(rc)::value;
@@ -1663,7 +1678,7 @@ int run_icd_update_moments(const umbir_geometry& G, const IcdGroup& gp, int Sr, 
                  size_t(planes) * G.mom.Ms * sizeof(unsigned long long), s, mom, G.mom.Ms, planes, G.legs, G.n_off,
                  G.tau, G.base, G.P, G.K, log2_int(G.Q), G.M, gp, Sr, Sc, delta);
     with_tiles(moment_tiles(G), [&](auto nc) {
-      launch_mconv<R, decltype(nc)::value, UMBIR_STORAGE_F32>(G, mom, e, -1.0f, nullptr, e, s);
+      launch_mconv<R, decltype(nc)::value, UMBIR_STORAGE_F32>(G, mom, base, -1.0f, nullptr, abs_op, e, s);
     });
   });
   return check_hip(hipGetLastError(), "icd moment update");
@@ -1775,6 +1790,11 @@ MomentShape moment_shape(const MomentInput& in) {
   if (in.n_gamma == 1 && gather_window_bytes(in.nx, in.nz, long(P) * K, long(in.M) * Q, in.storage) == 0) return ms;
   ms.R = R;
   ms.NG = in.n_gamma;
+  // |A|: the weights are not negative (an even power of the cosine), and the
+  // pulse's sign changes fall on samples
+  const double half = in.fs / (2.0 * in.f_c), mid = tc * in.fs;
+  ms.absolute = in.n_gamma == 1 && in.beta % 2 == 0 && std::fabs(half - std::round(half)) < 1e-9 * half &&
+                std::fabs(mid - std::round(mid)) < 1e-9 * mid;
   ms.Ms = (in.M + 31) & ~31;
   ms.LT = LT;
   ms.pitch = int(pitch);
@@ -1788,7 +1808,7 @@ MomentShape moment_shape(const MomentInput& in) {
   ms.work_bytes = ms.u_bytes + (size_t(in.nz) * ms.pitch * ms.Lq * 4 + 255 & ~size_t(255));
   ms.records = size_t(K) * in.nz * ms.NR;
   ms.table_bytes = ms.records * 4 * (R + 1) + size_t(K) * (size_t(ms.NG) * in.M + 1) * 4 +
-                   size_t(ms.NG) * R * 3 * LT * 16 + (ms.NG > 1 ? size_t(ms.NG) * 8 : 0);
+                   (1 + ms.absolute) * ms.taps_words() * 16 + (ms.NG > 1 ? size_t(ms.NG) * 8 : 0);
   return ms;
 }
 
@@ -1842,7 +1862,8 @@ int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s) {
     }
   const size_t fit_bytes = (fit.size() * sizeof(double) + 255) & ~size_t(255);
   const size_t count_bytes = (n_count * sizeof(int) + 255) & ~size_t(255);
-  const size_t g_bytes = (size_t(ms.NG) * R * G->Lh * sizeof(float) + 255) & ~size_t(255);
+  const int g_rows = ms.NG * R * (1 + ms.absolute);
+  const size_t g_bytes = (size_t(g_rows) * G->Lh * sizeof(float) + 255) & ~size_t(255);
   char* tmp = nullptr;
   int st = check_hip(hipMallocAsync(reinterpret_cast<void**>(&tmp),
                                     fit_bytes + 256 + g_bytes + count_bytes + ms.records * sizeof(unsigned), s),
@@ -1864,10 +1885,10 @@ int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s) {
                    G->Lh, G->bank, fit_dev, g);
     else
       UMBIR_LAUNCH("moment_fit", k_moment_fit, dim3(unsigned((G->Lh + 3) / 4)), dim3(256), 0, s, R, Q, G->Lh,
-                   1.0 / (double(Q) * G->fs), G->f_c, 1.0 / (2.0 * G->sigma_t * G->sigma_t), 0.5 * G->t_win, fit_dev, g);
-    // (the templates' rows follow one another in g and in the table)
-    UMBIR_LAUNCH("moment_table", k_moment_table, dim3(unsigned((ms.NG * R * ms.LT + 255) / 256)), dim3(256), 0, s,
-                 ms.NG * R, G->Lh, ms.LT, g, G->mom_taps);
+                   1.0 / (double(Q) * G->fs), G->f_c, 1.0 / (2.0 * G->sigma_t * G->sigma_t), 0.5 * G->t_win, fit_dev, ms.absolute, g);
+    // (the templates' rows, and those of |b|, follow one another in g and in the table)
+    UMBIR_LAUNCH("moment_table", k_moment_table, dim3(unsigned((g_rows * ms.LT + 255) / 256)), dim3(256), 0, s,
+                 g_rows, G->Lh, ms.LT, g, G->mom_taps);
     UMBIR_LAUNCH("plan_count", k_plan_count, cg, dim3(256), lds, s, G->legs, G->gunit, G->base, ms, G->P, K, G->nz,
                  G->n_off, M, counts);
     UMBIR_LAUNCH("plan_scan", k_plan_scan, dim3(unsigned(K)), dim3(1024), 0, s, NB, chunks, cap, counts, G->mom_start,

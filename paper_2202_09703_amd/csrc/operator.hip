@@ -2586,7 +2586,7 @@ int run_prescale_blocks(const umbir_geometry& G, const float* x, void* fine, uns
 int run_forward(const umbir_geometry& G, const float* x, void* out, const void* base, float sign,
                 const float* g, bool abs_op, bool mom, void* fine, hipStream_t s, const unsigned* pre_max,
                 int n_pre_max, const CostFold* fold) {
-  if (mom) return run_forward_moments(G, x, out, base, sign, g, fine, s, pre_max != nullptr, fold);
+  if (mom) return run_forward_moments(G, x, out, base, sign, g, abs_op, fine, s, pre_max != nullptr, fold);
   // after the fine grid(s): the prescaled image tau x, then one 32-bit
   // scalar, the largest |tau x|
   float* xt = reinterpret_cast<float*>(static_cast<char*>(fine) + G.grids_bytes());
@@ -2687,7 +2687,7 @@ int run_forward(const umbir_geometry& G, const float* x, void* out, const void* 
 
 int run_adjoint_partial(const umbir_geometry& G, const void* r, bool abs_op, bool mom, void* fine, float* partial,
                         hipStream_t s) {
-  if (mom) return run_adjoint_moments(G, static_cast<const float*>(r), fine, partial, s);
+  if (mom) return run_adjoint_moments(G, static_cast<const float*>(r), abs_op, fine, partial, s);
   const int MQ = int(G.fine_per_trace());
   const int qs = log2_int(G.Q);
   const int tpg = (G.traces() + G.trace_groups - 1) / G.trace_groups;
@@ -2869,8 +2869,9 @@ int umbir_sqs_denominator(const umbir_geometry* G, double sigma, float* d, void*
   void* fine = cv.take<char>(G->fine_bytes());
   float* partial = cv.take<float>(size_t(G->trace_groups) * G->voxels());
   void* col = cv.take<char>(G->trace_bytes());
-  if ((st = run_forward(*G, nullptr, col, nullptr, 1.0f, nullptr, true, false, fine, s))) return st;
-  return run_adjoint(*G, col, d, float(1.0 / (sigma * sigma)), true, false, fine, partial, s);
+  const bool mom = abs_moments_on(*G);
+  if ((st = run_forward(*G, nullptr, col, nullptr, 1.0f, nullptr, true, mom, fine, s))) return st;
+  return run_adjoint(*G, col, d, float(1.0 / (sigma * sigma)), true, mom, fine, partial, s);
 }
 
 int umbir_autotune(umbir_geometry* G, void* stream, umbir_tuning* chosen) {

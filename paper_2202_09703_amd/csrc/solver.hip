@@ -431,9 +431,10 @@ size_t iter_bytes(const umbir_geometry& G) {
 }
 
 int enqueue_curvature(const umbir_geometry& G, const IterBuffers& b, const PriorConst& pc, hipStream_t s) {
-  int st = run_forward(G, nullptr, b.e, nullptr, 1.0f, nullptr, true, false, b.fine, s);
+  const bool mom = b.mom && G.mom.absolute;
+  int st = run_forward(G, nullptr, b.e, nullptr, 1.0f, nullptr, true, mom, b.fine, s);
   if (st) return st;
-  return run_adjoint(G, b.e, b.den, pc.inv_sigma2, true, false, b.fine, b.partial, s);
+  return run_adjoint(G, b.e, b.den, pc.inv_sigma2, true, mom, b.fine, b.partial, s);
 }
 
 // One surrogate iteration from x_in to x_out (or, with last, only the cost of
@@ -1229,8 +1230,8 @@ int umbir_reconstruct_icd(const umbir_geometry* G, const umbir_prior* pr, const 
   // us with 1024 members at 256 x 256 voxels, 512 traces of 2048 samples (70
   // against 66 with 441, 117 against 374 with 4096), 42 against 62 us with 1024
   // at 128 x 128, 128 traces (39 against 38 with 441), 33 against 38 us with
-  // 1024 at 64 x 64, 8 traces (30 against 25 with 441).  The curvatures stay:
-  // |b| is no polynomial where the pulse changes sign.
+  // 1024 at 64 x 64, 8 traces (30 against 25 with 441).  The curvatures
+  // likewise, where |A| has moments.
   const bool mom = moments_on(*G) && gmax >= 768;
 
   const size_t lds_dots = (size_t(M) + QLh + 2) * sizeof(float);
@@ -1263,10 +1264,18 @@ int umbir_reconstruct_icd(const umbir_geometry* G, const umbir_prior* pr, const 
   for (int k = 0; k < n_groups; ++k) {
     const IcdGroup gp = icd_group(*G, Sr, Sc, k);
     if (gp.size == 0) continue;
-    if ((st = launch_fill(etmp, size_t(PK) * M, 0.0f, s))) return st;
-    UMBIR_LAUNCH("icd_unit", k_icd_unit, dim3(unsigned((gp.size + 255) / 256)), dim3(256), 0, s, gp.size, delta);
-    scatter(true, gp, etmp);
-    dots(true, gp, etmp);
+    if (mom && G->mom.absolute) {
+      float* mv = static_cast<float*>(fine);
+      UMBIR_LAUNCH("icd_unit", k_icd_unit, dim3(unsigned((gp.size + 255) / 256)), dim3(256), 0, s, gp.size, delta);
+      if ((st = run_icd_update_moments(*G, true, gp, Sr, Sc, delta, mv, nullptr, etmp, s)) ||
+          (st = run_icd_dots_moments(*G, etmp, true, gp, Sr, Sc, mv, part, s)))
+        return st;
+    } else {
+      if ((st = launch_fill(etmp, size_t(PK) * M, 0.0f, s))) return st;
+      UMBIR_LAUNCH("icd_unit", k_icd_unit, dim3(unsigned((gp.size + 255) / 256)), dim3(256), 0, s, gp.size, delta);
+      scatter(true, gp, etmp);
+      dots(true, gp, etmp);
+    }
     UMBIR_LAUNCH("icd_step", k_icd_step<true>, sgrid(gp), sblk, 0, s, part, PK, gp, Sr, Sc, G->nx, G->nz, pc,
                  ms_row, den, nullptr, nullptr);
   }
@@ -1287,14 +1296,14 @@ int umbir_reconstruct_icd(const umbir_geometry* G, const umbir_prior* pr, const 
       const IcdGroup gp = icd_group(*G, Sr, Sc, k);
       if (gp.size == 0) continue;
       if (mom) {
-        if ((st = run_icd_dots_moments(*G, e, gp, Sr, Sc, static_cast<float*>(fine), part, s))) return st;
+        if ((st = run_icd_dots_moments(*G, e, false, gp, Sr, Sc, static_cast<float*>(fine), part, s))) return st;
       } else {
         dots(false, gp, e);
       }
       UMBIR_LAUNCH("icd_step", k_icd_step<false>, sgrid(gp), sblk, 0, s, part, PK, gp, Sr, Sc, G->nx, G->nz, pc,
                    ms_row, den, x_io, delta);
       if (mom) {
-        if ((st = run_icd_update_moments(*G, gp, Sr, Sc, delta, static_cast<float*>(fine), e, s))) return st;
+        if ((st = run_icd_update_moments(*G, false, gp, Sr, Sc, delta, static_cast<float*>(fine), e, e, s))) return st;
       } else {
         scatter(false, gp, e);
       }

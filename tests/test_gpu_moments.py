@@ -96,6 +96,28 @@ def test_moments_match_oracle_and_fine_grid(dev, name):
     geom.free()
 
 
+@pytest.mark.parametrize("kw, on", [
+    (CASES["one-scan-r5"], True), (CASES["reversed"], True), (CASES["two-chunks"], True), (CASES["r8"], True),
+    (CASES["short-record"], True),
+    (dict(CASES["reversed"], f_c=0.45), False),  # 22.2 samples between the pulse's zeros
+])
+def test_curvature_as_moments(dev, kw, on):
+    """The curvature |A|^T |A| 1 runs as moments where the pulse's zeros fall on
+    samples; elsewhere |b| has kinks inside a sample and the fine grid serves."""
+    c = card(**kw)
+    geom = umbir.build_geometry(c)
+    d = umbir.sqs_denominator(geom, 0.5)
+    if on:
+        geom.set_tuning(products=1)
+        assert not torch.equal(d, umbir.sqs_denominator(geom, 0.5))
+    ref = oo.adjoint(c, oo.forward(c, np.ones((c.grid.nz, c.grid.nx)), b=oo.default_bank(c, True), weight_abs=True),
+                     b=oo.default_bank(c, True), weight_abs=True) / 0.25
+    e = rel(d.cpu(), ref)
+    print("curvature rel L2 %.2e" % e)
+    assert e <= TOL
+    geom.free()
+
+
 @pytest.mark.parametrize("scale, lo, hi", [(3, 2048, 4096), (5, 3500, 4800), (8, 5600, 7700)])
 def test_long_gather_windows(dev, scale, lo, hi):
     """Voxels of 3, 5 and 8 mm under a slow top layer: the top tiles' windows
