@@ -1314,13 +1314,16 @@ __global__ __launch_bounds__(1024) void k_icd_mdots(const float* __restrict__ v,
   extern __shared__ __align__(16) float sm[];  // [planes][Ms]
   const int t = blockIdx.x;
   const float* vt = v + size_t(t) * R * Ms;
-  for (int k = threadIdx.x; k < planes * Ms / 4; k += blockDim.x)
-    reinterpret_cast<float4*>(sm)[k] = reinterpret_cast<const float4*>(vt)[k];
   const int bt = base[t / K], br = base[P + t];
   const float h = 2.0f / float(1 << qs);
+  const int i0 = blockIdx.y * blockDim.x + threadIdx.x;
+  // the first member's legs arrive while v is staged
+  IcdMember mb = icd_moment_member(legs, n_off, tau, bt, br, gp, Sr, Sc, qs, min(i0, gp.size - 1));
+  stage_block<float4>(planes * Ms / 4, [&](int k) { return reinterpret_cast<const float4*>(vt)[k]; },
+                      [&](int k, const float4& x) { reinterpret_cast<float4*>(sm)[k] = x; });
   __syncthreads();
-  for (int i = blockIdx.y * blockDim.x + threadIdx.x; i < gp.size; i += gridDim.y * blockDim.x) {
-    const IcdMember mb = icd_moment_member(legs, n_off, tau, bt, br, gp, Sr, Sc, qs, i);
+  for (int i = i0; i < gp.size; i += gridDim.y * blockDim.x) {
+    if (i != i0) mb = icd_moment_member(legs, n_off, tau, bt, br, gp, Sr, Sc, qs, i);
     float f0 = 0.0f, f1 = 0.0f;
     if (mb.n < unsigned(M)) {
       const float z1 = mb.z0 + h;
@@ -1346,29 +1349,32 @@ __global__ __launch_bounds__(1024) void k_icd_msplat(float* __restrict__ u, int 
                                                      const float* __restrict__ delta) {
   extern __shared__ __align__(16) unsigned long long sums[];  // [planes][Ms]
   __shared__ float wmax[16];
-  const int t = blockIdx.x;
-  float mx = 0.0f;
-  for (int i = threadIdx.x; i < gp.size; i += blockDim.x) mx = fmaxf(mx, fabsf(delta[i]));
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-  if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = mx;
-  __syncthreads();
-  float dmax = 0.0f;
-  for (int k = 0; k < int(blockDim.x >> 6); ++k) dmax = fmaxf(dmax, wmax[k]);
-  int lg = 0;
-  while ((1 << lg) < gp.size) ++lg;
-  const int kx = dmax > 0.0f ? 61 - lg - ilogbf(dmax) : 0;
-  const double scale = ldexp(1.0, kx);
+  const int t = blockIdx.x, tid = int(threadIdx.x);
   const int bt = base[t / K], br = base[P + t];
   const float h = 2.0f / float(1 << qs);
+  // the first member's step and legs arrive while the sums are cleared
+  const float dl0 = tid < gp.size ? delta[tid] : 0.0f;
+  const IcdMember mb0 = icd_moment_member(legs, n_off, tau, bt, br, gp, Sr, Sc, qs, min(tid, gp.size - 1));
+  float mx = fabsf(dl0);
+  for (int i = tid + int(blockDim.x); i < gp.size; i += blockDim.x) mx = fmaxf(mx, fabsf(delta[i]));
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+  if ((tid & 63) == 0) wmax[tid >> 6] = mx;
+  ulonglong2* sums2 = reinterpret_cast<ulonglong2*>(sums);
   float* ut = u + size_t(t) * R * Ms;
   for (int p0 = 0; p0 < R; p0 += planes) {
     const int np = min(planes, R - p0);
-    for (int k = threadIdx.x; k < np * Ms; k += blockDim.x) sums[k] = 0ull;
+    for (int k = tid; k < np * Ms / 2; k += blockDim.x) sums2[k] = make_ulonglong2(0ull, 0ull);
     __syncthreads();
-    for (int i = threadIdx.x; i < gp.size; i += blockDim.x) {
-      const float dl = delta[i];
+    float dmax = 0.0f;
+    for (int k = 0; k < int(blockDim.x >> 6); ++k) dmax = fmaxf(dmax, wmax[k]);
+    int lg = 0;
+    while ((1 << lg) < gp.size) ++lg;
+    const int kx = dmax > 0.0f ? 61 - lg - ilogbf(dmax) : 0;
+    const double scale = ldexp(1.0, kx), back = ldexp(1.0, -kx);
+    for (int i = tid; i < gp.size; i += blockDim.x) {
+      const float dl = i == tid ? dl0 : delta[i];
       if (dl == 0.0f) continue;
-      const IcdMember mb = icd_moment_member(legs, n_off, tau, bt, br, gp, Sr, Sc, qs, i);
+      const IcdMember mb = i == tid ? mb0 : icd_moment_member(legs, n_off, tau, bt, br, gp, Sr, Sc, qs, i);
       if (mb.n >= unsigned(M)) continue;
       const float z1 = mb.z0 + h;
       float a1 = dl * mb.w * mb.phi, a0 = dl * mb.w * (1.0f - mb.phi);
@@ -1382,8 +1388,11 @@ __global__ __launch_bounds__(1024) void k_icd_msplat(float* __restrict__ u, int 
       }
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < np * Ms; k += blockDim.x)
-      ut[size_t(p0) * Ms + k] = float(ldexp(double(static_cast<long long>(sums[k])), -kx));
+    for (int k = tid; k < np * Ms / 4; k += blockDim.x) {
+      const ulonglong2 x = sums2[2 * k], y = sums2[2 * k + 1];
+      auto value = [&](unsigned long long s) { return float(double(static_cast<long long>(s)) * back); };
+      reinterpret_cast<float4*>(ut + size_t(p0) * Ms)[k] = make_float4(value(x.x), value(x.y), value(y.x), value(y.y));
+    }
     __syncthreads();
   }
 }
