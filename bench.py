@@ -74,6 +74,7 @@ def traffic_from(fetch_csv, write_csv, copy_fetch_csv, copy_write_csv):
             # as "conv", k_corr_mfma / k_corr_x3 as "corr", k_gather_lds as
             # "gather"
             name = re.sub(r"_(mfma(16)?|x3|lds)$", "", m.group(1))
+            name = re.sub(r"^m(splat|conv|corr|gather)$", r"\1", name)  # the moment form's
             n, v = acc.setdefault(name, [0, 0.0]), float(row["Counter_Value"])
             n[0] += 1
             n[1] += v

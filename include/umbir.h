@@ -344,7 +344,8 @@ int umbir_get_dims(const umbir_geometry* geom, umbir_dims* out);
  * storage, one template, scan positions a constant whole number of voxels
  * apart, Q >= 16 and a pulse that a polynomial of degree 7 or less follows over
  * a sample period to 1e-8 of its peak), the launch and tile shapes and the
- * gather's form concern the curvature pass only:
+ * gather's form concern only the curvature of a pulse whose zeros fall between
+ * samples; with attenuation, what is not a forward or an adjoint alone:
  *  splat_blocks     target workgroup count of the splat: the fine grid of each
  *                   trace is cut into ceil(splat_blocks / traces) chunks of at
  *                   least 1024 positions.  Results are bitwise identical for

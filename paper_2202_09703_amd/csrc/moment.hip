@@ -31,6 +31,13 @@
 // for all scan positions is then a sum over its records of coefficients times
 // consecutive elements of the image (stored by phase of the pitch), in
 // registers: no atomics, and a fixed order of the sums.
+//
+// With attenuation every pair belongs to one of NG templates; a forward or an
+// adjoint alone runs with u and v per template (R = 8: six moments and the two
+// ends of the window, see k_template_fit), the records sorted by (template,
+// sample).  |A| has tables of its own where |b| is b or -b over every cell.
+// Grouped ICD's large groups use C and C^T as they are, with a splat and a
+// gather over the group's members.
 
 #include <algorithm>
 #include <cmath>
@@ -556,7 +563,7 @@ __global__ __launch_bounds__(64 * kMsWaves) void k_msplat(const float* __restric
 // attenuation.  The fine-grid form fills one dense grid per template: 512
 // traces of 65536 positions in 16 templates are 2.1 GB, and writing and reading
 // them took 1158 and 1328 us at 256 x 256; u (0.5 GB at most, the spans' share
-// of it) takes 137 and 275 us.
+// of it) takes 139 and 257 us.
 __global__ __launch_bounds__(64 * kMsWaves) void k_msplat_att(const float* __restrict__ xp, int xp_bytes,
                                                               const int* __restrict__ start,
                                                               const float4* __restrict__ rec4,
@@ -1583,7 +1590,11 @@ int run_forward_moments(const umbir_geometry& G, const float* x, void* out, cons
     const dim3 grid(unsigned(G.K), unsigned(ms.Ms / kMsBins), unsigned((G.P + 63) / 64 * ms.NG));
     UMBIR_LAUNCH("splat", k_msplat_att, grid, dim3(64 * kMsWaves), msplat_lds<8>(ms.ls), s, xp, xp_bytes, G.mom_start,
                  G.mom_rec4, G.mom_rec_hi, G.P, G.K, G.M, ms, G.mom_span, u);
-    with_tiles(moment_tiles(G), [&](auto nc) {
+    // tiles differ in how many templates reach them: four to a block only from two
+    // blocks per CU on (at one per CU 276 us, with two tiles to a block 257)
+    const long tt = (G.traces() + 31) / 32;
+    const int tiles = moment_tiles(G) == 4 && tt * ((G.M + 127) / 128) < 512 ? 2 : moment_tiles(G);
+    with_tiles(tiles, [&](auto nc) {
       constexpr int NTC = decltype(nc)::value;
       const dim3 cgrid(unsigned((G.traces() + 31) / 32), unsigned((G.M + 32 * NTC - 1) / (32 * NTC)));
       UMBIR_LAUNCH("conv", (k_mconv_att<NTC>), cgrid, dim3(64 * kMcWaves), mconv_lds(8, ms.LT, NTC), s, u, ms.Ms,
@@ -1756,9 +1767,9 @@ static double fit_remainder(double f_c, double sigma_t, double half_width, int R
 MomentShape moment_shape(const MomentInput& in) {
   MomentShape ms;
   const int Q = in.Q;
-  // the dense part pays from Q >= 2 R on; longer records than the plan's LDS
-  // histograms keep the fine grid
-  if (Q < 16 || in.M > 16384 || long(in.M) * in.n_gamma > 262140) return ms;  // (plan_emit's grid)
+  // the dense part pays from Q >= 2 R on; longer records, or more bins than the
+  // plan's grid holds, keep the fine grid
+  if (Q < 16 || in.M > 16384 || long(in.M) * in.n_gamma > 262140) return ms;
   // the window must end where the pulse is (numerically) zero: the table's
   // forced zeros at its ends are then no step
   const double tc = 0.5 * in.t_win;
