@@ -966,9 +966,9 @@ __global__ __launch_bounds__(64 * kMcWaves) void k_mcorr_att(const float* __rest
 // from memory paced the whole launch, 1345 us against 1088 us staged.  A
 // block's tiles lie a whole generation of blocks apart, so that no block has
 // two of them: 927 us.  (Tiles that stop at layers' faces instead: 1160 us, and
-// 12 % more of them.)  Bound by its vector instructions (38 per wave and
-// trace-voxel, 56 % of the cycles at 256 x 256), the load unit (55 %) and LDS
-// (35 %), which the barrier of each trace keeps from overlapping fully.
+// 12 % more of them.)  Bound by its vector instructions (34 per wave and
+// trace-voxel, 54 % of the cycles at 256 x 256), the load unit (65 %) and LDS
+// (36 %), which the barrier of each trace keeps from overlapping fully.
 // Sharing a record between voxels a pitch apart, four traces a barrier and
 // windows dealt to the waves piece by piece halved single shares of these but
 // not the time (57 .. 95 us against 57 at 256 x 256, 910 .. 1440 at 512 x 512).
