@@ -581,7 +581,7 @@ void umbir_geometry_free(umbir_geometry* G) {
   (void)hipGetDevice(&cur);
   if (G->device >= 0) (void)hipSetDevice(G->device);
   void* ptrs[] = {G->legs, G->legs_t, G->tau, G->base, G->bank, G->h, G->habs, G->dbasis, G->dnorm, G->gmask,
-                  G->gunit, G->gunit_t, G->gwin, G->mom_start, G->mom_rec4, G->mom_rec_hi, G->mom_taps, G->mom_span};
+                  G->gunit, G->gunit_t, G->gwin, G->mom_rec4};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (cur >= 0) (void)hipSetDevice(cur);
@@ -836,12 +836,14 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
   int max_bin = 0;
   if (G->mom.R) {
     const MomentShape& ms = G->mom;
-    if ((st = alloc((void**)&G->mom_start, size_t(G->K) * (size_t(ms.NG) * G->M + 1) * sizeof(int))) ||
-        (st = alloc((void**)&G->mom_rec4, ms.records * sizeof(float4))) ||
-        (st = alloc((void**)&G->mom_rec_hi, ms.records * (ms.R - 3) * sizeof(float))) ||
-        (st = alloc((void**)&G->mom_taps, (1 + ms.absolute) * ms.taps_words() * sizeof(uint4))) ||
-        (ms.NG > 1 && (st = alloc((void**)&G->mom_span, size_t(ms.NG) * sizeof(int2)))) ||
-        (st = build_moments(G, &max_bin, s)))
+    char* t = nullptr;
+    if ((st = alloc((void**)&t, ms.table_bytes))) return bail(st);
+    G->mom_rec4 = reinterpret_cast<float4*>(t);
+    G->mom_rec_hi = reinterpret_cast<float*>(t + ms.hi_at);
+    G->mom_taps = reinterpret_cast<uint4*>(t + ms.taps_at);
+    G->mom_start = reinterpret_cast<int*>(t + ms.start_at);
+    G->mom_span = reinterpret_cast<int2*>(t + ms.span_at);
+    if ((st = build_moments(G, &max_bin, s)))
       return bail(st);
   }
   if (gam_dev) (void)hipFreeAsync(gam_dev, s);
@@ -852,13 +854,11 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
   if (!st) st = st2;
   if (!st && !moment_plan_fits(max_bin)) {  // the fine grid stays
     G->bytes -= G->mom.table_bytes;
-    void* tables[] = {G->mom_start, G->mom_rec4, G->mom_rec_hi, G->mom_taps, G->mom_span};
-    for (void* p : tables)
-      if (p) (void)hipFree(p);
-    G->mom_start = nullptr;
+    (void)hipFree(G->mom_rec4);
     G->mom_rec4 = nullptr;
     G->mom_rec_hi = nullptr;
     G->mom_taps = nullptr;
+    G->mom_start = nullptr;
     G->mom_span = nullptr;
     G->mom = MomentShape{};
   }

@@ -181,6 +181,7 @@ struct MomentShape {
   int pitch = 0, Lq = 0, NR = 0, rel0 = 0, ls = 0, reversed = 0;
   size_t taps_words() const { return size_t(NG) * R * 3 * LT; }
   size_t u_bytes = 0, work_bytes = 0, records = 0, table_bytes = 0;
+  size_t hi_at = 0, taps_at = 0, start_at = 0, span_at = 0;  // where the tables after rec4 begin
 };
 
 // What decides it.
@@ -279,7 +280,7 @@ struct umbir_geometry {
   // receiver, where each sample's begin, and the dense kernels' table
   umbir::MomentShape mom;
   int* mom_start = nullptr;         // [K][NG M + 1]
-  float4* mom_rec4 = nullptr;       // [records] coefficients 0 .. 3
+  float4* mom_rec4 = nullptr;       // [records] coefficients 0 .. 3; the others follow in its allocation
   float* mom_rec_hi = nullptr;      // [records][R - 3] the others, then the byte offset in the image by phase
   uint4* mom_taps = nullptr;        // [NG][R][3][LT], with mom.absolute then those of |b|
   int2* mom_span = nullptr;         // [NG] first sample with a record and the one past the last (attenuation)

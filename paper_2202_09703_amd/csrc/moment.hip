@@ -104,7 +104,7 @@ constexpr int kPlanSlice = 36864;
 
 // counts[j][chunk][b]: records of receiver j and the chunk's relative columns
 // in bin b (of NB = NG M).
-__global__ __launch_bounds__(256) void k_plan_count(const Leg* __restrict__ legs, const double* __restrict__ gunit,
+__global__ __launch_bounds__(1024) void k_plan_count(const Leg* __restrict__ legs, const double* __restrict__ gunit,
                                                     const int* __restrict__ base, MomentShape ms, int P, int K, int nz,
                                                     int n_off, int M, int* __restrict__ counts) {
   extern __shared__ int hist[];
@@ -140,7 +140,13 @@ __global__ __launch_bounds__(1024) void k_plan_scan(int M, int chunks, int cap, 
     const int n = n0 + t;
     int c = 0;
     if (n < M)
-      for (int k = 0; k < chunks; ++k) c += cj[size_t(k) * M + n];
+      for (int k0 = 0; k0 < chunks; k0 += 8) {
+        int v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = cj[size_t(min(k0 + k, chunks - 1)) * M + n];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) c += k0 + k < chunks ? v[k] : 0;
+      }
     big = max(big, c);
     int before = c;  // inclusive over the wave, then exclusive over the block
     for (int off = 1; off < 64; off <<= 1) {
@@ -159,10 +165,16 @@ __global__ __launch_bounds__(1024) void k_plan_scan(int M, int chunks, int cap, 
     if (n < M) {
       int p = at + before;
       start[size_t(j) * (M + 1) + n] = p;
-      for (int k = 0; k < chunks; ++k) {
-        const int v = cj[size_t(k) * M + n];
-        cj[size_t(k) * M + n] = p;
-        p += v;
+      for (int k0 = 0; k0 < chunks; k0 += 8) {
+        int v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = cj[size_t(min(k0 + k, chunks - 1)) * M + n];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          if (k0 + k >= chunks) break;
+          cj[size_t(k0 + k) * M + n] = p;
+          p += v[k];
+        }
       }
     }
     at += total;
@@ -172,7 +184,7 @@ __global__ __launch_bounds__(1024) void k_plan_scan(int M, int chunks, int cap, 
 }
 
 // Keys row * NR + (rel - rel0) of every record into its bin, in any order.
-__global__ __launch_bounds__(256) void k_plan_fill(const Leg* __restrict__ legs, const double* __restrict__ gunit,
+__global__ __launch_bounds__(1024) void k_plan_fill(const Leg* __restrict__ legs, const double* __restrict__ gunit,
                                                    const int* __restrict__ base, MomentShape ms, int P, int K, int nz,
                                                    int n_off, int M, const int* __restrict__ first,
                                                    unsigned* __restrict__ keys) {
@@ -357,8 +369,9 @@ __global__ __launch_bounds__(256) void k_template_fit(int Q, int Lh, const float
 // values G_p[D], G_p[D - 1], ..., G_p[D - 7] (zero outside [0, Lh)) split into
 // three bf16 pieces.
 __global__ __launch_bounds__(256) void k_moment_table(int R, int Lh, int LT, const float* __restrict__ g,
-                                                      uint4* __restrict__ F) {
+                                                      uint4* __restrict__ F, int* __restrict__ max_bin) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) *max_bin = 0;  // for k_plan_scan
   if (i >= R * LT) return;
   const int p = i / LT, D = i - p * LT - 1;
   float v[8];
@@ -1827,8 +1840,17 @@ MomentShape moment_shape(const MomentInput& in) {
   // the image by phase, and the lanes past the last scan position of it
   ms.work_bytes = ms.u_bytes + (size_t(in.nz) * ms.pitch * ms.Lq * 4 + 255 & ~size_t(255));
   ms.records = size_t(K) * in.nz * ms.NR;
-  ms.table_bytes = ms.records * 4 * (R + 1) + size_t(K) * (size_t(ms.NG) * in.M + 1) * 4 +
-                   (1 + ms.absolute) * ms.taps_words() * 16 + (ms.NG > 1 ? size_t(ms.NG) * 8 : 0);
+  // one allocation: rec4, rec_hi, taps, start, span
+  auto place = [&](size_t bytes) {
+    const size_t at = ms.table_bytes;
+    ms.table_bytes += (bytes + 255) & ~size_t(255);
+    return at;
+  };
+  (void)place(ms.records * sizeof(float4));
+  ms.hi_at = place(ms.records * (R - 3) * sizeof(float));
+  ms.taps_at = place((1 + ms.absolute) * ms.taps_words() * sizeof(uint4));
+  ms.start_at = place(size_t(K) * (size_t(ms.NG) * in.M + 1) * sizeof(int));
+  ms.span_at = place(size_t(ms.NG) * sizeof(int2));
   return ms;
 }
 
@@ -1898,8 +1920,7 @@ int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s) {
   const size_t lds = size_t(std::min(NB, kPlanSlice)) * sizeof(int);
   const dim3 cg{unsigned(K), unsigned(chunks), unsigned((NB + kPlanSlice - 1) / kPlanSlice)};
   if (!(st = check_hip(hipMemcpyAsync(fit_dev, fit.data(), fit.size() * sizeof(double), hipMemcpyHostToDevice, s),
-                       "hipMemcpyAsync(fit)")) &&
-      !(st = check_hip(hipMemsetAsync(mb, 0, sizeof(int), s), "hipMemsetAsync(plan)"))) {
+                       "hipMemcpyAsync(fit)"))) {
     if (ms.NG > 1)
       UMBIR_LAUNCH("moment_fit", k_template_fit, dim3(unsigned((G->Lh + 3) / 4), unsigned(ms.NG)), dim3(256), 0, s, Q,
                    G->Lh, G->bank, fit_dev, g);
@@ -1908,14 +1929,14 @@ int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s) {
                    1.0 / (double(Q) * G->fs), G->f_c, 1.0 / (2.0 * G->sigma_t * G->sigma_t), 0.5 * G->t_win, fit_dev, ms.absolute, g);
     // (the templates' rows, and those of |b|, follow one another in g and in the table)
     UMBIR_LAUNCH("moment_table", k_moment_table, dim3(unsigned((g_rows * ms.LT + 255) / 256)), dim3(256), 0, s,
-                 g_rows, G->Lh, ms.LT, g, G->mom_taps);
-    UMBIR_LAUNCH("plan_count", k_plan_count, cg, dim3(256), lds, s, G->legs, G->gunit, G->base, ms, G->P, K, G->nz,
+                 g_rows, G->Lh, ms.LT, g, G->mom_taps, mb);
+    UMBIR_LAUNCH("plan_count", k_plan_count, cg, dim3(1024), lds, s, G->legs, G->gunit, G->base, ms, G->P, K, G->nz,
                  G->n_off, M, counts);
     UMBIR_LAUNCH("plan_scan", k_plan_scan, dim3(unsigned(K)), dim3(1024), 0, s, NB, chunks, cap, counts, G->mom_start,
                  mb);
     if (ms.NG > 1)
       UMBIR_LAUNCH("plan_span", k_plan_span, dim3(unsigned(ms.NG)), dim3(256), 0, s, G->mom_start, K, M, NB, G->mom_span);
-    UMBIR_LAUNCH("plan_fill", k_plan_fill, cg, dim3(256), lds, s, G->legs, G->gunit, G->base, ms, G->P, K, G->nz,
+    UMBIR_LAUNCH("plan_fill", k_plan_fill, cg, dim3(512), lds, s, G->legs, G->gunit, G->base, ms, G->P, K, G->nz,
                  G->n_off, M, counts, keys);
     with_r(R, [&](auto rc) {
       UMBIR_LAUNCH("plan_emit", k_plan_emit<decltype(rc)::value>, dim3(unsigned(K), unsigned((NB + 3) / 4)), dim3(256),
