@@ -30,6 +30,15 @@ thread_local std::string g_last_error;
 
 constexpr int kBisectSteps = 60;
 
+// Depth of a row's centre, rounded twice on the host and on the device: a
+// contracted multiply-add on one side only would put a centre that lies exactly
+// on an interface into different layers there, and the layer segments
+// (host) would then join rows whose delays (device) do not grow with depth.
+__host__ __device__ inline double row_depth(double z0, double dz, int row) {
+#pragma clang fp contract(off)
+  return z0 + (row + 0.5) * dz;
+}
+
 // One leg per thread: the Snell ray parameter kappa = sin(theta_l) / c_l by
 // bisection on the lateral offset it reaches (Eqs. (5)-(6)), then the travel
 // time (Eq. (4)), cos^beta of the angle sum (Eq. (12)) and, when `gam` is not
@@ -44,7 +53,7 @@ __global__ void k_legs(Layers L, int nz, int n_off, double z0, double dz, double
   const int slot = idx - row * n_off;
   const int half = n_off / 2;
   const int o = slot < half ? 2 * slot : 2 * (slot - half) + 1;
-  const double z = z0 + (row + 0.5) * dz;
+  const double z = row_depth(z0, dz, row);
   const double X = o * half_dx;
   double eta[kMaxLayers];
   double cmax = 0.0;
@@ -639,7 +648,7 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
     // lies above its centre (the legs' crossing extents use the same rule)
     int prev = -1;
     for (int r = 0; r < G->nz; ++r) {
-      const double z = G->z0 + (r + 0.5) * G->dz;
+      const double z = row_depth(G->z0, G->dz, r);
       int l = 0;
       while (l + 1 < G->layers.n && z > G->layers.top[l + 1]) ++l;
       if (l != prev) {
@@ -688,7 +697,7 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
   // both ways at normal incidence, Z = rho c; layer 0 has tau = 1.
   std::vector<float> tau(G->nz);
   for (int r = 0; r < G->nz; ++r) {
-    const double z = G->z0 + (r + 0.5) * G->dz;
+    const double z = row_depth(G->z0, G->dz, r);
     double t = 1.0;
     for (int l = 0; l + 1 < G->layers.n; ++l) {
       if (z > G->layers.bottom[l]) {

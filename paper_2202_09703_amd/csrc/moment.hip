@@ -1124,19 +1124,22 @@ __device__ __forceinline__ void mgather_body(int bx, int by, const float* __rest
     auto add = [&](const Legs& L, int2 W, int t, const float* buf, int plane) {
       if (W.y == 0) return;
       const bool fits = W.y <= plane;
-      const float* vt = v + size_t(t) * R * Ms;
+      const float* vt = v + size_t(t) * R * Ms + W.x;
+      // the window's samples of the record: it holds every voxel of the tile
+      // in the record, and bounds each index here
+      const unsigned cnt = unsigned(min(W.y, M - W.x));
 #pragma unroll
       for (int q = 0; q < VPT; ++q) {
         const uint64_t D = uint64_t(TX.d[q] + L.d[q]);
-        const unsigned n = unsigned(D >> 32);
-        const bool in = n < unsigned(M);
+        const unsigned n = unsigned(D >> 32) - unsigned(W.x);  // in the window
+        const bool in = n < cnt;
         const unsigned fr = unsigned(D);
         const float w = TX.p[q] * L.p[q];
         const float z0 = fmaf(float(fr >> (32 - qs)), h, -1.0f), z1 = z0 + h;
         const float phi = float(fr << qs) * 2.3283064365386963e-10f;
         float c[R];
         if (fits) {
-          const float* s = buf + (in ? int(n) - W.x : 0);
+          const float* s = buf + (in ? n : 0u);
 #pragma unroll
           for (int p = 0; p < R; ++p) c[p] = s[p * plane];
         } else {
