@@ -416,8 +416,9 @@ int umbir_get_dims(const umbir_geometry* geom, umbir_dims* out);
  * outside the values above).  The tuning of
  * a geometry must not change while another call uses it.
  * umbir_autotune times candidates of each field on `stream` (an A + A^T pair
- * for the form, the forward for the splat and the convolution, the adjoint
- * for the correlation and the gather, a dense all-ones image), applies the
+ * for the form; on the fine grid the forward for the splat and the
+ * convolution and the adjoint for the correlation and the gather, where
+ * anything runs on it; a dense all-ones image), applies the
  * fastest and writes the chosen values to *chosen (may be NULL); it allocates
  * its own workspace and synchronizes the stream.  Errors: EINVAL, ENOMEM,
  * EDEVICE. */

@@ -2903,10 +2903,9 @@ int umbir_autotune(umbir_geometry* G, void* stream, umbir_tuning* chosen) {
     *ms /= 3.0f;
     return r;
   };
-  auto forward = [&]() {
-    return run_forward(*G, nullptr, traces, nullptr, 1.0f, nullptr, false, moments_on(*G), fine, s);
-  };
-  auto adjoint = [&]() { return run_adjoint(*G, traces, img, 1.0f, false, moments_on(*G), fine, partial, s); };
+  bool mom = false;
+  auto forward = [&]() { return run_forward(*G, nullptr, traces, nullptr, 1.0f, nullptr, false, mom, fine, s); };
+  auto adjoint = [&]() { return run_adjoint(*G, traces, img, 1.0f, false, mom, fine, partial, s); };
   // the operator's form: factored (splat + convolution, correlation +
   // gather) or direct, for an A + A^T pair with the current launch shapes
   if (direct_eligible(*G)) {
@@ -2914,6 +2913,7 @@ int umbir_autotune(umbir_geometry* G, void* stream, umbir_tuning* chosen) {
     float best_pair = 3.4e38f;
     for (int f : {1, 2}) {
       G->form = f;
+      mom = moments_on(*G);
       float ms = 0.0f;
       if ((st = time_ms([&]() {
              int r = forward();
@@ -2924,6 +2924,10 @@ int umbir_autotune(umbir_geometry* G, void* stream, umbir_tuning* chosen) {
     }
     G->form = best_form;
   }
+  // the shapes below are the fine grid's: where nothing runs on it (moments
+  // throughout, or the direct form) they are left alone, else timed on it
+  const bool shapes = G->form == 1 && !abs_moments_on(*G);
+  mom = false;
   // the splat: one to four chunks per trace, and fixed workgroup targets
   const long PK = G->traces();
   std::vector<long> cand = {PK, 2 * PK, 4 * PK, 1024, 2048, 4096};
@@ -2932,6 +2936,7 @@ int umbir_autotune(umbir_geometry* G, void* stream, umbir_tuning* chosen) {
   long best_blocks = G->splat_blocks;
   float best = 3.4e38f;
   for (long c : cand) {
+    if (!shapes || st) break;
     apply_splat_blocks(G, c);
     float ms = 0.0f;
     if ((st = time_ms(forward, &ms))) break;
@@ -2940,7 +2945,7 @@ int umbir_autotune(umbir_geometry* G, void* stream, umbir_tuning* chosen) {
   apply_splat_blocks(G, best_blocks);
   // the matrix-core convolution's output tiles per workgroup and tile order
   // (FP32, Q of 32 or 64)
-  if (!st && G->storage == UMBIR_STORAGE_F32 && (G->Q == 32 || G->Q == 64)) {
+  if (!st && shapes && G->storage == UMBIR_STORAGE_F32 && (G->Q == 32 || G->Q == 64)) {
     int best_grid = G->conv_grid, best_tiles = G->conv_tiles;
     best = 3.4e38f;
     for (int nt : {1, 2, 4}) {
@@ -2958,7 +2963,7 @@ int umbir_autotune(umbir_geometry* G, void* stream, umbir_tuning* chosen) {
   }
   // the matrix-core correlation's tile rows per wave (FP32 products only:
   // the bf16-piece form has one tile shape) and workgroup count
-  if (!st && G->storage == UMBIR_STORAGE_F32 && (G->Q == 32 || G->Q == 64)) {
+  if (!st && shapes && G->storage == UMBIR_STORAGE_F32 && (G->Q == 32 || G->Q == 64)) {
     int best_t = G->corr_tiles, best_b = G->corr_blocks;
     best = 3.4e38f;
     const bool one_shape = corr_split(*G);
@@ -2982,7 +2987,7 @@ int umbir_autotune(umbir_geometry* G, void* stream, umbir_tuning* chosen) {
   best = 3.4e38f;
   for (int gf = 1; gf <= (G->gwin ? 2 : 1); ++gf)
     for (int kb : {2048, 4096, 8192, 16384, 32768}) {
-      if (st) break;
+      if (st || !shapes) break;
       G->gather_form = gf;
       G->gather_batch_kb = kb;
       float ms = 0.0f;
