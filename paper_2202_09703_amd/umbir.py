@@ -222,9 +222,11 @@ class Geometry:
     @property
     def shape_key(self):
         """What the launch- and tile-shape tuning depends on (window L_h, record
-        M, traces P x K, grid nz x nx, storage, and the rest of the shape)."""
+        M, traces P x K, grid nz x nx, storage, and the rest of the shape; the
+        bytes of the tables tell geometries that run as moments, with or
+        without the curvature, from those of the same shape that do not)."""
         return (self.nx, self.nz, self.n_scans, self.n_rx, self.n_samples, self.oversample, self.window,
-                self.n_layers, self.storage, self.n_gamma)
+                self.n_layers, self.storage, self.n_gamma, self.bytes)
 
     def tuning(self) -> dict:
         t = _Tuning()

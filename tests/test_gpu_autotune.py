@@ -58,3 +58,12 @@ def test_shapes_of_a_fine_grid_curvature_are_timed_on_the_fine_grid():
     if chosen["operator_form"] == 1:
         assert n["gather"] > n["reduce_groups"] > 8  # the moment gather is one launch
     geom.free()
+
+
+def test_a_cache_tells_the_routes_apart():
+    keys = set()
+    for kw in (dict(), dict(beta=7), dict(shift=MM)):
+        geom = umbir.build_geometry(card(**kw))
+        keys.add(geom.shape_key)
+        geom.free()
+    assert len(keys) == 3
