@@ -102,13 +102,18 @@ constexpr int kPlanChunk = 64;
 // Bins a plan block holds in LDS at a time; a block takes slice blockIdx.z.
 constexpr int kPlanSlice = 36864;
 
-// counts[j][chunk][b]: records of receiver j and the chunk's relative columns
-// in bin b (of NB = NG M).
+// Bytes of the histograms: as many receivers at a time as fit, with one launch
+// of each of the three kernels per such part (one part up to 64 receivers, 16
+// chunks and 16384 bins).
+constexpr size_t kPlanCountBytes = size_t(256) << 20;
+
+// counts[j - j0][chunk][b]: records of receiver j and the chunk's relative
+// columns in bin b (of NB = NG M); j0: the part's first receiver.
 __global__ __launch_bounds__(1024) void k_plan_count(const Leg* __restrict__ legs, const double* __restrict__ gunit,
-                                                    const int* __restrict__ base, MomentShape ms, int P, int K, int nz,
-                                                    int n_off, int M, int* __restrict__ counts) {
+                                                    const int* __restrict__ base, MomentShape ms, int P, int K, int j0,
+                                                    int nz, int n_off, int M, int* __restrict__ counts) {
   extern __shared__ int hist[];
-  const int j = blockIdx.x, ch = blockIdx.y, NB = ms.NG * M;
+  const int j = j0 + blockIdx.x, ch = blockIdx.y, NB = ms.NG * M;
   const int b0 = blockIdx.z * kPlanSlice, nb = min(NB - b0, kPlanSlice);
   for (int i = threadIdx.x; i < nb; i += blockDim.x) hist[i] = 0;
   __syncthreads();
@@ -123,18 +128,18 @@ __global__ __launch_bounds__(1024) void k_plan_count(const Leg* __restrict__ leg
     if (b >= b0 && b < b0 + nb) atomicAdd(&hist[b - b0], 1);
   }
   __syncthreads();
-  int* out = counts + (size_t(j) * gridDim.y + ch) * NB + b0;
+  int* out = counts + (size_t(blockIdx.x) * gridDim.y + ch) * NB + b0;
   for (int i = threadIdx.x; i < nb; i += blockDim.x) out[i] = hist[i];
 }
 
 // Per receiver: start[j][n] (the first record of bin n of M, start[j][M] the
 // end) and, in place of each count, the first record of (chunk, n).  Records
 // of receiver j begin at j * cap.  max_bin receives the largest bin.
-__global__ __launch_bounds__(1024) void k_plan_scan(int M, int chunks, int cap, int* __restrict__ counts,
+__global__ __launch_bounds__(1024) void k_plan_scan(int M, int chunks, int cap, int j0, int* __restrict__ counts,
                                                     int* __restrict__ start, int* __restrict__ max_bin) {
   __shared__ int waves[16];
-  const int j = blockIdx.x, t = threadIdx.x, lane = t & 63;
-  int* cj = counts + size_t(j) * chunks * M;
+  const int j = j0 + blockIdx.x, t = threadIdx.x, lane = t & 63;
+  int* cj = counts + size_t(blockIdx.x) * chunks * M;
   int at = j * cap, big = 0;
   for (int n0 = 0; n0 < M; n0 += 1024) {  // 1024 bins at a time, neighbours in neighbouring threads
     const int n = n0 + t;
@@ -185,13 +190,13 @@ __global__ __launch_bounds__(1024) void k_plan_scan(int M, int chunks, int cap, 
 
 // Keys row * NR + (rel - rel0) of every record into its bin, in any order.
 __global__ __launch_bounds__(1024) void k_plan_fill(const Leg* __restrict__ legs, const double* __restrict__ gunit,
-                                                   const int* __restrict__ base, MomentShape ms, int P, int K, int nz,
-                                                   int n_off, int M, const int* __restrict__ first,
+                                                   const int* __restrict__ base, MomentShape ms, int P, int K, int j0,
+                                                   int nz, int n_off, int M, const int* __restrict__ first,
                                                    unsigned* __restrict__ keys) {
   extern __shared__ int cursor[];
-  const int j = blockIdx.x, ch = blockIdx.y, NB = ms.NG * M;
+  const int j = j0 + blockIdx.x, ch = blockIdx.y, NB = ms.NG * M;
   const int b0 = blockIdx.z * kPlanSlice, nb = min(NB - b0, kPlanSlice);
-  const int* f = first + (size_t(j) * gridDim.y + ch) * NB + b0;
+  const int* f = first + (size_t(blockIdx.x) * gridDim.y + ch) * NB + b0;
   for (int i = threadIdx.x; i < nb; i += blockDim.x) cursor[i] = f[i];
   __syncthreads();
   int bt, br;
@@ -1867,6 +1872,9 @@ MomentShape moment_shape(const MomentInput& in) {
   const double Lq = std::ceil(double(in.nx) / pitch) + 2.0 * (P - 1);
   const double recs = double(K) * in.nz * NR;
   if (recs * 4.0 * (R + 1) > 4e9 || recs > 1e9 || double(in.nz) * pitch * Lq > 1e8) return ms;
+  // the plan's grid, and its histogram of one receiver
+  const double chunks = std::ceil(NR / kPlanChunk);
+  if (chunks > 65535 || chunks * in.M * in.n_gamma * 4.0 > double(kPlanCountBytes)) return ms;
   const int LT = in.Lh + 9;
   if (size_t(R) * 3 * LT * 16 > 150u * 1024 || double(K) * in.M * in.n_gamma > 6.4e7) return ms;
   if (in.n_gamma == 1 && gather_window_bytes(in.nx, in.nz, long(P) * K, long(in.M) * Q, in.storage) == 0) return ms;
@@ -1937,14 +1945,17 @@ static std::vector<double> fit_matrix(int R, int Q, int skip = -1) {
 }
 
 // Queues the plan's kernels (G's legs, bases and tau are queued before on s);
-// scratch is allocated and freed in stream order, *max_bin (a host word that
+// scratch (a word per record, kPlanCountBytes of histograms at most, small
+// tables) is allocated and freed in stream order, *max_bin (a host word that
 // lives until the stream was synchronized) receives the largest bin.
+// UMBIR_ENOMEM: nothing was queued.
 int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s) {
   const MomentShape& ms = G->mom;
   const int R = ms.R, K = G->K, M = G->M, Q = G->Q;
   const int chunks = (ms.NR + kPlanChunk - 1) / kPlanChunk;
   const int NB = ms.NG * M;
-  const size_t n_count = size_t(K) * chunks * NB;
+  const size_t count_row = size_t(chunks) * NB;  // of one receiver
+  const int part = int(std::min<size_t>(K, std::max<size_t>(1, kPlanCountBytes / sizeof(int) / count_row)));
   std::vector<double> fit = fit_matrix(ms.NG > 1 ? 6 : R, Q);
   if (ms.NG > 1)
     for (int skip : {Q, 0}) {
@@ -1952,7 +1963,7 @@ int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s) {
       fit.insert(fit.end(), f.begin(), f.end());
     }
   const size_t fit_bytes = (fit.size() * sizeof(double) + 255) & ~size_t(255);
-  const size_t count_bytes = (n_count * sizeof(int) + 255) & ~size_t(255);
+  const size_t count_bytes = (part * count_row * sizeof(int) + 255) & ~size_t(255);
   const int g_rows = ms.NG * R * (1 + ms.absolute);
   const size_t g_bytes = (size_t(g_rows) * G->Lh * sizeof(float) + 255) & ~size_t(255);
   char* tmp = nullptr;
@@ -1967,7 +1978,7 @@ int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s) {
   unsigned* keys = reinterpret_cast<unsigned*>(tmp + fit_bytes + 256 + g_bytes + count_bytes);
   const int cap = G->nz * ms.NR;
   const size_t lds = size_t(std::min(NB, kPlanSlice)) * sizeof(int);
-  const dim3 cg{unsigned(K), unsigned(chunks), unsigned((NB + kPlanSlice - 1) / kPlanSlice)};
+  const unsigned slices = unsigned((NB + kPlanSlice - 1) / kPlanSlice);
   if (!(st = check_hip(hipMemcpyAsync(fit_dev, fit.data(), fit.size() * sizeof(double), hipMemcpyHostToDevice, s),
                        "hipMemcpyAsync(fit)"))) {
     if (ms.NG > 1)
@@ -1979,14 +1990,17 @@ int build_moments(umbir_geometry* G, int* max_bin, hipStream_t s) {
     // (the templates' rows, and those of |b|, follow one another in g and in the table)
     UMBIR_LAUNCH("moment_table", k_moment_table, dim3(unsigned((g_rows * ms.LT + 255) / 256)), dim3(256), 0, s,
                  g_rows, G->Lh, ms.LT, g, G->mom_taps, mb);
-    UMBIR_LAUNCH("plan_count", k_plan_count, cg, dim3(1024), lds, s, G->legs, G->gunit, G->base, ms, G->P, K, G->nz,
-                 G->n_off, M, counts);
-    UMBIR_LAUNCH("plan_scan", k_plan_scan, dim3(unsigned(K)), dim3(1024), 0, s, NB, chunks, cap, counts, G->mom_start,
-                 mb);
+    for (int j0 = 0; j0 < K; j0 += part) {
+      const dim3 cg{unsigned(std::min(part, K - j0)), unsigned(chunks), slices};
+      UMBIR_LAUNCH("plan_count", k_plan_count, cg, dim3(1024), lds, s, G->legs, G->gunit, G->base, ms, G->P, K, j0,
+                   G->nz, G->n_off, M, counts);
+      UMBIR_LAUNCH("plan_scan", k_plan_scan, dim3(cg.x), dim3(1024), 0, s, NB, chunks, cap, j0, counts, G->mom_start,
+                   mb);
+      UMBIR_LAUNCH("plan_fill", k_plan_fill, cg, dim3(512), lds, s, G->legs, G->gunit, G->base, ms, G->P, K, j0, G->nz,
+                   G->n_off, M, counts, keys);
+    }
     if (ms.NG > 1)
       UMBIR_LAUNCH("plan_span", k_plan_span, dim3(unsigned(ms.NG)), dim3(256), 0, s, G->mom_start, K, M, NB, G->mom_span);
-    UMBIR_LAUNCH("plan_fill", k_plan_fill, cg, dim3(512), lds, s, G->legs, G->gunit, G->base, ms, G->P, K, G->nz,
-                 G->n_off, M, counts, keys);
     with_r(R, [&](auto rc) {
       UMBIR_LAUNCH("plan_emit", k_plan_emit<decltype(rc)::value>, dim3(unsigned(K), unsigned((NB + 3) / 4)), dim3(256),
                    0, s, G->legs, G->base, G->tau, ms, G->P, K, G->n_off, log2_int(Q), NB, G->mom_start, keys, mb,
