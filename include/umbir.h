@@ -165,7 +165,12 @@ int umbir_build_geometry(const umbir_problem* problem, void* stream, umbir_geome
 void umbir_geometry_free(umbir_geometry* geom);
 
 /* Device bytes held by a geometry, and an estimate for a problem before it is
- * built (0 if the problem is invalid).  Workspace is not included. */
+ * built (0 if the problem is invalid).  Workspace is not included, nor what
+ * the build itself needs and gives back: for the tables of the moment form
+ * (see umbir_tuning) a word per record, K nz (nx + (P - 1) scan step in
+ * voxels) of them, and up to 256 MiB.  Where those tables or this scratch find
+ * no memory, or a sample has more than 8192 records, the geometry keeps the
+ * fine grid and holds fewer bytes than estimated. */
 size_t umbir_geometry_bytes(const umbir_geometry* geom);
 size_t umbir_estimate_bytes(const umbir_problem* problem);
 

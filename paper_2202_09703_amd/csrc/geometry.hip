@@ -840,20 +840,43 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
                  size_t(G->mask_blocks) * sizeof(unsigned long long), s, G->legs, G->gunit, G->n_off, G->base, G->P,
                  G->K, G->nx, G->voxels(), qs, MQ, NG - 1, G->mask_blocks, G->gmask);
   }
-  // the moment form's tables, where the geometry takes it
+  // the moment form's tables, where the geometry takes it and they fit in
+  // memory (the fine grid serves without them)
+  auto drop_moments = [&]() {
+    if (G->mom_rec4) {
+      G->bytes -= G->mom.table_bytes;
+      (void)hipFree(G->mom_rec4);
+    }
+    G->mom_rec4 = nullptr;
+    G->mom_rec_hi = nullptr;
+    G->mom_taps = nullptr;
+    G->mom_start = nullptr;
+    G->mom_span = nullptr;
+    G->mom = MomentShape{};
+  };
   if (NG == dv.n_gamma) G->mom = moment_shape(moment_input(pb, dv));
   int max_bin = 0;
   if (G->mom.R) {
     const MomentShape& ms = G->mom;
     char* t = nullptr;
-    if ((st = alloc((void**)&t, ms.table_bytes))) return bail(st);
-    G->mom_rec4 = reinterpret_cast<float4*>(t);
-    G->mom_rec_hi = reinterpret_cast<float*>(t + ms.hi_at);
-    G->mom_taps = reinterpret_cast<uint4*>(t + ms.taps_at);
-    G->mom_start = reinterpret_cast<int*>(t + ms.start_at);
-    G->mom_span = reinterpret_cast<int2*>(t + ms.span_at);
-    if ((st = build_moments(G, &max_bin, s)))
-      return bail(st);
+    const hipError_t e = hipMalloc((void**)&t, ms.table_bytes);
+    if (e == hipSuccess) {
+      G->bytes += ms.table_bytes;
+      G->mom_rec4 = reinterpret_cast<float4*>(t);
+      G->mom_rec_hi = reinterpret_cast<float*>(t + ms.hi_at);
+      G->mom_taps = reinterpret_cast<uint4*>(t + ms.taps_at);
+      G->mom_start = reinterpret_cast<int*>(t + ms.start_at);
+      G->mom_span = reinterpret_cast<int2*>(t + ms.span_at);
+      st = build_moments(G, &max_bin, s);
+    } else {
+      st = check_hip(e, "hipMalloc(moments)");
+    }
+    if (st == UMBIR_ENOMEM) {
+      (void)hipGetLastError();  // handled here
+      drop_moments();
+      st = UMBIR_OK;
+    }
+    if (st) return bail(st);
   }
   if (gam_dev) (void)hipFreeAsync(gam_dev, s);
   if (nodes_dev) (void)hipFreeAsync(nodes_dev, s);
@@ -861,16 +884,7 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
   (void)hipFreeAsync(td_dev, s);
   const int st2 = check_hip(hipStreamSynchronize(s), "hipStreamSynchronize(build_geometry)");
   if (!st) st = st2;
-  if (!st && !moment_plan_fits(max_bin)) {  // the fine grid stays
-    G->bytes -= G->mom.table_bytes;
-    (void)hipFree(G->mom_rec4);
-    G->mom_rec4 = nullptr;
-    G->mom_rec_hi = nullptr;
-    G->mom_taps = nullptr;
-    G->mom_start = nullptr;
-    G->mom_span = nullptr;
-    G->mom = MomentShape{};
-  }
+  if (!st && !moment_plan_fits(max_bin)) drop_moments();  // the fine grid stays
   if (st) {
     umbir_geometry_free(G);
     return st;

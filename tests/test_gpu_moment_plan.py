@@ -1,6 +1,6 @@
 """The moment form's tables: built in parts where their histograms are large,
-and left out, with the fine grid in their place, where a sample has too many
-records.
+and left out, with the fine grid in their place, where they find no memory or a
+sample has too many records.
 
 Tolerance: as for the other tests of the moment form, 2e-6 relative L2."""
 import dataclasses
@@ -70,4 +70,28 @@ def test_too_many_records_of_a_sample():
     vox = np.arange(0, 512 * 512, 3001)
     assert rel(y, oo.forward(c, x.numpy().astype(np.float64))) <= TOL
     assert rel(xa.reshape(-1)[vox], oo.adjoint_voxels(c, r.numpy().astype(np.float64), vox)) <= TOL
+    geom.free()
+
+
+def test_no_memory_for_the_tables():
+    """A device with 1 GiB left: the tables (1.6 GB) do not fit, the rest of the
+    geometry (0.1 GB) does, so it is built, on the fine grid."""
+    c = card(512, 512, 64, 128, 64, step=8, spread=4)
+    full = umbir.build_geometry(c)
+    assert full.bytes - 1.2e9 < 0.5e9 < 1.2e9 < full.bytes
+    x, r, y, xa = pair(full)
+    full.free()
+    torch.cuda.empty_cache()
+    torch.cuda.synchronize()
+    free, _ = torch.cuda.mem_get_info()
+    filler = torch.empty(free - (1 << 30), dtype=torch.uint8, device="cuda")
+    try:
+        geom = umbir.build_geometry(c)
+    finally:
+        del filler
+        torch.cuda.empty_cache()
+    assert geom.bytes < 0.5e9 and umbir.estimate_bytes(c) > 1.2e9
+    _, _, y1, xa1 = pair(geom)
+    assert not torch.equal(y, y1)
+    assert rel(y1, y) <= TOL and rel(xa1, xa) <= TOL
     geom.free()
