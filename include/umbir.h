@@ -276,7 +276,9 @@ size_t umbir_icd_workspace_bytes(const umbir_geometry* geom, int group_rows, int
  * umbir_solver_read: queues copies of the current x and g (either may be
  *   NULL) and, if cost_dev is not NULL, evaluates the cost of the current
  *   state and copies iterations() + 1 history entries (float64) to cost_dev.
- * umbir_solver_bytes: device bytes a session would hold (for admission).
+ * umbir_solver_bytes: device bytes a session would hold (for admission) if it
+ *   were created with the geometry's present tuning: one that runs wholly as
+ *   moments (see umbir_tuning) holds those, not the fine grid.
  * One session must not be stepped from two streams at once. */
 typedef struct umbir_solver umbir_solver;
 size_t umbir_solver_bytes(const umbir_geometry* geom, int max_iter);
@@ -344,7 +346,7 @@ typedef struct {
 int umbir_get_dims(const umbir_geometry* geom, umbir_dims* out);
 
 /* Launch and tile shapes of the sweeps, tunable per problem shape.  None
- * changes a result beyond rounding order, nor any memory size.  Where the
+ * changes a result beyond rounding order, nor any workspace size.  Where the
  * factored form with bf16-piece products (both defaults) runs as moments (FP32
  * storage, one template, scan positions a constant whole number of voxels
  * apart, Q >= 16 and a pulse that a polynomial of degree 7 or less follows over

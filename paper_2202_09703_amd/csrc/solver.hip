@@ -408,11 +408,15 @@ struct IterBuffers {
   bool mom;  // runs as moments, decided here once: the image the prior update leaves for the next forward is that form's
 };
 
+// What an iteration and the curvature before it need of the fine workspace:
+// where both run as moments, theirs.
+size_t iter_fine_bytes(const umbir_geometry& G) { return abs_moments_on(G) ? G.mom.work_bytes : G.fine_bytes(); }
+
 IterBuffers carve_iter(Carve& cv, const umbir_geometry& G) {
   const size_t N = G.voxels(), PK = G.traces();
   IterBuffers b;
   b.nblk = int((N + kPriorVox - 1) / kPriorVox);
-  b.fine = cv.take<char>(G.fine_bytes());
+  b.fine = cv.take<char>(iter_fine_bytes(G));
   b.partial = cv.take<float>(size_t(G.trace_groups) * N);
   b.e = cv.take<char>(G.trace_bytes());
   b.den = cv.take<float>(N);
@@ -808,11 +812,13 @@ struct umbir_batch {
 
 namespace {
 
+// (iter_bytes, the caller's workspace, does not depend on the tuning: it holds
+// the whole fine grid)
 size_t solver_bytes(const umbir_geometry& G, int max_iter) {
   const size_t N = G.voxels(), PK = G.traces();
-  return iter_bytes(G) + aligned(G.trace_bytes()) + 2 * aligned(N * sizeof(float)) +
-         aligned(PK * sizeof(float)) + aligned((size_t(max_iter) + 1) * sizeof(double)) + aligned(sizeof(int)) +
-         8 * 256;
+  return iter_bytes(G) - aligned(G.fine_bytes()) + aligned(iter_fine_bytes(G)) + aligned(G.trace_bytes()) +
+         2 * aligned(N * sizeof(float)) + aligned(PK * sizeof(float)) +
+         aligned((size_t(max_iter) + 1) * sizeof(double)) + aligned(sizeof(int)) + 8 * 256;
 }
 
 void solver_release(umbir_solver* S) {

@@ -95,3 +95,26 @@ def test_no_memory_for_the_tables():
     assert not torch.equal(y, y1)
     assert rel(y1, y) <= TOL and rel(xa1, xa) <= TOL
     geom.free()
+
+
+def test_sessions_of_moments_hold_no_fine_grid():
+    """A session that runs wholly as moments and its geometry's tables together
+    need less than the same problem on the fine grid (an uneven scan), so a
+    memory budget admits no fewer sessions; it gives umbir_reconstruct's
+    result."""
+    c = dataclasses.replace(card(96, 80, 6, 8, 1100, step=4), n_iter=4)
+    uneven = dataclasses.replace(c, array=dataclasses.replace(c.array, tx_x=c.array.tx_x[:-1] + (19 * MM,)))
+    need = []
+    for cc in (c, uneven):
+        geom = umbir.build_geometry(cc)
+        need.append(geom.bytes + umbir.solver_bytes(geom, 4))
+        y = torch.tensor(random_vector(geom.trace_shape, seed=93), dtype=torch.float32, device="cuda")
+        x, g, cost = umbir.reconstruct(geom, cc.prior, 0.5, y, 4)
+        s = umbir.Solver(geom, cc.prior, 0.5, y, 4)
+        assert s.bytes == umbir.solver_bytes(geom, 4)
+        s.step(4)
+        xs, gs, cs = s.read()
+        assert torch.equal(xs, x) and torch.equal(gs, g) and torch.equal(cs, cost)
+        s.free()
+        geom.free()
+    assert need[0] < need[1]
