@@ -855,6 +855,11 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
     G->mom = MomentShape{};
   };
   if (NG == dv.n_gamma) G->mom = moment_shape(moment_input(pb, dv));
+  // Its workspace shares the fine grid's and may not outgrow it by more than a
+  // trifle (records of a few samples rounded up to 32): the image by phase is
+  // 2 (P - 1) steps wider than the grid, which few traces over scan positions
+  // far apart do not make up for.
+  if (G->mom.work_bytes > std::max(G->grid_work_bytes(), size_t(1) << 20)) G->mom = MomentShape{};
   int max_bin = 0;
   if (G->mom.R) {
     const MomentShape& ms = G->mom;

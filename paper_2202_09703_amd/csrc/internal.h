@@ -309,8 +309,11 @@ struct umbir_geometry {
   // the fine-grid workspace: the grid(s), then the forward's prescaled image
   // and the prescale blocks' maxima; the moment form's u or v and its image
   // share the bytes
+  size_t grid_work_bytes() const {
+    return grids_bytes() + ((size_t(nx) * nzp * 4 + 15) & ~size_t(15)) + 4 * umbir::kPrescaleBlocks;
+  }
   size_t fine_bytes() const {
-    const size_t fine = grids_bytes() + ((size_t(nx) * nzp * 4 + 15) & ~size_t(15)) + 4 * umbir::kPrescaleBlocks;
+    const size_t fine = grid_work_bytes();
     return fine > mom.work_bytes ? fine : mom.work_bytes;
   }
   size_t prescale_max_offset() const { return grids_bytes() + ((size_t(nx) * nzp * 4 + 15) & ~size_t(15)); }
