@@ -657,6 +657,9 @@ int umbir_build_geometry(const umbir_problem* pb, void* stream, umbir_geometry**
         prev = l;
       }
       G->seg_hi[G->n_seg - 1] = r + 1;
+      double t = 0.0;
+      for (int k = 0; k <= l; ++k) t += (std::min(z, G->layers.bottom[k]) - G->layers.top[k]) / G->layers.speed[k];
+      if (2.0 * t * G->fs < G->M) G->rows_in_record = r + 1;
     }
     apply_splat_blocks(G, G->splat_blocks);
     // output tiles per convolution workgroup: with FP32 products two when

@@ -284,6 +284,7 @@ struct umbir_geometry {
   float* mom_rec_hi = nullptr;      // [records][R - 3] the others, then the byte offset in the image by phase
   uint4* mom_taps = nullptr;        // [NG][R][3][LT], with mom.absolute then those of |b|
   int2* mom_span = nullptr;         // [NG] first sample with a record and the one past the last (attenuation)
+  int rows_in_record = 0;           // rows whose echo straight down begins within the record
   size_t bytes = 0;
 
   int traces() const { return P * K; }

@@ -1232,13 +1232,24 @@ int umbir_reconstruct_icd(const umbir_geometry* G, const umbir_prior* pr, const 
   const int n_groups = Sr * Sc;
   // The sweeps as moments from 768 members in the largest group on: the dense
   // products cost the same for any group, the window dots and updates a
-  // member's window each.  Per group, moments against windows: 79 against 114
-  // us with 1024 members at 256 x 256 voxels, 512 traces of 2048 samples (70
-  // against 66 with 441, 117 against 374 with 4096), 42 against 62 us with 1024
-  // at 128 x 128, 128 traces (39 against 38 with 441), 33 against 38 us with
-  // 1024 at 64 x 64, 8 traces (30 against 25 with 441).  The curvatures
-  // likewise, where |A| has moments.
-  const bool mom = moments_on(*G) && gmax >= 768;
+  // member's window each.  A thread walks its member's window, so a short one
+  // counts twice, and members past the record cost nothing: the members in the
+  // record (at most those of the rows whose echo straight down is) times the
+  // window squared from 8e6 on.  Us per group and sweep, moments against
+  // windows, members (in the record):
+  //   window 240, 512 traces of 2048: 74 : 114 at 1024, 69 : 87 at 754,
+  //     67 : 67 at 484; 8 traces of 512: 32 : 38 at 841 (210)
+  //   window 120 (10 MHz), 8 traces of 1024: 28 : 37 at 841; 8 of 256: 27 : 26
+  //     at 1024 (260), 30 : 31 at 2752 (690), 34 : 41 at 4096 (1030)
+  //   window 60 (2 MHz pulse), 512 traces of 1024: 56 : 35 at 841 (460), 73 :
+  //     69 at 2752 (1500), 84 : 98 at 4096 (2250); 8 traces 27 : 21, 30 : 34,
+  //     36 : 46
+  // Below 8 traces 768 members alone decide (6 traces of 2900, window 60: 31 :
+  // 23 at 841, most of it launches).  The curvatures likewise, where |A| has
+  // moments.
+  const double in_record = double(gmax) * G->rows_in_record / G->nz;
+  const bool mom = moments_on(*G) && gmax >= 768 &&
+                   (G->traces() < 8 || in_record * G->Lh * G->Lh >= 8e6);
 
   const size_t lds_dots = (size_t(M) + QLh + 2) * sizeof(float);
   const size_t lds_scatter = size_t(M) * sizeof(unsigned long long) + (size_t(QLh) + 2) * sizeof(float);
