@@ -95,10 +95,15 @@ typedef struct {
  * than the sampling grid and interpolated linearly between grid points;
  * Q must be a power of two in 1..64.
  * `storage` is the element type of every trace buffer (y, r, residuals), of
- * the tabulated pulse as the sweeps use it and of the fine-grid workspace:
- * UMBIR_STORAGE_F32, _F16 (IEEE half) or _BF16 (bfloat16, passed as 16-bit
- * words).  Images, direct-arrival weights and all accumulation stay FP32 and
- * the leg search FP64 in every mode.  16-bit storage needs Q = 32 or 64. */
+ * the tabulated pulse as the fine-grid sweeps use it and of the fine-grid
+ * workspace: UMBIR_STORAGE_F32, _F16 (IEEE half) or _BF16 (bfloat16, passed as
+ * 16-bit words).  Images, direct-arrival weights and all accumulation stay
+ * FP32 and the leg search FP64 in every mode.  16-bit storage needs Q = 32 or
+ * 64.  A forward alone (umbir_forward) runs as moments where the geometry takes
+ * them (see umbir_tuning): then only its result is rounded to 16 bits, once,
+ * and it is nearer the exact sum than the A of a reconstruction and the
+ * transpose of umbir_adjoint, which keep the 16-bit table and fine grid; all of
+ * them agree to the rounding of the type. */
 enum { UMBIR_STORAGE_F32 = 0, UMBIR_STORAGE_F16 = 1, UMBIR_STORAGE_BF16 = 2 };
 typedef struct {
     int n_samples;             /* M >= 1 */
@@ -115,10 +120,12 @@ typedef struct {
      * largest one-way path attenuation sum_l alpha_l eta_l / cos(theta_l) of
      * the problem's legs, and each pair uses the template nearest its gamma,
      * floor((Gamma_tx + Gamma_rx) / dgamma + 1/2) in float64 (at most
-     * n_gamma - 1).  The forward runs one
-     * splat + convolution per template; the adjoint one correlation per
-     * template, each into its own resident fine grid (its workspace grows
-     * n_gamma-fold), then one gather over all of them. */
+     * n_gamma - 1).  On the fine grid the forward runs one splat +
+     * convolution per template and the adjoint one correlation per template,
+     * each into its own resident grid, then one gather over all of them.  So
+     * do reconstructions and the curvature; a forward or an adjoint alone runs
+     * as moments per template where the geometry takes them (see
+     * umbir_tuning).  The workspace holds the grids: it grows n_gamma-fold. */
     int n_gamma;
 } umbir_acq;
 
@@ -187,7 +194,7 @@ int umbir_forward(const umbir_geometry* geom, const float* x_dev, void* y_dev,
                   int accumulate, void* work, size_t work_bytes, void* stream);
 
 /* x = A^T r, the exact transpose of umbir_forward (same W, delays and
- * interpolation).  r_dev: [P][K][M]; x_dev: [nz][nx].  Deterministic: the
+ * interpolation; with 16-bit storage to the rounding of the type).  r_dev: [P][K][M]; x_dev: [nz][nx].  Deterministic: the
  * same inputs give bitwise the same output. */
 int umbir_adjoint(const umbir_geometry* geom, const void* r_dev, float* x_dev,
                   void* work, size_t work_bytes, void* stream);
@@ -347,12 +354,14 @@ int umbir_get_dims(const umbir_geometry* geom, umbir_dims* out);
 
 /* Launch and tile shapes of the sweeps, tunable per problem shape.  None
  * changes a result beyond rounding order, nor any workspace size.  Where the
- * factored form with bf16-piece products (both defaults) runs as moments (FP32
- * storage, one template, scan positions a constant whole number of voxels
- * apart, Q >= 16 and a pulse that a polynomial of degree 7 or less follows over
- * a sample period to 1e-8 of its peak), the launch and tile shapes and the
- * gather's form concern only the curvature of a pulse whose zeros fall between
- * samples; with attenuation, what is not a forward or an adjoint alone:
+ * factored form with bf16-piece products (both defaults) runs as moments (scan
+ * positions a constant whole number of voxels apart, Q >= 16, at most 16384
+ * samples, a pulse that a polynomial of degree 7 or less follows over a sample
+ * period to 1e-8 of its peak, tables that fit), the launch and tile shapes and
+ * the gather's form have no effect.  They concern what keeps the fine grid: the
+ * curvature of a pulse whose zeros fall between samples or of an odd beta; with
+ * attenuation, what is not a forward or an adjoint alone; with 16-bit storage,
+ * what is not a forward alone:
  *  splat_blocks     target workgroup count of the splat: the fine grid of each
  *                   trace is cut into ceil(splat_blocks / traces) chunks of at
  *                   least 1024 positions.  Results are bitwise identical for

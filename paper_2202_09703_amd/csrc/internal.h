@@ -44,10 +44,11 @@ constexpr int kMaskShift = 10;
 
 __host__ __device__ __forceinline__ int leg_slot(int o, int half) { return (o >> 1) + (o & 1) * half; }
 
-// The windowed gather (FP32 fine grid): voxel tiles of kGatherTileRows x
-// kGatherTileCols, and for every (tile, trace) the window of fine positions
-// its voxels read, staged in LDS when it fits kGatherWinBytes (16384 FP32 or
-// 32768 16-bit positions); windows start and end on 16-byte boundaries
+// The windowed gathers (of the fine grid and of moments): voxel tiles of
+// kGatherTileRows x kGatherTileCols, and for every (tile, trace) the window of
+// fine positions its voxels read, staged in LDS: of the fine grid when it fits
+// kGatherWinBytes (16384 FP32 or 32768 16-bit positions), of moments see
+// k_mgather; windows start and end on 16-byte boundaries of the fine grid
 // (gather_window_align positions).
 constexpr int kGatherTileRows = 32, kGatherTileCols = 64, kGatherWinBytes = 65536;
 inline int gather_window_align(int storage) { return storage == UMBIR_STORAGE_F32 ? 4 : 8; }

@@ -581,7 +581,7 @@ __global__ __launch_bounds__(64 * kMsWaves) void k_msplat(const float* __restric
 // attenuation.  The fine-grid form fills one dense grid per template: 512
 // traces of 65536 positions in 16 templates are 2.1 GB, and writing and reading
 // them took 1158 and 1328 us at 256 x 256; u (0.5 GB at most, the spans' share
-// of it) takes 139 and 257 us.
+// of it) takes 139 and 255 us.
 __global__ __launch_bounds__(64 * kMsWaves) void k_msplat_att(const float* __restrict__ xp, int xp_bytes,
                                                               const int* __restrict__ start,
                                                               const float4* __restrict__ rec4,
@@ -897,10 +897,11 @@ __device__ __forceinline__ void mcorr_shared_steps(int bx, int by, const float* 
 // launch's): the waves share the moments, ceil(R NT / 8) each over all of the
 // window, so that there are no sums to add up between them; each splits the
 // samples for itself.  8.8 against 12.9 us for 8 traces of 256 samples (10 MHz,
-// between events around the launch).  With four tiles the running sum of a
-// whole window in one wave rounds more (2.5e-7 against 2.0e-7 relative L2 of the
-// adjoint at 256 x 256); adding each step by itself, as here, takes registers
-// that halve the blocks of a CU (165 against 142 us at 512 x 512).
+// between events around the launch).  With four tiles, moments per wave left the
+// adjoint at 256 x 256 at 2.5e-7 with running sums (2.0e-7 with the steps shared,
+// 1.8e-7 since every other wave's samples are negated), and adding each step by
+// itself, as here, takes registers that halve the blocks of a CU (165 against
+// 142 us at 512 x 512).
 template <int R, int NT, bool PAIR>
 __device__ __forceinline__ void mcorr_shared_moments(int bx, int by, const float* __restrict__ r,
                                                      const uint4* __restrict__ F, int LT, int M, int Lh, int PK,
@@ -1022,13 +1023,14 @@ __global__ __launch_bounds__(64 * kMcWaves) void k_mcorr_att(const float* __rest
 // one row of tiles of 16 at 512 x 512, 4096 samples, where a third of them read
 // from memory paced the whole launch, 1345 us against 1088 us staged.  A
 // block's tiles lie a whole generation of blocks apart, so that no block has
-// two of them: 927 us.  (Tiles that stop at layers' faces instead: 1160 us, and
-// 12 % more of them.)  Bound by its vector instructions (34 per wave and
+// two of them: 927 us, and 880 as it stands.  (Tiles that stop at layers' faces
+// instead: 1160 us, and 12 % more of them.)  Bound by its vector instructions (34 per wave and
 // trace-voxel, 54 % of the cycles at 256 x 256), the load unit (65 %) and LDS
 // (36 %), which the barrier of each trace keeps from overlapping fully.
 // Sharing a record between voxels a pitch apart, four traces a barrier and
 // windows dealt to the waves piece by piece halved single shares of these but
-// not the time (57 .. 95 us against 57 at 256 x 256, 910 .. 1440 at 512 x 512).
+// not the time (57 .. 95 us against 57 then, 50 now, at 256 x 256; 910 .. 1440 at
+// 512 x 512).
 constexpr int kMgBufBytes = 40960;  // one window buffer; two per block, two blocks per CU
 
 template <int R>
@@ -1658,7 +1660,8 @@ int run_forward_moments(const umbir_geometry& G, const float* x, void* out, cons
     UMBIR_LAUNCH("splat", k_msplat_att, grid, dim3(64 * kMsWaves), msplat_lds<8>(ms.ls), s, xp, xp_bytes, G.mom_start,
                  G.mom_rec4, G.mom_rec_hi, G.P, G.K, G.M, ms, G.mom_span, u);
     // tiles differ in how many templates reach them: four to a block only from two
-    // blocks per CU on (at one per CU 276 us, with two tiles to a block 257)
+    // blocks per CU on (at one per CU 276 us, with two tiles to a block 257 at the
+    // time)
     const long tt = (G.traces() + 31) / 32;
     const int tiles = moment_tiles(G) == 4 && tt * ((G.M + 127) / 128) < 512 ? 2 : moment_tiles(G);
     with_tiles(tiles, [&](auto nc) {
@@ -1842,6 +1845,9 @@ MomentShape moment_shape(const MomentInput& in) {
   const double tc = 0.5 * in.t_win;
   if (std::fabs(std::sin(2.0 * M_PI * in.f_c * tc)) * std::exp(-tc * tc / (2.0 * in.sigma_t * in.sigma_t)) > 1e-9)
     return ms;
+  // 8 moments (a 2 MHz pulse at 20 MHz), 512 traces of 2048 samples at 256 x 256,
+  // against the fine grid: forward 62 for 153 us, adjoint 140 for 143, an
+  // iteration of both 204 for 294
   int R = 0;
   for (int c : {5, 6, 8})
     if (!R && 2 * c <= Q && fit_remainder(in.f_c, in.sigma_t, 0.5 / in.fs, c) <= 1e-8) R = c;
