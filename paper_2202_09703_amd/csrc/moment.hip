@@ -629,11 +629,14 @@ __device__ __forceinline__ void stage_table(uint4* tab, const uint4* __restrict_
 // roundings average out: 3.8e-7 relative L2 of the adjoint at 512 x 512, 2048
 // traces, with errors of neighbouring voxels alike.  So every other wave (ATT:
 // and template) multiplies the negated samples and is subtracted, here and in
-// the correlation: with the gather's partial sums 1.9e-7, at 544 for 541 us
-// forward and the same time back.  The items take the moments in turn so that
-// with R = 6 and 8 too each wave gets large and small ones, and both kinds of
-// wave each: the attenuated forward at 256 x 256 1.2e-7 for 1.93e-7 (1.7e-7
-// with a moment per wave), 372 for 363 us.
+// the correlation: with the gather's partial sums 1.9e-7 at the same time.  The
+// items take the moments in turn so that with R = 6 and 8 too each wave gets
+// large and small ones, and both kinds of wave each: the attenuated forward at
+// 256 x 256 1.2e-7 for 1.93e-7 (1.7e-7 with a moment per wave), 266 for 257 us.
+// Without templates an item's six products are summed by themselves, so that
+// the sum of the window is rounded once an item: 2.85e-7 before both, 2.4e-7
+// with the signs and 1.9e-7 so for a sparse image at 512 x 512 (1.86e-7 on the
+// fine grid), 21 us for 20 at 256 x 256.
 struct MomentTemplates {
   const int2* span;  // [n]
   int n;
@@ -647,7 +650,7 @@ __device__ __forceinline__ void mconv_body(int bx, int by, const float* __restri
   extern __shared__ __align__(16) float sm[];
   uint4* tab = reinterpret_cast<uint4*>(sm);
   const int tr0 = bx * 32, m0 = by * 32 * NTC;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int li = lane & 31, lk = lane >> 5;
   if constexpr (!ATT) stage_table(tab, F, R * 3 * LT);
   // the epilogue's inputs, fetched while the window multiplies: thread
@@ -696,7 +699,14 @@ __device__ __forceinline__ void mconv_body(int bx, int by, const float* __restri
       if (dj + 31 < 0 || dj - 8 > Lh + 6) continue;  // uniform: no tap meets the tile
       const int D = min(max(dj + li - 8 * lk, -1), LT - 2);
       const uint4 b[3] = {tp[D], tp[LT + D], tp[2 * LT + D]};
-      acc[j] = mfma_bf16x3(a.p, b, acc[j]);
+      if constexpr (ATT) {
+        acc[j] = mfma_bf16x3(a.p, b, acc[j]);
+      } else {
+        floatx16 t;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) t[i] = 0.0f;
+        acc[j] += mfma_bf16x3(a.p, b, t);
+      }
     }
   };
   auto window = [&]() {
@@ -819,7 +829,7 @@ __device__ __forceinline__ void mcorr_shared_steps(int bx, int by, const float* 
   constexpr int KS = kMcWaves / NT;
   uint4* tab = reinterpret_cast<uint4*>(sm);
   const int tr0 = bx * 32;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int li = lane & 31, lk = lane >> 5;
   const int jt = wave % NT, ks = wave / NT;
   const int n0 = (by * NT + jt) * 32;

@@ -62,3 +62,25 @@ def test_forward_over_16_templates(dev):
     print(f"attenuated forward, {len(traces)} traces: rel L2 {e:.2e}")
     assert e <= 2.5 * U
     geom.free()
+
+
+def test_forward_is_no_further_off_than_the_fine_grid(dev):
+    """Interfaces and point reflectors only, where a sample is a few coherent
+    terms that partly cancel: the moment form against the fine grid that it
+    stands in for, on the same traces.  Moving the last scan position makes the
+    geometry keep the fine grid and leaves the other positions' traces as they
+    are.  A quarter is allowed for the choice of traces."""
+    card = card_c3()
+    tx = card.array.tx_x
+    moved = dataclasses.replace(card, array=dataclasses.replace(card.array, tx_x=tx[:-1] + (tx[-1] + card.grid.dx,)))
+    x = torch.tensor(phantom(card), dtype=torch.float32)
+    traces = [(i, j) for i in (0, 12, 24, 36, 48, 62) for j in (0, 11, 20, 31)]
+    ref = oo.forward(card, x.numpy().astype(np.float64), traces=traces, workers=None)
+    e = []
+    for c in (card, moved):
+        geom = umbir.build_geometry(c)
+        y = umbir.forward(geom, x.to(dev)).cpu().numpy()
+        e.append(rel([y[t] for t in traces], [ref[t] for t in traces]))
+        geom.free()
+    print(f"forward of the phantom, {len(traces)} traces: rel L2 {e[0]:.2e}, fine grid {e[1]:.2e}")
+    assert e[0] != e[1] and e[0] <= 1.25 * e[1]
