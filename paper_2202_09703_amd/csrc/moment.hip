@@ -1062,7 +1062,9 @@ __device__ __forceinline__ void mgather_body(int bx, int by, const float* __rest
   const int n_tiles = tiles_x * ((nz + kGatherTileRows - 1) / kGatherTileRows);
   const int blocks = (n_tiles + tiles_per_block - 1) / tiles_per_block;
   const int half = n_off / 2;
-  const int wave = int(threadIdx.x >> 6), lane = int(threadIdx.x & 63);
+  // (the wave's number in a scalar register: the rows' offsets then take none of
+  // the 128 vector registers that four waves per SIMD leave)
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = int(threadIdx.x & 63);
   const float h = 2.0f / float(1 << qs);
   const __amdgpu_buffer_rsrc_t leg_rs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<Leg*>(legs), 0, nz * n_off * int(sizeof(Leg)), kBufferWord3);
