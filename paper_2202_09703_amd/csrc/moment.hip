@@ -624,15 +624,16 @@ __device__ __forceinline__ void stage_table(uint4* tab, const uint4* __restrict_
 // after the other, each over the samples its span reaches, each summed by
 // itself and added to the ones before.
 //
-// The matrix cores round their running sums to one side.  Per trace that is
-// less than FP32 rounding, but it adds up over the traces of an image where
-// roundings average out: 3.8e-7 relative L2 of the adjoint at 512 x 512, 2048
+// The matrix cores cut the bits of C below the products' grid towards minus
+// infinity (a sixth of the largest term's last place in the mean where C is a
+// hundredth of the products).  Per trace that is less than FP32 rounding, but it
+// adds up over the traces of an image where roundings average out: 3.8e-7 relative L2 of the adjoint at 512 x 512, 2048
 // traces, with errors of neighbouring voxels alike.  So every other wave (ATT:
 // and template) multiplies the negated samples and is subtracted, here and in
 // the correlation: with the gather's partial sums 1.9e-7 at the same time.  The
 // items take the moments in turn so that with R = 6 and 8 too each wave gets
 // large and small ones, and both kinds of wave each: the attenuated forward at
-// 256 x 256 1.2e-7 for 1.93e-7 (1.7e-7 with a moment per wave), 266 for 257 us.
+// 256 x 256 1.2e-7 for 1.93e-7 (1.7e-7 with a moment per wave), 260 for 257 us.
 // Without templates an item's six products are summed by themselves, so that
 // the sum of the window is rounded once an item: 2.85e-7 before both, 2.4e-7
 // with the signs and 1.9e-7 so for a sparse image at 512 x 512 (1.86e-7 on the
